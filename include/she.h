@@ -225,7 +225,8 @@ enum { SHE_OPT_FOLD_CONSTANTS = 1, SHE_OPT_NATIVE_MUX = 2, SHE_OPT_SPLIT_BELOW =
 int she_set_option(she_ctx *ctx, int option, int value);
 int she_get_option(she_ctx *ctx, int option, int *value);   /* SHE_EINVAL for an unknown option or a null pointer */
 /* SHE_OPT_SPLIT_BELOW (default: 6 x the device's compute units, 1536 on MI355X): a kernel launch of at
- * most this many blind rotations spreads each one over two wavefronts (one per accumulator component),
+ * most this many blind rotations spreads each one over two wavefronts (one per accumulator component) or four
+ * (one per component and half of the spectrum),
  * which shortens the serial chain per CMux when the level is too small to fill the chip; larger launches
  * keep one wavefront per rotation.  0 never splits.  Every ciphertext comes out the same word for word
  * either way (both kernels round exact integers). */

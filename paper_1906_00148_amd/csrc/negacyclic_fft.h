@@ -309,6 +309,81 @@ __host__ __device__ __forceinline__ void node_pass_inverse(double (&xr)[P], doub
     }
 }
 
+// ---- half transforms (N = 1024) ------------------------------------------------------------------------------------
+// The node-ordered transform of 512 points splits after its first stage into two transforms of 256 points that never
+// meet again: node h = 0 continues on a + w b, node h = 1 on a - w b, w = exp(i*pi/4), and ends with the frequencies
+// k = h + 2k'.  One wavefront runs one of them, 4 points per lane in four passes of two stages, so that two wavefronts
+// share a polynomial with no data between them (both read the polynomial's words, which are in LDS).  Bits of the
+// position within the half that a pass needs in the register index come from the lane index:
+//   pass A (stages 1, 2)  lane = b5 b4 b3 b2 b1 b0, register = b7 b6          -> register k1 k2
+//   swap   lane bits 5, 4 <-> register (v_permlane32_swap, v_permlane16_swap)
+//   pass B (stages 3, 4)  lane = k1 k2 b3 b2 b1 b0, register = b5 b4          -> register k3 k4
+//   LDS exchange          lane bits 3, 2 <-> register
+//   pass C (stages 5, 6)  lane = k1 k2 k3 k4 b1 b0, register = b3 b2          -> register k5 k6
+//   LDS exchange          lane bits 1, 0 <-> register, and the lane bits permuted
+//   pass D (stages 7, 8)  lane = k6 k2 k1 k5 k4 k3, register = b1 b0          -> register k7 k8
+// (highest bit first; k1..k8 are the bits of k from bit 1 up).  The last lane order makes eight consecutive lanes read
+// eight consecutive values of a key row in the order that Plan<3, 3> leaves its spectra in, whole 128-byte lines.
+struct HalfPlan {
+    static constexpr int P = 4, L = 64, M = 512, N = 1024;
+    static constexpr int XSLOTS = 4 * 68;                       // exchange slots of 16 bytes per wavefront
+    static constexpr int ROW = 64;                              // plain rows [register][lane] for whole-wavefront hand-overs
+    // Slots of the two exchanges: stored at [register][lane], read where the partner bits are.  Sixteen neighbouring
+    // lanes read sixteen slots that differ modulo 16 (rows of 68; rows of 65 with the upper lanes moved by one).
+    __host__ __device__ static constexpr int store1(int m, int t) { return m * 68 + t; }
+    __host__ __device__ static constexpr int load1(int m, int t) { return ((t >> 2) & 3) * 68 + (t & 0x33) + 4 * m; }
+    __host__ __device__ static constexpr int store2(int m, int t) { return m * 65 + t + (t >> 5); }
+    __host__ __device__ static constexpr int load2(int m, int t)
+    {
+        return (2 * ((t >> 2) & 1) + (t >> 5)) * 65 + 33 * ((t >> 3) & 1) + 16 * ((t >> 4) & 1) + 8 * (t & 1) +
+               4 * ((t >> 1) & 1) + m;
+    }
+    // Twiddle table: two entries (cos, tan) per pass and lane group, [half][entry][group]; passes B (lanes that share
+    // k1 k2), C (k1..k4), D (every lane).  Pass A's are the same for the whole wavefront.
+    static constexpr int OFF_B = 0, OFF_C = 16, OFF_D = 80, COUNT = 336;
+    __host__ __device__ static constexpr int entry(int pass, int h, int e, int t)
+    {
+        return pass == 1 ? OFF_B + (h * 2 + e) * 4 + (t >> 4)
+             : pass == 2 ? OFF_C + (h * 2 + e) * 16 + (t >> 2)
+                         : OFF_D + (h * 2 + e) * 64 + t;
+    }
+    // where the value of lane t, register m sits in a key row's component of Plan<3, 3>: 64*(k >> 6) + 8*(k & 7) + ((k >> 3) & 7)
+    __host__ __device__ static constexpr int key_lane(int h, int t) { return (t & 7) + 8 * h + 16 * ((t >> 3) & 3) + 64 * (t >> 5); }
+    __host__ __device__ static constexpr int key_reg(int m) { return 128 * (m >> 1) + 256 * (m & 1); }
+    // pass A's entries (stage 1 and 2 of node h)
+    __host__ __device__ static CosTan first_entry(int h, int e)
+    {
+        // pi/8, 5pi/8; pi/16, 5pi/16
+        constexpr CosTan v[2][2] = {{{0.92387953251128675613, 0.41421356237309504880}, {0.98078528040323044913, 0.19891236737965800691}},
+                                    {{-0.38268343236508977173, -2.41421356237309504880}, {0.55557023301960222474, 1.49660576266548901760}}};
+        return v[h][e];
+    }
+};
+
+inline void make_half_twiddles(double *out /* [HalfPlan::COUNT][2] */)
+{
+    const long double pi = 3.14159265358979323846264338327950288L;
+    for (int pass = 1; pass < 4; pass++)
+        for (int h = 0; h < 2; h++)
+            for (int t = 0; t < 64; t++) {
+                // node index: h and the frequency bits that the lane holds before this pass
+                const int b[6] = {t & 1, (t >> 1) & 1, (t >> 2) & 1, (t >> 3) & 1, (t >> 4) & 1, (t >> 5) & 1};
+                int R = h;
+                if (pass < 3) {
+                    R += 2 * b[5] + 4 * b[4];
+                    if (pass == 2) R += 8 * b[3] + 16 * b[2];
+                } else {
+                    R += 2 * b[3] + 4 * b[4] + 8 * b[0] + 16 * b[1] + 32 * b[2] + 64 * b[5];
+                }
+                for (int e = 0; e < 2; e++) {
+                    const long double ang = pi * node_angle(2 * pass + 1 + e, R);
+                    double *o = out + 2 * (size_t)HalfPlan::entry(pass, h, e, t);
+                    o[0] = (double)cosl(ang);
+                    o[1] = (double)tanl(ang);
+                }
+            }
+}
+
 template <class PL> inline void make_twiddles(double *out /* [TwTable::COUNT][2] */)
 {
     if constexpr (PL::NODES) {
@@ -498,6 +573,105 @@ __device__ __forceinline__ void inverse_halves(const LaneCtx<PL> &lc, double2 *c
 #pragma unroll
         for (int m = 0; m < PL::P; m++) { xr[b][m] *= scale; xi[b][m] *= scale; }
     }
+}
+
+// ---- half transforms on the device ---------------------------------------------------------------------------------
+// Lane bit 5 (or 4) <-> register: the upper lanes of `a` change places with the lower lanes of `b`.
+__device__ __forceinline__ void swap_lane_bit5(double &a, double &b)
+{
+    const auto lo = __builtin_amdgcn_permlane32_swap(__double2loint(a), __double2loint(b), false, false);
+    const auto hi = __builtin_amdgcn_permlane32_swap(__double2hiint(a), __double2hiint(b), false, false);
+    a = __hiloint2double(hi[0], lo[0]); b = __hiloint2double(hi[1], lo[1]);
+}
+__device__ __forceinline__ void swap_lane_bit4(double &a, double &b)
+{
+    const auto lo = __builtin_amdgcn_permlane16_swap(__double2loint(a), __double2loint(b), false, false);
+    const auto hi = __builtin_amdgcn_permlane16_swap(__double2hiint(a), __double2hiint(b), false, false);
+    a = __hiloint2double(hi[0], lo[0]); b = __hiloint2double(hi[1], lo[1]);
+}
+__device__ __forceinline__ void swap_registers_with_lane_bits54(double (&x)[4])
+{
+    swap_lane_bit5(x[0], x[2]); swap_lane_bit5(x[1], x[3]);
+    swap_lane_bit4(x[0], x[1]); swap_lane_bit4(x[2], x[3]);
+}
+
+struct HalfCtx {
+    int t, h;
+    double2 *xch;                    // this wavefront's exchange buffer (HalfPlan::XSLOTS slots)
+    const double2 *tw_b, *tw_c, *tw_d;   // this lane's entries of passes B, C, D in LDS
+    int ld1, st2, ld2;
+    CosTan ea[2];
+
+    __device__ __forceinline__ void init(int lane, int half, double2 *xbuf, const double2 *tw)
+    {
+        t = lane; h = half; xch = xbuf;
+        tw_b = tw + HalfPlan::entry(1, h, 0, t);
+        tw_c = tw + HalfPlan::entry(2, h, 0, t);
+        tw_d = tw + HalfPlan::entry(3, h, 0, t);
+        ld1 = HalfPlan::load1(0, t); st2 = HalfPlan::store2(0, t); ld2 = HalfPlan::load2(0, t);
+        for (int e = 0; e < 2; e++) ea[e] = h ? HalfPlan::first_entry(1, e) : HalfPlan::first_entry(0, e);
+    }
+    template <int PASS> __device__ __forceinline__ void entries(CosTan (&e)[2]) const
+    {
+        const double2 *p = PASS == 1 ? tw_b : PASS == 2 ? tw_c : tw_d;
+        constexpr int next = PASS == 1 ? 4 : PASS == 2 ? 16 : 64;
+        const double2 v0 = p[0], v1 = p[next];
+        e[0].c = v0.x; e[0].t = v0.y; e[1].c = v1.x; e[1].t = v1.y;
+    }
+};
+
+// The passes of a forward half transform, each with the exchange that follows it (its values are first needed by the
+// next pass, so another polynomial's pass can run while they are under way).
+// In: xr/xi[m] = position 64 m + t of the half (first stage done).  Out: frequencies in HalfPlan's last order.
+__device__ __forceinline__ void half_pass_a(const HalfCtx &hc, double (&xr)[4], double (&xi)[4])
+{
+    node_pass<4>(xr, xi, hc.ea);
+    swap_registers_with_lane_bits54(xr);
+    swap_registers_with_lane_bits54(xi);
+}
+__device__ __forceinline__ void half_pass_b(const HalfCtx &hc, double (&xr)[4], double (&xi)[4], const CosTan (&e)[2])
+{
+    node_pass<4>(xr, xi, e);
+    wave_lds_fence();
+#pragma unroll
+    for (int m = 0; m < 4; m++) hc.xch[hc.t + 68 * m] = make_double2(xr[m], xi[m]);
+    wave_lds_fence();
+#pragma unroll
+    for (int m = 0; m < 4; m++) { const double2 v = hc.xch[hc.ld1 + 4 * m]; xr[m] = v.x; xi[m] = v.y; }
+}
+__device__ __forceinline__ void half_pass_c(const HalfCtx &hc, double (&xr)[4], double (&xi)[4], const CosTan (&e)[2])
+{
+    node_pass<4>(xr, xi, e);
+    wave_lds_fence();
+#pragma unroll
+    for (int m = 0; m < 4; m++) hc.xch[hc.st2 + 65 * m] = make_double2(xr[m], xi[m]);
+    wave_lds_fence();
+#pragma unroll
+    for (int m = 0; m < 4; m++) { const double2 v = hc.xch[hc.ld2 + m]; xr[m] = v.x; xi[m] = v.y; }
+}
+
+// The mirror; out: 256 times the half's values at position 64 m + t.
+__device__ __forceinline__ void inverse_half(const HalfCtx &hc, double (&xr)[4], double (&xi)[4], const CosTan (&eb)[2],
+                                             const CosTan (&ec)[2], const CosTan (&ed)[2])
+{
+    node_pass_inverse<4>(xr, xi, ed);
+    wave_lds_fence();
+#pragma unroll
+    for (int m = 0; m < 4; m++) hc.xch[hc.ld2 + m] = make_double2(xr[m], xi[m]);
+    wave_lds_fence();
+#pragma unroll
+    for (int m = 0; m < 4; m++) { const double2 v = hc.xch[hc.st2 + 65 * m]; xr[m] = v.x; xi[m] = v.y; }
+    node_pass_inverse<4>(xr, xi, ec);
+    wave_lds_fence();
+#pragma unroll
+    for (int m = 0; m < 4; m++) hc.xch[hc.ld1 + 4 * m] = make_double2(xr[m], xi[m]);
+    wave_lds_fence();
+#pragma unroll
+    for (int m = 0; m < 4; m++) { const double2 v = hc.xch[hc.t + 68 * m]; xr[m] = v.x; xi[m] = v.y; }
+    node_pass_inverse<4>(xr, xi, eb);
+    swap_registers_with_lane_bits54(xr);
+    swap_registers_with_lane_bits54(xi);
+    node_pass_inverse<4>(xr, xi, hc.ea);
 }
 
 // Forward transform of NB independent polynomials held by the same lanes (NB register sets, NB

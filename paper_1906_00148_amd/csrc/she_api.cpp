@@ -436,6 +436,12 @@ try {
         fill_twiddles(P.N, tw.data());
         HIP_TRY(cc, hipMalloc((void **)&cc->dk.twiddles, std::max<size_t>(tw.size(), 2) * sizeof(double)));
         HIP_TRY(cc, hipMemcpy(cc->dk.twiddles, tw.data(), tw.size() * sizeof(double), hipMemcpyHostToDevice));
+        if (const size_t half = half_twiddle_doubles(P.N)) {
+            tw.resize(half);
+            fill_half_twiddles(tw.data());
+            HIP_TRY(cc, hipMalloc((void **)&cc->dk.half_twiddles, half * sizeof(double)));
+            HIP_TRY(cc, hipMemcpy(cc->dk.half_twiddles, tw.data(), half * sizeof(double), hipMemcpyHostToDevice));
+        }
         // bootstrapping key: upload integers, transform on the device, drop the integers
         uint32_t *d_bk_int = nullptr;
         HIP_TRY(cc, hipMalloc((void **)&d_bk_int, cc->hk.bk.size() * sizeof(uint32_t)));
@@ -481,7 +487,7 @@ void she_free(she_ctx *c)
 {
     if (!c) return;
     if (c->stream) hipStreamSynchronize(c->stream); else hipDeviceSynchronize();
-    hipFree(c->dk.bk_hat); hipFree(c->dk.ks); hipFree(c->dk.ks_bytes); hipFree(c->dk.twiddles);
+    hipFree(c->dk.bk_hat); hipFree(c->dk.ks); hipFree(c->dk.ks_bytes); hipFree(c->dk.twiddles); hipFree(c->dk.half_twiddles);
     if (c->pool_owned) hipFree(c->pool);
     hipFree(c->temp);
     hipFree(c->work.bar); hipFree(c->work.ext_b); hipFree(c->work.ksd);

@@ -29,6 +29,7 @@ struct DeviceKeys {
     int8_t *ks_bytes = nullptr;   // [N][4 byte planes][ks_cols][32 = 8 digits x 4 values] signed bytes (base 4, t = 8)
     uint32_t ks_cols = 0;         // n+1 rounded up to 32
     double2 *twiddles = nullptr;  // [K-1][P][L]
+    double2 *half_twiddles = nullptr;   // table of the half transforms (N = 1024)
     uint32_t ks_stride = 0;
     uint32_t cus = 1;             // compute units of the device (launch shaping)
 };
@@ -47,6 +48,8 @@ struct LevelWork {                // scratch of one level launch, sized for `gat
 bool plan_supported(uint32_t N);
 size_t twiddle_doubles(uint32_t N);
 void fill_twiddles(uint32_t N, double *host_out);
+size_t half_twiddle_doubles(uint32_t N);    // 0: no half transforms at this ring degree
+void fill_half_twiddles(double *host_out);
 size_t bk_hat_elems(const she_params &P);   // number of double2 in DeviceKeys::bk_hat
 
 hipError_t launch_bk_transform(const she_params &P, const uint32_t *d_bk_int, const DeviceKeys &K, hipStream_t st);
@@ -62,7 +65,7 @@ hipError_t launch_lincomb(const she_params &P, const CtSpace &cs, const uint8_t 
 hipError_t launch_blind_rotate(const she_params &P, const DeviceKeys &K, const CtSpace &cs, const uint32_t *d_out,
                                size_t gates, const LevelWork &W, unsigned *d_round_err /* nullptr = no tracking */,
                                hipStream_t st, bool raw = false /* write W.raw_ext instead of digits and slots */,
-                               bool split = false /* two wavefronts per gate: for levels that leave the chip underfilled */);
+                               bool split = false /* several wavefronts per gate: for levels that leave the chip underfilled */);
 // MUX m: sample = raw_ext[2m] + raw_ext[2m+1] + (0, 1/8) -> key-switch digits, body and slot initialisation of gate m
 hipError_t launch_mux_combine(const she_params &P, const DeviceKeys &K, const CtSpace &cs, const uint32_t *d_out,
                               size_t muxes, const LevelWork &W, hipStream_t st);

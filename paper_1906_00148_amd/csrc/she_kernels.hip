@@ -459,6 +459,204 @@ __global__ __launch_bounds__(128 * GB, 2) void k_blind_rotate_split(
     }
 }
 
+// ------------------------------------------------------------------------------------------
+// Blind rotation of a level of at most two gates per compute unit: one gate per workgroup of four wavefronts (N = 1024,
+// l = LR).  What bounds such a level is the length of one gate's chain of n CMuxes, so the chain is cut as far as the
+// transforms allow without a wavefront waiting for another inside one.
+// Wavefront (c, h) owns accumulator component c and half h of the spectrum (HalfPlan): it cuts the digits of all of
+// D_c = X^abar ACC_c - ACC_c, runs the first stage of its LR transforms for half h only and then LR transforms of 256
+// points, multiplies with rows c*LR.. of the key for both outputs, hands the other component's partial half spectrum to
+// wavefront (c^1, h), transforms its own component's half back, swaps the result with wavefront (c, h^1) and finishes
+// the last stage for the coefficients that it keeps in registers: those of the 256-blocks h and h + 2.
+// Nobody reads the accumulator with computed addresses: its owner writes ACC - (decomposition offset) in place and
+// X^abar ACC already rotated (8 computed addresses and signs per lane instead of 16), so D_c is one subtraction of two
+// words at fixed offsets.
+// A CMux takes 3.5 us (8300 cycles): 600 FP64 instructions per wavefront at the 2.5 ns that a wavefront alone on its SIMD
+// issues them, 190 integer ones at 2 ns, 64 lane swaps at 3.6 ns, and the LDS pipe is busy 1.3 us with the four
+// wavefronts' 40 stores and 49 loads of 1 KB each; the two overlap little, since the wavefronts run in step.
+// Measured at n = 630, ms per launch of 1 / 83 / 256 / 512 gates: 2.2 / 2.2 / 2.3 / 3.6 against 3.2 / 3.2 / 3.2 / 4.0 of
+// k_blind_rotate_split; beyond two gates per compute unit that kernel is the faster one (700 gates: 5.2 against 4.9).
+// ------------------------------------------------------------------------------------------
+template <bool TRACK, int LR>
+__global__ __launch_bounds__(256, 2) void k_blind_rotate_quad(
+    const uint16_t *__restrict__ bar, uint32_t bar_stride, uint32_t n, uint32_t bg_bit,
+    const double2 *__restrict__ bk_hat, const double2 *__restrict__ half_table, uint32_t ks_bits,
+    uint32_t *__restrict__ ext_b, uint16_t *__restrict__ ksd, unsigned *round_err, CtSpace cs,
+    const uint32_t *__restrict__ out_ids, uint32_t *__restrict__ raw_ext)
+{
+    using HP = HalfPlan;
+    constexpr int N = HP::N, L = HP::L;
+    __shared__ uint32_t s_rot[2][N], s_base[2][N];
+    __shared__ double2 s_xch[4][HP::XSLOTS], s_hand[4][4 * HP::ROW];
+    __shared__ double2 s_tw[HP::COUNT];
+
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), t = threadIdx.x & 63;
+    const int c = wave >> 1, h = wave & 1;
+    const uint32_t g = blockIdx.x;
+    for (int e = threadIdx.x; e < HP::COUNT; e += 256) s_tw[e] = half_table[e];
+    __syncthreads();
+    HalfCtx hc;
+    hc.init(t, h, s_xch[wave], s_tw);
+    const double2 *from_other = s_hand[wave ^ 2], *from_half = s_xch[wave ^ 1];
+    const uint16_t *mybar = bar + (size_t)g * bar_stride;
+
+    const uint32_t half_bg = 1u << (bg_bit - 1);
+    uint32_t dec_off = 1u << (31 - LR * bg_bit);
+    uint32_t flip = 0;      // top bit of every digit field: field ^ top, read as signed, is field - Bg/2
+#pragma unroll
+    for (int p = 1; p <= LR; p++) { dec_off += half_bg << (32 - p * bg_bit); flip |= half_bg << (32 - p * bg_bit); }
+    float worst = 0.f;
+
+    // own coefficients: v[m] at t + 64 (4h + m), v[4 + m] at t + 64 (4h + m) + 512; ACC = (0, X^(-bbar) * testv)
+    uint32_t v[8];
+    const int own = t + 256 * h;
+    {
+        const uint32_t bbar = mybar[n];
+#pragma unroll
+        for (int q = 0; q < 8; q++) {
+            const uint32_t j = own + 64 * (q & 3) + 512 * (q >> 2);
+            v[q] = c == 0 ? 0u : (((j + bbar) & N) ? 0u - (1u << 29) : (1u << 29));
+        }
+    }
+    auto publish = [&](uint32_t abar) {
+        const uint32_t x0 = 4 * ((uint32_t)own + abar);
+        char *const rot = reinterpret_cast<char *>(s_rot[c]);
+#pragma unroll
+        for (int q = 0; q < 8; q++) {
+            s_base[c][own + 64 * (q & 3) + 512 * (q >> 2)] = v[q] - dec_off;
+            const uint32_t x = x0 + 256 * (q & 3) + 2048 * (q >> 2);          // 4 * (j + abar): bit 12 is the sign
+            const uint32_t neg = (uint32_t)__builtin_amdgcn_sbfe((int)x, 12, 1);
+            *reinterpret_cast<uint32_t *>(rot + (x & (4 * N - 1))) = (v[q] ^ neg) - neg;
+        }
+    };
+
+    // Key values of one output component (o = 0: the other one, o = 1: the own one) of a step, requested as the products
+    // of the component before them free their registers.  (All 24 of a step held at once, requested at other points of
+    // the step, is no faster: 2.2 to 2.4 ms.)
+    const size_t row_elems = (size_t)2 * HP::M;
+    const int key_lane = HP::key_lane(h, t);
+    double2 kv[LR][4];
+    auto request = [&](uint32_t step, int o, int p) {
+        const double2 *row = bk_hat + ((size_t)step * 2 * LR + c * LR + p) * row_elems + (o ? c : c ^ 1) * HP::M;
+#pragma unroll
+        for (int m = 0; m < 4; m++) kv[p][m] = row[HP::key_reg(m) + key_lane];
+    };
+#pragma unroll
+    for (int p = 0; p < LR; p++) request(0, 0, p);
+    publish(mybar[0]);
+    uint32_t abar_next = mybar[1];                                            // n == 1 reads bbar: harmless
+    const double cs1 = h ? -0.70710678118654752440 : 0.70710678118654752440; // +-cos(pi/4) of the first stage
+    CosTan eb[2], ec[2], ed[2];
+    hc.entries<1>(eb); hc.entries<2>(ec); hc.entries<3>(ed);
+    for (uint32_t i = 0; i < n; i++) {
+        lds_barrier();                                                        // both arrays of both components are written
+        uint32_t dlo[8], dhi[8];
+#pragma unroll
+        for (int m = 0; m < 8; m++) {
+            dlo[m] = (s_rot[c][t + L * m] - s_base[c][t + L * m]) ^ flip;
+            dhi[m] = (s_rot[c][t + L * m + 512] - s_base[c][t + L * m + 512]) ^ flip;
+        }
+        double xr[LR][4], xi[LR][4];
+        double mr[4], mi[4], orr[4], oi[4];                                   // half spectra: own component, the other one
+        // first stage: a +- exp(i pi/4) b with a, b the positions 64 m + t and 64 m + t + 256; (1 + i) b in integers
+        auto head = [&](int p) {
+#pragma unroll
+            for (int m = 0; m < 4; m++) {
+                const uint32_t sh = 32 - (p + 1) * bg_bit;
+                const int ar = (int)__builtin_amdgcn_sbfe((int)dlo[m], sh, bg_bit), ai = (int)__builtin_amdgcn_sbfe((int)dhi[m], sh, bg_bit);
+                const int br = (int)__builtin_amdgcn_sbfe((int)dlo[m + 4], sh, bg_bit), bi = (int)__builtin_amdgcn_sbfe((int)dhi[m + 4], sh, bg_bit);
+                xr[p][m] = __builtin_fma(cs1, (double)(br - bi), (double)ar);
+                xi[p][m] = __builtin_fma(cs1, (double)(br + bi), (double)ai);
+            }
+            half_pass_a(hc, xr[p], xi[p]);
+        };
+        auto products = [&](int p, double (&ar)[4], double (&ai)[4]) {
+#pragma unroll
+            for (int m = 0; m < 4; m++) {
+                const double2 b = kv[p][m];
+                if (p == 0) {
+                    ar[m] = __builtin_fma(-xi[p][m], b.y, xr[p][m] * b.x);
+                    ai[m] = __builtin_fma(xi[p][m], b.x, xr[p][m] * b.y);
+                } else {
+                    ar[m] = __builtin_fma(-xi[p][m], b.y, __builtin_fma(xr[p][m], b.x, ar[m]));
+                    ai[m] = __builtin_fma(xi[p][m], b.x, __builtin_fma(xr[p][m], b.y, ai[m]));
+                }
+            }
+        };
+        // The exchanges of one polynomial run beside the arithmetic of the others: with the passes of all of them side by
+        // side the four wavefronts, which run in step, wait for the LDS pipe together (2.59 against 2.49 ms).
+#pragma unroll
+        for (int s = 0; s < LR + 2; s++) {
+            if (s < LR) { head(s); half_pass_b(hc, xr[s], xi[s], eb); }
+            if (s >= 1 && s - 1 < LR) half_pass_c(hc, xr[s - 1], xi[s - 1], ec);
+            if (s >= 2) {
+                node_pass<4>(xr[s - 2], xi[s - 2], ed);
+                products(s - 2, orr, oi);
+                request(i, 1, s - 2);
+            }
+        }
+#pragma unroll
+        for (int m = 0; m < 4; m++) s_hand[wave][m * HP::ROW + t] = make_double2(orr[m], oi[m]);
+        // the own component's products run while the hand-over is under way; then the next step's first values are
+        // requested (the last step's again at the end)
+#pragma unroll
+        for (int p = 0; p < LR; p++) { products(p, mr, mi); request(std::min(i + 1, n - 1), 0, p); }
+        lds_barrier();
+#pragma unroll
+        for (int m = 0; m < 4; m++) { const double2 w = from_other[m * HP::ROW + t]; mr[m] += w.x; mi[m] += w.y; }
+        inverse_half(hc, mr, mi, eb, ec, ed);
+        // the exchange buffer is free again; the partner has read it before it meets the barrier at the loop's top
+        wave_lds_fence();
+#pragma unroll
+        for (int m = 0; m < 4; m++) hc.xch[m * HP::ROW + t] = make_double2(mr[m], mi[m]);
+        lds_barrier();
+        // last stage: (y0 + y1) / 512 for half 0, conj(w) (y0 - y1) / 512 for half 1; adding 1.5*2^52 leaves the rounded
+        // value modulo 2^32 in the low word
+        constexpr double magic = 6755399441055744.0, scale = 1.0 / 512, rot = 0.70710678118654752440 / 512;
+#pragma unroll
+        for (int m = 0; m < 4; m++) {
+            const double2 w = from_half[m * HP::ROW + t];
+            double re, im, f;
+            if (h == 0) {
+                re = mr[m] + w.x; im = mi[m] + w.y; f = scale;
+            } else {
+                const double dr = w.x - mr[m], di = w.y - mi[m];
+                re = dr + di; im = di - dr; f = rot;
+            }
+            if (TRACK) {
+                worst = fmaxf(worst, (float)fabs(re * f - rint(re * f)));
+                worst = fmaxf(worst, (float)fabs(im * f - rint(im * f)));
+            }
+            v[m] += (uint32_t)__double2loint(__builtin_fma(re, f, magic));
+            v[4 + m] += (uint32_t)__double2loint(__builtin_fma(im, f, magic));
+        }
+        publish(abar_next);
+        abar_next = mybar[std::min(i + 2, n)];
+    }
+    if (TRACK && round_err) atomicMax(round_err, __float_as_uint(worst));
+
+    // sample extraction by the whole workgroup: a''_0 = A_0, a''_j = -A_{N-j}, b'' = B_0
+    lds_barrier();
+    const uint32_t body = s_base[1][0] + dec_off;
+    if (raw_ext) {
+        uint32_t *dst = raw_ext + (size_t)g * (N + 1);
+        for (int j = threadIdx.x; j < N; j += 256) dst[j] = (j == 0) ? s_base[0][0] + dec_off : 0u - (s_base[0][N - j] + dec_off);
+        if (threadIdx.x == 0) dst[N] = body;
+    } else {
+        const uint32_t rnd = 1u << (31 - ks_bits), sh = 32 - ks_bits;
+        uint16_t *dst = ksd + ((size_t)(g / KS_GROUP) * N) * KS_GROUP + (g % KS_GROUP);
+        for (int j = threadIdx.x; j < N; j += 256) {
+            const uint32_t a = (j == 0) ? s_base[0][0] + dec_off : 0u - (s_base[0][N - j] + dec_off);
+            dst[(size_t)j * KS_GROUP] = (uint16_t)((a + rnd) >> sh);
+        }
+        if (threadIdx.x == 0) ext_b[g] = body;
+        if (out_ids) {                       // the key switch subtracts its rows from (0, b'')
+            uint32_t *o = ct_ptr(cs, out_ids[g]);
+            for (uint32_t w = threadIdx.x; w <= n; w += 256) o[w] = (w == n) ? body : 0u;
+        }
+    }
+}
+
 // Second half of a native MUX: the two rotations' samples are added, 1/8 goes on the body, and the
 // sum is prepared for the key switch exactly as the blind rotation's epilogue prepares a gate.
 __global__ __launch_bounds__(256) void k_mux_combine(const uint32_t *__restrict__ raw_ext, uint32_t N, uint32_t n,
@@ -974,6 +1172,9 @@ void fill_twiddles(uint32_t N, double *out)
     }
 }
 
+size_t half_twiddle_doubles(uint32_t N) { return N == HalfPlan::N ? 2 * (size_t)HalfPlan::COUNT : 0; }
+void fill_half_twiddles(double *out) { make_half_twiddles(out); }
+
 size_t bk_hat_elems(const she_params &P) { return (size_t)P.n * 2 * P.l * 2 * (P.N / 2); }
 
 template <class PL>
@@ -1073,6 +1274,17 @@ static hipError_t blind_rotate_t(const she_params &P, const DeviceKeys &K, size_
                                  uint32_t *raw_ext, bool split)
 {
     const uint32_t ks_bits = P.ks_t * P.ks_basebit;
+    if constexpr (PL::N == HalfPlan::N) {
+        // up to two gates per compute unit: four wavefronts per gate (measured beside the kernel)
+        if (split && P.l == 3 && gates <= 2 * (size_t)K.cus) {
+#define SHE_LAUNCH_QUAD(TRACK)                                                                                        \
+    hipLaunchKernelGGL((k_blind_rotate_quad<TRACK, 3>), dim3((unsigned)gates), dim3(256), 0, st, W.bar, W.bar_stride, \
+                       P.n, P.bg_bit, K.bk_hat, K.half_twiddles, ks_bits, W.ext_b, W.ksd, d_round_err, cs, d_out, raw_ext)
+            if (d_round_err) SHE_LAUNCH_QUAD(true); else SHE_LAUNCH_QUAD(false);
+#undef SHE_LAUNCH_QUAD
+            return hipGetLastError();
+        }
+    }
     if (split) {
         // One gate (two wavefronts) or two gates per workgroup.  Measured at n=630, N=1024 on 256 compute units, in ms
         // for 256 / 512 / 768 / 1024 / 1280 / 1536 gates: one per workgroup 3.4 / 5.1 / 5.3 / 6.2 / 9.2 / 12.1, two per
