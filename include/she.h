@@ -228,7 +228,8 @@ int she_get_option(she_ctx *ctx, int option, int *value);   /* SHE_EINVAL for an
  * most this many blind rotations spreads each one over two wavefronts (one per accumulator component) or four
  * (one per component and half of the spectrum),
  * which shortens the serial chain per CMux when the level is too small to fill the chip; larger launches
- * keep one wavefront per rotation.  0 never splits.  Every ciphertext comes out the same word for word
+ * keep one wavefront per rotation, except that the rotations beyond full rounds of the chip (4 per compute unit), if
+ * they are at most two per compute unit and at most this many, run on four each.  0 never splits.  Every ciphertext comes out the same word for word
  * either way (both kernels round exact integers). */
 /* SHE_OPT_COLUMN_ADDER (default 0; needs SHE_OPT_FOLD_CONSTANTS and SHE_OPT_GATE3_CELLS, else she_shift_acc returns
  * SHE_EINVAL): she_shift_acc sums by column compression instead of adder trees and a subtraction (Section 3.3: adders

@@ -144,7 +144,7 @@ int enqueue_level_on(she_ctx *c, const LevelWork &W, bool timed, const uint8_t *
                                   c->stream));
         if (timer) HIP_TRY(c, timer->mark(c->stream));
         HIP_TRY(c, launch_blind_rotate(c->P, c->dk, cs, d_out + off, cnt, W, c->track_round ? c->d_round_err : nullptr, c->stream,
-                                       false, cnt <= c->split_below));
+                                       false, c->split_below));
         if (timer) HIP_TRY(c, timer->mark(c->stream));
         HIP_TRY(c, launch_key_switch(c->P, c->dk, cs, d_out + off, cnt, W, c->stream));
         if (timer) HIP_TRY(c, timer->mark(c->stream));
@@ -174,7 +174,7 @@ int enqueue_mux_level(she_ctx *c, const uint8_t *d_jtype, const uint32_t *d_jin0
                                   c->stream));
         if (timer) HIP_TRY(c, timer->mark(c->stream));
         HIP_TRY(c, launch_blind_rotate(c->P, c->dk, cs, nullptr, 2 * cnt, c->work,
-                                       c->track_round ? c->d_round_err : nullptr, c->stream, true, 2 * cnt <= c->split_below));
+                                       c->track_round ? c->d_round_err : nullptr, c->stream, true, c->split_below));
         if (timer) HIP_TRY(c, timer->mark(c->stream));
         HIP_TRY(c, launch_mux_combine(c->P, c->dk, cs, d_out + off, cnt, c->work, c->stream));
         HIP_TRY(c, launch_key_switch(c->P, c->dk, cs, d_out + off, cnt, c->work, c->stream));

@@ -65,7 +65,8 @@ hipError_t launch_lincomb(const she_params &P, const CtSpace &cs, const uint8_t 
 hipError_t launch_blind_rotate(const she_params &P, const DeviceKeys &K, const CtSpace &cs, const uint32_t *d_out,
                                size_t gates, const LevelWork &W, unsigned *d_round_err /* nullptr = no tracking */,
                                hipStream_t st, bool raw = false /* write W.raw_ext instead of digits and slots */,
-                               bool split = false /* several wavefronts per gate: for levels that leave the chip underfilled */);
+                               size_t split_below = 0 /* levels, and rests beyond full rounds, of at most this many
+                                                        gates may run on several wavefronts per gate */);
 // MUX m: sample = raw_ext[2m] + raw_ext[2m+1] + (0, 1/8) -> key-switch digits, body and slot initialisation of gate m
 hipError_t launch_mux_combine(const she_params &P, const DeviceKeys &K, const CtSpace &cs, const uint32_t *d_out,
                               size_t muxes, const LevelWork &W, hipStream_t st);

@@ -81,25 +81,29 @@ constexpr int BR_WAVES = 4;     // measured: 2 and 8 wavefronts per workgroup ar
 
 // LC: the gadget length when it is known at compile time (the loops over the 2 LC rows of a step are then unrolled:
 // shifts and row offsets become constants, measured 1.2 % faster at l = 3 on alternating runs), 0 for any length.
+template <class PL> struct WaveShared {               // the LDS arrays of one workgroup
+    uint32_t acc[BR_WAVES * PL::GPW][2][PL::N];
+    double2 xch[BR_WAVES * PL::GPW][PL::XSLOTS];
+    double2 tw[TwTable<PL>::COUNT];
+};
+
 template <class PL, bool TRACK, int LC>
-__global__ __launch_bounds__(64 * BR_WAVES, 2) void k_blind_rotate(
+__device__ __forceinline__ void rotate_by_wavefront(
+    uint32_t (*s_acc)[2][PL::N], double2 (*s_xch)[PL::XSLOTS], double2 *s_tw, uint32_t block,
     const uint16_t *__restrict__ bar, uint32_t bar_stride, uint32_t n, uint32_t l_arg, uint32_t bg_bit,
     const double2 *__restrict__ bk_hat, const double2 *__restrict__ tw_table, uint32_t ks_bits,
-    uint32_t *__restrict__ ext_b, uint16_t *__restrict__ ksd, uint32_t gates, unsigned *round_err, CtSpace cs,
+    uint32_t *__restrict__ ext_b, uint16_t *__restrict__ ksd, uint32_t gates, unsigned *round_err, const CtSpace &cs,
     const uint32_t *__restrict__ out_ids, uint32_t *__restrict__ raw_ext)
 {
     constexpr int P = PL::P, L = PL::L, M = PL::M, N = PL::N, GPW = PL::GPW;
     const uint32_t l = LC ? (uint32_t)LC : l_arg;
-    __shared__ uint32_t s_acc[BR_WAVES * GPW][2][N];
-    __shared__ double2 s_xch[BR_WAVES * GPW][PL::XSLOTS];
-    __shared__ double2 s_tw[TwTable<PL>::COUNT];
 
     const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
     const int sub = lane / L, t = lane % L;
     const int slot = wave * GPW + sub;
-    const uint32_t g_raw = (blockIdx.x * BR_WAVES + wave) * GPW + sub;
+    const uint32_t g_raw = (block * BR_WAVES + wave) * GPW + sub;
     load_twiddles<PL>(s_tw, tw_table);                                    // the only workgroup barrier
-    if ((blockIdx.x * BR_WAVES + wave) * GPW >= gates) return;          // whole wavefront idle
+    if ((block * BR_WAVES + wave) * GPW >= gates) return;               // whole wavefront idle
     const bool live = g_raw < gates;
     const uint32_t g = live ? g_raw : gates - 1;                          // idle lanes shadow the last gate
 
@@ -240,6 +244,20 @@ __global__ __launch_bounds__(64 * BR_WAVES, 2) void k_blind_rotate(
             for (uint32_t c = t; c <= n; c += L) o[c] = (c == n) ? body : 0u;
         }
     }
+}
+
+template <class PL, bool TRACK, int LC>
+__global__ __launch_bounds__(64 * BR_WAVES, 2) void k_blind_rotate(
+    const uint16_t *__restrict__ bar, uint32_t bar_stride, uint32_t n, uint32_t l, uint32_t bg_bit,
+    const double2 *__restrict__ bk_hat, const double2 *__restrict__ tw_table, uint32_t ks_bits,
+    uint32_t *__restrict__ ext_b, uint16_t *__restrict__ ksd, uint32_t gates, unsigned *round_err, CtSpace cs,
+    const uint32_t *__restrict__ out_ids, uint32_t *__restrict__ raw_ext)
+{
+    __shared__ uint32_t s_acc[BR_WAVES * PL::GPW][2][PL::N];
+    __shared__ double2 s_xch[BR_WAVES * PL::GPW][PL::XSLOTS];
+    __shared__ double2 s_tw[TwTable<PL>::COUNT];
+    rotate_by_wavefront<PL, TRACK, LC>(s_acc, s_xch, s_tw, blockIdx.x, bar, bar_stride, n, l, bg_bit, bk_hat, tw_table,
+                                       ks_bits, ext_b, ksd, gates, round_err, cs, out_ids, raw_ext);
 }
 
 // ------------------------------------------------------------------------------------------
@@ -477,22 +495,26 @@ __global__ __launch_bounds__(128 * GB, 2) void k_blind_rotate_split(
 // Measured at n = 630, ms per launch of 1 / 83 / 256 / 512 gates: 2.2 / 2.2 / 2.3 / 3.6 against 3.2 / 3.2 / 3.2 / 4.0 of
 // k_blind_rotate_split; beyond two gates per compute unit that kernel is the faster one (700 gates: 5.2 against 4.9).
 // ------------------------------------------------------------------------------------------
+struct QuadShared {
+    uint32_t rot[2][HalfPlan::N], base[2][HalfPlan::N];
+    double2 xch[4][HalfPlan::XSLOTS], hand[4][4 * HalfPlan::ROW];
+    double2 tw[HalfPlan::COUNT];
+};
+
 template <bool TRACK, int LR>
-__global__ __launch_bounds__(256, 2) void k_blind_rotate_quad(
+__device__ __forceinline__ void rotate_by_quad(
+    QuadShared &sh, uint32_t g,
     const uint16_t *__restrict__ bar, uint32_t bar_stride, uint32_t n, uint32_t bg_bit,
     const double2 *__restrict__ bk_hat, const double2 *__restrict__ half_table, uint32_t ks_bits,
-    uint32_t *__restrict__ ext_b, uint16_t *__restrict__ ksd, unsigned *round_err, CtSpace cs,
+    uint32_t *__restrict__ ext_b, uint16_t *__restrict__ ksd, unsigned *round_err, const CtSpace &cs,
     const uint32_t *__restrict__ out_ids, uint32_t *__restrict__ raw_ext)
 {
     using HP = HalfPlan;
     constexpr int N = HP::N, L = HP::L;
-    __shared__ uint32_t s_rot[2][N], s_base[2][N];
-    __shared__ double2 s_xch[4][HP::XSLOTS], s_hand[4][4 * HP::ROW];
-    __shared__ double2 s_tw[HP::COUNT];
+    auto &s_rot = sh.rot; auto &s_base = sh.base; auto &s_xch = sh.xch; auto &s_hand = sh.hand; auto &s_tw = sh.tw;
 
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), t = threadIdx.x & 63;
     const int c = wave >> 1, h = wave & 1;
-    const uint32_t g = blockIdx.x;
     for (int e = threadIdx.x; e < HP::COUNT; e += 256) s_tw[e] = half_table[e];
     __syncthreads();
     HalfCtx hc;
@@ -655,6 +677,45 @@ __global__ __launch_bounds__(256, 2) void k_blind_rotate_quad(
             for (uint32_t w = threadIdx.x; w <= n; w += 256) o[w] = (w == n) ? body : 0u;
         }
     }
+}
+
+template <bool TRACK, int LR>
+__global__ __launch_bounds__(256, 2) void k_blind_rotate_quad(
+    const uint16_t *__restrict__ bar, uint32_t bar_stride, uint32_t n, uint32_t bg_bit,
+    const double2 *__restrict__ bk_hat, const double2 *__restrict__ half_table, uint32_t ks_bits,
+    uint32_t *__restrict__ ext_b, uint16_t *__restrict__ ksd, unsigned *round_err, CtSpace cs,
+    const uint32_t *__restrict__ out_ids, uint32_t *__restrict__ raw_ext)
+{
+    __shared__ QuadShared sh;
+    rotate_by_quad<TRACK, LR>(sh, blockIdx.x, bar, bar_stride, n, bg_bit, bk_hat, half_table, ks_bits, ext_b, ksd, round_err,
+                              cs, out_ids, raw_ext);
+}
+
+// Both in one launch: workgroups below `wave_blocks` run four gates on a wavefront each, every later one a single gate on
+// four wavefronts.  A level of gates on a wavefront each takes whole rounds: with one gate more than a multiple of four
+// per compute unit, one more workgroup sits on a few compute units for as long as a full round does (its wavefronts run
+// 630 CMuxes of 10 us alone, whatever else is idle).  Here the rest beyond full rounds runs its 630 CMuxes in 3.6 us
+// each, beside the wavefronts of the last round that the hardware let fall behind (of two on a SIMD the older one goes
+// first: 6.9 ms against 10.7).  Measured at n = 630 on 256 compute units, in ms, one wavefront per gate (or the split
+// kernel, up to 1536) against mixed: 1100 gates 8.4 / 6.2, 1280 8.4 / 7.0, 1536 9.7 / 8.8, 2100 16.1 / 12.3, 2304 16.1 /
+// 12.1, 2500 16.0 / 14.4, 3300 20.2 / 16.0, 4352 25.3 / 21.0, 4608 25.5 / 23.3, 6500 34.6 / 33.0, 8600 44.1 / 42.5.  A
+// rest of more than two gates per compute unit gains nothing (3600: 20.3 / 20.4, 5000: 25.1 / 26.6, 13001: 62.8 / 63.0).
+template <bool TRACK, int LR>
+__global__ __launch_bounds__(256, 2) void k_blind_rotate_mixed(
+    const uint16_t *__restrict__ bar, uint32_t bar_stride, uint32_t n, uint32_t bg_bit,
+    const double2 *__restrict__ bk_hat, const double2 *__restrict__ tw_table, const double2 *__restrict__ half_table,
+    uint32_t ks_bits, uint32_t *__restrict__ ext_b, uint16_t *__restrict__ ksd, uint32_t wave_blocks, unsigned *round_err,
+    CtSpace cs, const uint32_t *__restrict__ out_ids, uint32_t *__restrict__ raw_ext)
+{
+    using PL = Plan<3, 3>;
+    static_assert(PL::N == HalfPlan::N && PL::GPW == 1 && BR_WAVES == 4, "both forms on 256 threads at the same ring degree");
+    __shared__ union { WaveShared<PL> wave; QuadShared quad; } sh;
+    if (blockIdx.x < wave_blocks)
+        rotate_by_wavefront<PL, TRACK, LR>(sh.wave.acc, sh.wave.xch, sh.wave.tw, blockIdx.x, bar, bar_stride, n, LR, bg_bit,
+                                           bk_hat, tw_table, ks_bits, ext_b, ksd, wave_blocks * BR_WAVES, round_err, cs, out_ids, raw_ext);
+    else
+        rotate_by_quad<TRACK, LR>(sh.quad, wave_blocks * BR_WAVES + (blockIdx.x - wave_blocks), bar, bar_stride, n, bg_bit,
+                                  bk_hat, half_table, ks_bits, ext_b, ksd, round_err, cs, out_ids, raw_ext);
 }
 
 // Second half of a native MUX: the two rotations' samples are added, 1/8 goes on the body, and the
@@ -1271,10 +1332,23 @@ hipError_t launch_lincomb(const she_params &P, const CtSpace &cs, const uint8_t 
 template <class PL>
 static hipError_t blind_rotate_t(const she_params &P, const DeviceKeys &K, size_t gates, const LevelWork &W,
                                  unsigned *d_round_err, const CtSpace &cs, const uint32_t *d_out, hipStream_t st,
-                                 uint32_t *raw_ext, bool split)
+                                 uint32_t *raw_ext, size_t split_below)
 {
     const uint32_t ks_bits = P.ks_t * P.ks_basebit;
+    const bool split = gates <= split_below;
     if constexpr (PL::N == HalfPlan::N) {
+        // full rounds on one wavefront per gate, the rest on four (measured beside the kernel)
+        const size_t round = BR_WAVES * (size_t)K.cus, rest = gates % round;
+        if (P.l == 3 && gates > round && rest && rest <= std::min<size_t>(2 * (size_t)K.cus, split_below)) {
+            const size_t wave_blocks = (gates - rest) / BR_WAVES;
+#define SHE_LAUNCH_MIXED(TRACK)                                                                                       \
+    hipLaunchKernelGGL((k_blind_rotate_mixed<TRACK, 3>), dim3((unsigned)(wave_blocks + rest)), dim3(64 * BR_WAVES), 0, \
+                       st, W.bar, W.bar_stride, P.n, P.bg_bit, K.bk_hat, K.twiddles, K.half_twiddles, ks_bits, W.ext_b, \
+                       W.ksd, (uint32_t)wave_blocks, d_round_err, cs, d_out, raw_ext)
+            if (d_round_err) SHE_LAUNCH_MIXED(true); else SHE_LAUNCH_MIXED(false);
+#undef SHE_LAUNCH_MIXED
+            return hipGetLastError();
+        }
         // up to two gates per compute unit: four wavefronts per gate (measured beside the kernel)
         if (split && P.l == 3 && gates <= 2 * (size_t)K.cus) {
 #define SHE_LAUNCH_QUAD(TRACK)                                                                                        \
@@ -1323,15 +1397,16 @@ static hipError_t blind_rotate_t(const she_params &P, const DeviceKeys &K, size_
 }
 
 hipError_t launch_blind_rotate(const she_params &P, const DeviceKeys &K, const CtSpace &cs, const uint32_t *d_out,
-                               size_t gates, const LevelWork &W, unsigned *d_round_err, hipStream_t st, bool raw, bool split)
+                               size_t gates, const LevelWork &W, unsigned *d_round_err, hipStream_t st, bool raw,
+                               size_t split_below)
 {
     if (!gates) return hipSuccess;
     if (!K.ks_bytes) d_out = nullptr;      // the generic key switch writes the slot itself
     uint32_t *raw_ext = raw ? W.raw_ext : nullptr;
     switch (P.N) {
-    case 256: return blind_rotate_t<Plan256>(P, K, gates, W, d_round_err, cs, d_out, st, raw_ext, split);
-    case 512: return blind_rotate_t<Plan512>(P, K, gates, W, d_round_err, cs, d_out, st, raw_ext, split);
-    case 1024: return blind_rotate_t<Plan1024>(P, K, gates, W, d_round_err, cs, d_out, st, raw_ext, split);
+    case 256: return blind_rotate_t<Plan256>(P, K, gates, W, d_round_err, cs, d_out, st, raw_ext, split_below);
+    case 512: return blind_rotate_t<Plan512>(P, K, gates, W, d_round_err, cs, d_out, st, raw_ext, split_below);
+    case 1024: return blind_rotate_t<Plan1024>(P, K, gates, W, d_round_err, cs, d_out, st, raw_ext, split_below);
     }
     return hipErrorInvalidValue;
 }

@@ -38,3 +38,11 @@ def level():
 def test_level_sizes_give_the_same_words(level, count, tracking):
     run, default, want = level
     assert np.array_equal(run(count, default, tracking), want[:count])
+
+
+# full rounds of four gates per compute unit on a wavefront each, the rest (1 .. 2 per compute unit) on four
+@pytest.mark.parametrize("tracking", [False, True])
+@pytest.mark.parametrize("count", [1025, 1536, 1537, 2049, 2560])
+def test_a_rest_beyond_full_rounds_gives_the_same_words(level, count, tracking):
+    run, default, want = level
+    assert np.array_equal(run(count, default, tracking), want[:count])
