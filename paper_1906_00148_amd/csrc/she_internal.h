@@ -59,6 +59,9 @@ hipError_t launch_trgsw_transform(const she_params &P, const DeviceKeys &K, cons
 hipError_t launch_cmux(const she_params &P, const DeviceKeys &K, const double2 *trgsw_hat, uint32_t *trlwe,
                        const uint32_t *d_sel, const uint32_t *d_in1, const uint32_t *d_in0, const uint32_t *d_out,
                        size_t count, unsigned *d_round_err, hipStream_t st);
+// samples ids[0 .. count) of the pool -> d_dst [count][2][N] in the order of their coefficients
+hipError_t launch_trlwe_gather(const uint32_t *trlwe, uint32_t *d_dst, const uint32_t *d_ids, size_t count, uint32_t N,
+                               hipStream_t st);
 // d_in2 may be null when no type is a three-input gate
 hipError_t launch_lincomb(const she_params &P, const CtSpace &cs, const uint8_t *d_type, const uint32_t *d_in0,
                           const uint32_t *d_in1, const uint32_t *d_in2, size_t gates, const LevelWork &W, hipStream_t st);

@@ -1008,6 +1008,21 @@ __global__ __launch_bounds__(64 * BR_WAVES, 2) void k_cmux(const double2 *__rest
     if (TRACK && round_err) atomicMax(round_err, __float_as_uint(worst));
 }
 
+// TRLWE samples from the pool into consecutive places, in the order of their coefficients, for one copy to the host (33
+// samples of N = 1024 read back: 40 us; a copy for each and the reordering on the host 510).  The 16-byte word (q, t) of
+// a component holds the coefficients t + 128 q, t + 128 q + N/2, t + 128 q + 64, t + 128 q + 64 + N/2.
+__global__ __launch_bounds__(256) void k_trlwe_gather(const uint32_t *__restrict__ trlwe, uint32_t *__restrict__ dst,
+                                                      const uint32_t *__restrict__ ids, uint32_t N)
+{
+    const uint4 *src = reinterpret_cast<const uint4 *>(trlwe + (size_t)ids[blockIdx.x] * 2 * N);
+    uint32_t *d = dst + (size_t)blockIdx.x * 2 * N;
+    for (uint32_t w = threadIdx.x; w < N / 2; w += 256) {
+        const uint32_t c = w / (N / 4), q = w % (N / 4) / 64, j = c * N + 128 * q + w % 64;
+        const uint4 v = src[w];
+        d[j] = v.x; d[j + N / 2] = v.y; d[j + 64] = v.z; d[j + 64 + N / 2] = v.w;
+    }
+}
+
 // ------------------------------------------------------------------------------------------
 // Key switch.  Block = KS_GROUP gates x KS_COLS output words; every thread owns one output
 // word of all the gates, so each key row that is loaded serves KS_GROUP gates.
@@ -1305,6 +1320,14 @@ hipError_t launch_cmux(const she_params &P, const DeviceKeys &K, const double2 *
     case 2048: return cmux_t<Plan2048>(P, K, trgsw_hat, trlwe, d_sel, d_in1, d_in0, d_out, count, d_round_err, st);
     }
     return hipErrorInvalidValue;
+}
+
+hipError_t launch_trlwe_gather(const uint32_t *trlwe, uint32_t *d_dst, const uint32_t *d_ids, size_t count, uint32_t N,
+                               hipStream_t st)
+{
+    if (!count) return hipSuccess;
+    hipLaunchKernelGGL(k_trlwe_gather, dim3((unsigned)count), dim3(256), 0, st, trlwe, d_dst, d_ids, N);
+    return hipGetLastError();
 }
 
 hipError_t launch_bk_transform(const she_params &P, const uint32_t *d_bk_int, const DeviceKeys &K, hipStream_t st)

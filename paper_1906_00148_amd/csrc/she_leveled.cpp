@@ -9,6 +9,7 @@ using namespace she;
 namespace {
 
 constexpr size_t kTrgswChunk = 512;     // selectors generated, uploaded and transformed per round trip
+constexpr size_t kReadChunk = 1024;     // TRLWE samples gathered and copied back per round trip (16 MiB at N = 2048)
 
 size_t trgsw_hat_elems(const she_params &P) { return (size_t)2 * P.l * 2 * (P.N / 2); }   // double2 per selector
 
@@ -152,15 +153,17 @@ try {
     if ((rc = check_range(c, ids, count, c->lev.trlwe_cap, "she_trlwe_read"))) return rc;
     const uint32_t N = c->P.N;
     const size_t words = (size_t)2 * N;
-    std::vector<uint32_t> dev(count * words);
-    for (size_t k = 0; k < count; k++)
-        HIP_TRY(c, hipMemcpyAsync(dev.data() + k * words, c->lev.trlwe + ids[k] * words, words * 4, hipMemcpyDeviceToHost,
-                                  c->stream));
-    HIP_TRY(c, hipStreamSynchronize(c->stream));
-    for (size_t k = 0; k < count; k++)
-        for (uint32_t comp = 0; comp < 2; comp++)
-            for (uint32_t j = 0; j < N; j++)
-                samples[k * words + comp * N + j] = dev[k * words + comp * N + device_pos(N, j)];
+    // gathered and reordered on the device, then one copy per chunk
+    const size_t step = std::min(count, kReadChunk);
+    if ((rc = ensure_stage(c, step * words + step))) return rc;
+    uint32_t *d_ids = c->d_stage + step * words;
+    for (size_t off = 0; off < count; off += step) {
+        const size_t cnt = std::min(step, count - off);
+        HIP_TRY(c, hipMemcpyAsync(d_ids, ids + off, cnt * 4, hipMemcpyHostToDevice, c->stream));
+        HIP_TRY(c, launch_trlwe_gather(c->lev.trlwe, c->d_stage, d_ids, cnt, N, c->stream));
+        HIP_TRY(c, hipMemcpyAsync(samples + off * words, c->d_stage, cnt * words * 4, hipMemcpyDeviceToHost, c->stream));
+        HIP_TRY(c, hipStreamSynchronize(c->stream));
+    }
     return SHE_OK;
 } SHE_NOTHROW(c)
 
