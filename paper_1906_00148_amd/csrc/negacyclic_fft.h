@@ -674,6 +674,98 @@ __device__ __forceinline__ void inverse_half(const HalfCtx &hc, double (&xr)[4],
     node_pass_inverse<4>(xr, xi, hc.ea);
 }
 
+// The halves of a transform for kernels that give each one a wavefront: 2 P0 lanes' worth of points, P0 = POINTS per lane,
+// from the end of stage 0 (position 64 m + t of the half in register m) to the key rows' order and back.
+template <int N> struct HalfTransform;
+
+template <> struct HalfTransform<1024> {
+    static constexpr int POINTS = HalfPlan::P, XSLOTS = HalfPlan::XSLOTS, COUNT = HalfPlan::COUNT;
+    HalfCtx hc;
+    CosTan eb[2], ec[2], ed[2];
+    __device__ __forceinline__ void init(int lane, int half, double2 *xbuf, const double2 *tw)
+    {
+        hc.init(lane, half, xbuf, tw);
+        hc.entries<1>(eb); hc.entries<2>(ec); hc.entries<3>(ed);
+    }
+    __device__ __forceinline__ int key(int m) const { return HalfPlan::key_reg(m) + HalfPlan::key_lane(hc.h, hc.t); }
+    __device__ __forceinline__ void forward(double (&xr)[4], double (&xi)[4]) const
+    {
+        half_pass_a(hc, xr, xi);
+        half_pass_b(hc, xr, xi, eb);
+        half_pass_c(hc, xr, xi, ec);
+        node_pass<4>(xr, xi, ed);
+    }
+    __device__ __forceinline__ void inverse(double (&xr)[4], double (&xi)[4]) const { inverse_half(hc, xr, xi, eb, ec, ed); }
+};
+
+template <> struct HalfTransform<2048> {
+    using PL = Plan2048;
+    static constexpr int POINTS = PL::XP, XSLOTS = PL::XSLOTS, COUNT = TwTable<PL>::COUNT;
+    LaneCtx<PL> lc;
+    int h;
+    CosTan ea[4];
+    __device__ __forceinline__ void init(int lane, int half, double2 *xbuf, const double2 *tw)
+    {
+        lc.init(lane, xbuf, tw);
+        h = half;
+        // w(1, h), w(2, h), w(3, h), w(3, h + 2); w(1, 1) = i w(1, 0) has the angle 5 pi / 8
+        constexpr CosTan w11 = {-0.38268343236508977173, -2.41421356237309504880};
+        ea[0] = h ? w11 : first_pass_entry(1, 0);
+        ea[1] = h ? first_pass_entry(2, 1) : first_pass_entry(2, 0);
+        ea[2] = h ? first_pass_entry(3, 1) : first_pass_entry(3, 0);
+        ea[3] = h ? first_pass_entry(3, 3) : first_pass_entry(3, 2);
+    }
+    __device__ __forceinline__ int key(int m) const { return (POINTS * h + m) * PL::L + lc.t; }
+    __device__ __forceinline__ void forward(double (&xr)[8], double (&xi)[8]) const
+    {
+        node_pass<8>(xr, xi, ea);
+#pragma unroll
+        for (int pass = 1; pass < 3; pass++) {
+            CosTan e[4];
+            half_entries<PL>(lc, pass, h, e);
+            wave_lds_fence();
+#pragma unroll
+            for (int m = 0; m < 8; m++) lc.xch[brev(m, 3) * PL::xrow(pass - 1) + lc.t] = make_double2(xr[m], xi[m]);
+            wave_lds_fence();
+#pragma unroll
+            for (int m = 0; m < 8; m++) {
+                const double2 v = lc.xch[lc.rd_base[pass - 1] + m * ipow(8, 2 - pass)];
+                xr[m] = v.x; xi[m] = v.y;
+            }
+            node_pass<8>(xr, xi, e);
+        }
+        reverse(xr); reverse(xi);
+    }
+    __device__ __forceinline__ void inverse(double (&xr)[8], double (&xi)[8]) const
+    {
+        reverse(xr); reverse(xi);
+#pragma unroll
+        for (int pass = 2; pass >= 1; pass--) {
+            CosTan e[4];
+            half_entries<PL>(lc, pass, h, e);
+            node_pass_inverse<8>(xr, xi, e);
+            wave_lds_fence();
+#pragma unroll
+            for (int m = 0; m < 8; m++) lc.xch[lc.rd_base[pass - 1] + m * ipow(8, 2 - pass)] = make_double2(xr[m], xi[m]);
+            wave_lds_fence();
+#pragma unroll
+            for (int m = 0; m < 8; m++) {
+                const double2 v = lc.xch[brev(m, 3) * PL::xrow(pass - 1) + lc.t];
+                xr[m] = v.x; xi[m] = v.y;
+            }
+        }
+        node_pass_inverse<8>(xr, xi, ea);
+    }
+    static __device__ __forceinline__ void reverse(double (&x)[8])
+    {
+        double y[8];
+#pragma unroll
+        for (int m = 0; m < 8; m++) y[brev(m, 3)] = x[m];
+#pragma unroll
+        for (int m = 0; m < 8; m++) x[m] = y[m];
+    }
+};
+
 // Forward transform of NB independent polynomials held by the same lanes (NB register sets, NB
 // exchange buffers); their passes are written side by side so that one set's arithmetic can fill the
 // other's LDS round trips.  In: xr/xi[b][m] = u_{t + L*m} (folded, not yet twisted).  Out: spectra in

@@ -1008,6 +1008,142 @@ __global__ __launch_bounds__(64 * BR_WAVES, 2) void k_cmux(const double2 *__rest
     if (TRACK && round_err) atomicMax(round_err, __float_as_uint(worst));
 }
 
+// ------------------------------------------------------------------------------------------
+// Leveled CMux of small levels: one CMux per workgroup of four wavefronts, (component c, half h of the spectrum) as in
+// k_blind_rotate_quad.  Such a level takes as long as one CMux does, operands and selector rows fetched from memory: a
+// wavefront's chain of 2l + 2 transforms becomes l + 1 transforms of half the length.  Measured, us per launch of 1 / 33 /
+// 256 / 512 CMuxes, one wavefront against four: N = 1024 12.4 / 16.0 / 16.8 / 17.8 against 7.9 / 9.0 / 10.2 / 14.1, N =
+// 2048 21.9 / 28.0 / 33.4 / 36.4 against 13.8 / 15.2 / 22.1 / 28.5; with more than two CMuxes per compute unit a second
+// round of workgroups starts and k_cmux is as fast or faster (768: 18.7 against 17.9, 37.6 against 40.2).
+// ------------------------------------------------------------------------------------------
+template <int N, bool TRACK>
+__global__ __launch_bounds__(256, 2) void k_cmux_quad(const double2 *__restrict__ trgsw_hat, uint32_t *trlwe,
+                                                      const uint32_t *__restrict__ sel, const uint32_t *__restrict__ in1,
+                                                      const uint32_t *__restrict__ in0, const uint32_t *__restrict__ out,
+                                                      uint32_t l, uint32_t bg_bit, const double2 *__restrict__ table,
+                                                      unsigned *round_err)
+{
+    using HT = HalfTransform<N>;
+    constexpr int P = HT::POINTS, M = N / 2, L = 64;
+    __shared__ double2 s_xch[4][HT::XSLOTS], s_hand[4][P * L];
+    __shared__ double2 s_tw[HT::COUNT];
+
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), t = threadIdx.x & 63;
+    const int c = wave >> 1, h = wave & 1;
+    const uint32_t g = blockIdx.x;
+    const uint32_t *d1 = trlwe + (size_t)in1[g] * 2 * N, *d0 = trlwe + (size_t)in0[g] * 2 * N;
+    const double2 *rows = trgsw_hat + ((size_t)sel[g] * 2 + c) * l * 2 * M;     // rows of this component, [l][2][M]
+    // every word of d1 - d0's component c, before the table is waited for (16-byte words as in k_cmux)
+    uint4 u[P], v[P];
+#pragma unroll
+    for (int q = 0; q < P; q++) {
+        u[q] = (reinterpret_cast<const uint4 *>(d1 + c * N) + t)[q * L];
+        v[q] = (reinterpret_cast<const uint4 *>(d0 + c * N) + t)[q * L];
+    }
+    for (int e = threadIdx.x; e < HT::COUNT; e += 256) s_tw[e] = table[e];
+    __syncthreads();
+    HT ht;
+    ht.init(t, h, s_xch[wave], s_tw);
+
+    const uint32_t half_bg = 1u << (bg_bit - 1);
+    uint32_t dec_off = 1u << (31 - l * bg_bit);
+    uint32_t flip = 0;      // top bit of every digit field: field ^ top, read as signed, is field - Bg/2
+    for (uint32_t p = 1; p <= l; p++) { dec_off += half_bg << (32 - p * bg_bit); flip |= half_bg << (32 - p * bg_bit); }
+    float worst = 0.f;
+
+    uint32_t dlo[2 * P], dhi[2 * P];                                         // positions t + 64 m
+#pragma unroll
+    for (int q = 0; q < P; q++) {
+        dlo[2 * q] = (u[q].x - v[q].x + dec_off) ^ flip;     dhi[2 * q] = (u[q].y - v[q].y + dec_off) ^ flip;
+        dlo[2 * q + 1] = (u[q].z - v[q].z + dec_off) ^ flip; dhi[2 * q + 1] = (u[q].w - v[q].w + dec_off) ^ flip;
+    }
+    // Selector values of a row: output c ^ 1 is requested a row ahead, output c as well where registers allow (four points
+    // per lane), else once the transform has run (held through it with eight points, 55 registers are spilled).
+    constexpr bool BOTH_AHEAD = P <= 4;
+    double2 km[P], ko[P];
+    auto request = [&](double2 (&k)[P], uint32_t p, int o) {
+        const double2 *row = rows + ((size_t)p * 2 + o) * M;
+#pragma unroll
+        for (int m = 0; m < P; m++) k[m] = row[ht.key(m)];
+    };
+    request(ko, 0, c ^ 1);
+    if (BOTH_AHEAD) request(km, 0, c);
+    const double cs1 = h ? -0.70710678118654752440 : 0.70710678118654752440; // +-cos(pi/4) of the first stage
+    double mr[P], mi[P], orr[P], oi[P];                                      // partial half spectra: own component, the other one
+#pragma unroll
+    for (int m = 0; m < P; m++) mr[m] = mi[m] = orr[m] = oi[m] = 0.0;
+    for (uint32_t p = 0; p < l; p++) {
+        const uint32_t sh = 32 - (p + 1) * bg_bit;
+        double xr[P], xi[P];
+#pragma unroll
+        for (int m = 0; m < P; m++) {
+            const int ar = (int)__builtin_amdgcn_sbfe((int)dlo[m], sh, bg_bit), ai = (int)__builtin_amdgcn_sbfe((int)dhi[m], sh, bg_bit);
+            const int br = (int)__builtin_amdgcn_sbfe((int)dlo[m + P], sh, bg_bit), bi = (int)__builtin_amdgcn_sbfe((int)dhi[m + P], sh, bg_bit);
+            xr[m] = __builtin_fma(cs1, (double)(br - bi), (double)ar);
+            xi[m] = __builtin_fma(cs1, (double)(br + bi), (double)ai);
+        }
+        ht.forward(xr, xi);
+        if (!BOTH_AHEAD) {
+            __builtin_amdgcn_sched_barrier(0);
+            request(km, p, c);
+        }
+#pragma unroll
+        for (int m = 0; m < P; m++) {
+            orr[m] = __builtin_fma(-xi[m], ko[m].y, __builtin_fma(xr[m], ko[m].x, orr[m]));
+            oi[m] = __builtin_fma(xi[m], ko[m].x, __builtin_fma(xr[m], ko[m].y, oi[m]));
+        }
+#pragma unroll
+        for (int m = 0; m < P; m++) {
+            mr[m] = __builtin_fma(-xi[m], km[m].y, __builtin_fma(xr[m], km[m].x, mr[m]));
+            mi[m] = __builtin_fma(xi[m], km[m].x, __builtin_fma(xr[m], km[m].y, mi[m]));
+        }
+        if (p + 1 < l) {
+            request(ko, p + 1, c ^ 1);
+            if (BOTH_AHEAD) request(km, p + 1, c);
+        }
+    }
+    // the words of d0 that this wavefront's result is added to: 16-byte words P/2 h .. P/2 h + P/2 - 1
+    uint4 base[P / 2];
+#pragma unroll
+    for (int q = 0; q < P / 2; q++) base[q] = (reinterpret_cast<const uint4 *>(d0 + c * N) + t)[(P / 2 * h + q) * L];
+#pragma unroll
+    for (int m = 0; m < P; m++) s_hand[wave][m * L + t] = make_double2(orr[m], oi[m]);
+    lds_barrier();
+#pragma unroll
+    for (int m = 0; m < P; m++) { const double2 w = s_hand[wave ^ 2][m * L + t]; mr[m] += w.x; mi[m] += w.y; }
+    ht.inverse(mr, mi);
+    wave_lds_fence();
+#pragma unroll
+    for (int m = 0; m < P; m++) s_xch[wave][m * L + t] = make_double2(mr[m], mi[m]);
+    lds_barrier();
+    // last stage: (y0 + y1) / M for half 0, conj(w) (y0 - y1) / M for half 1; adding 1.5*2^52 leaves the rounded value
+    // modulo 2^32 in the low word
+    constexpr double magic = 6755399441055744.0, scale = 1.0 / M, rot = 0.70710678118654752440 / M;
+    uint32_t lo[P], hi[P];
+#pragma unroll
+    for (int m = 0; m < P; m++) {
+        const double2 w = s_xch[wave ^ 1][m * L + t];
+        double re, im, f;
+        if (h == 0) {
+            re = mr[m] + w.x; im = mi[m] + w.y; f = scale;
+        } else {
+            const double dr = w.x - mr[m], di = w.y - mi[m];
+            re = dr + di; im = di - dr; f = rot;
+        }
+        if (TRACK) {
+            worst = fmaxf(worst, (float)fabs(re * f - rint(re * f)));
+            worst = fmaxf(worst, (float)fabs(im * f - rint(im * f)));
+        }
+        lo[m] = (uint32_t)__double2loint(__builtin_fma(re, f, magic));
+        hi[m] = (uint32_t)__double2loint(__builtin_fma(im, f, magic));
+    }
+    uint4 *dst = reinterpret_cast<uint4 *>(trlwe + (size_t)out[g] * 2 * N + c * N) + t;
+#pragma unroll
+    for (int q = 0; q < P / 2; q++)
+        dst[(P / 2 * h + q) * L] = make_uint4(base[q].x + lo[2 * q], base[q].y + hi[2 * q], base[q].z + lo[2 * q + 1], base[q].w + hi[2 * q + 1]);
+    if (TRACK && round_err) atomicMax(round_err, __float_as_uint(worst));
+}
+
 // TRLWE samples from the pool into consecutive places, in the order of their coefficients, for one copy to the host (33
 // samples of N = 1024 read back: 40 us; a copy for each and the reordering on the host 510).  The 16-byte word (q, t) of
 // a component holds the coefficients t + 128 q, t + 128 q + N/2, t + 128 q + 64, t + 128 q + 64 + N/2.
@@ -1279,6 +1415,18 @@ static hipError_t cmux_t(const she_params &P, const DeviceKeys &K, const double2
                          const uint32_t *d_sel, const uint32_t *d_in1, const uint32_t *d_in0, const uint32_t *d_out,
                          size_t count, unsigned *d_round_err, hipStream_t st)
 {
+    if constexpr (PL::N == 1024 || PL::N == 2048) {
+        // up to two CMuxes per compute unit: four wavefronts each (measured beside the kernel)
+        if (count <= 2 * (size_t)K.cus) {
+            const double2 *table = PL::N == HalfPlan::N ? K.half_twiddles : K.twiddles;
+#define SHE_LAUNCH_CMUX_QUAD(TRACK)                                                                                   \
+    hipLaunchKernelGGL((k_cmux_quad<PL::N, TRACK>), dim3((unsigned)count), dim3(256), 0, st, trgsw_hat, trlwe, d_sel, \
+                       d_in1, d_in0, d_out, P.l, P.bg_bit, table, d_round_err)
+            if (d_round_err) SHE_LAUNCH_CMUX_QUAD(true); else SHE_LAUNCH_CMUX_QUAD(false);
+#undef SHE_LAUNCH_CMUX_QUAD
+            return hipGetLastError();
+        }
+    }
     // persistent: at most the workgroups per compute unit that fit (two; one at N = 2048), each wavefront loops over its share
     const size_t wgs = (count + BR_WAVES - 1) / BR_WAVES;
     const size_t per_cu = 2;
