@@ -508,32 +508,39 @@ try {
         if (bits[k] > 1) return fail(c, SHE_EINVAL, "bits must be 0 or 1");
     int rc = check_ids(c, dst_ids, nbits, "she_encrypt_bits");
     if (rc) return rc;
-    const size_t w = c->P.n + 1;
-    std::vector<uint32_t> host;
-    try { host.resize(nbits * w); } catch (const std::bad_alloc &) { return fail(c, SHE_ENOMEM, "host staging"); }
-    fresh_samples(c->P, c->hk.lwe_key, bits, nbits, enc_seed, host.data());
-    if ((rc = ensure_stage(c, nbits * w + nbits))) return rc;
-    uint32_t *d_ids = c->d_stage + nbits * w;
-    HIP_TRY(c, hipMemcpyAsync(c->d_stage, host.data(), nbits * w * 4, hipMemcpyHostToDevice, c->stream));
-    HIP_TRY(c, hipMemcpyAsync(d_ids, dst_ids, nbits * 4, hipMemcpyHostToDevice, c->stream));
-    HIP_TRY(c, launch_scatter(space(c), c->d_stage, d_ids, nbits, c->P.n, c->stream));
+    if (nbits > 0xFFFFFFFFu) return fail(c, SHE_EINVAL, "too many bits for one call");
+    // one upload: the count of samples to finish here (0), the ids, the bits, the key bits; their list is behind them
+    const size_t upload = (1 + nbits) * 4 + nbits + c->P.n, list = (upload + 3) / 4;
+    std::vector<uint8_t> host;
+    try { host.resize(upload); } catch (const std::bad_alloc &) { return fail(c, SHE_ENOMEM, "host staging"); }
+    std::memset(host.data(), 0, 4);
+    std::memcpy(host.data() + 4, dst_ids, nbits * 4);
+    std::memcpy(host.data() + (1 + nbits) * 4, bits, nbits);
+    std::memcpy(host.data() + (1 + nbits) * 4 + nbits, c->hk.lwe_key.data(), c->P.n);
+    if ((rc = ensure_stage(c, list + nbits))) return rc;
+    const uint8_t *d_bits = reinterpret_cast<const uint8_t *>(c->d_stage + 1 + nbits);
+    HIP_TRY(c, hipMemcpyAsync(c->d_stage, host.data(), upload, hipMemcpyHostToDevice, c->stream));
+    HIP_TRY(c, launch_fresh_samples(space(c), c->d_stage + 1, d_bits, d_bits + nbits, c->P.n, fresh_stream_base(enc_seed),
+                                    c->P.lwe_std, nbits, c->d_stage, c->d_stage + list, c->stream));
+    uint32_t unfinished = 0;
+    HIP_TRY(c, hipMemcpyAsync(&unfinished, c->d_stage, 4, hipMemcpyDeviceToHost, c->stream));
     HIP_TRY(c, hipStreamSynchronize(c->stream));
+    if (unfinished) {
+        std::vector<uint32_t> samples(unfinished), bodies(unfinished);
+        HIP_TRY(c, hipMemcpyAsync(samples.data(), c->d_stage + list, unfinished * 4, hipMemcpyDeviceToHost, c->stream));
+        HIP_TRY(c, hipStreamSynchronize(c->stream));
+        auto body = [&](uint32_t k) { return c->pool + (size_t)dst_ids[k] * c->stride + c->P.n; };
+        for (uint32_t q = 0; q < unfinished; q++)
+            HIP_TRY(c, hipMemcpyAsync(&bodies[q], body(samples[q]), 4, hipMemcpyDeviceToHost, c->stream));
+        HIP_TRY(c, hipStreamSynchronize(c->stream));
+        for (uint32_t q = 0; q < unfinished; q++) {
+            bodies[q] += fresh_error(c->P, enc_seed, samples[q]);
+            HIP_TRY(c, hipMemcpyAsync(body(samples[q]), &bodies[q], 4, hipMemcpyHostToDevice, c->stream));
+        }
+        HIP_TRY(c, hipStreamSynchronize(c->stream));
+    }
     return SHE_OK;
 } SHE_NOTHROW(c)
-
-static int fetch(she_ctx *c, const uint32_t *ids, size_t count, std::vector<uint32_t> &host)
-{
-    const size_t w = c->P.n + 1;
-    try { host.resize(count * w); } catch (const std::bad_alloc &) { return fail(c, SHE_ENOMEM, "host staging"); }
-    int rc = ensure_stage(c, count * w + count);
-    if (rc) return rc;
-    uint32_t *d_ids = c->d_stage + count * w;
-    HIP_TRY(c, hipMemcpyAsync(d_ids, ids, count * 4, hipMemcpyHostToDevice, c->stream));
-    HIP_TRY(c, launch_gather(space(c), c->d_stage, d_ids, count, c->P.n, c->stream));
-    HIP_TRY(c, hipMemcpyAsync(host.data(), c->d_stage, count * w * 4, hipMemcpyDeviceToHost, c->stream));
-    HIP_TRY(c, hipStreamSynchronize(c->stream));
-    return SHE_OK;
-}
 
 int she_decrypt(she_ctx *c, const uint32_t *ids, size_t count, uint8_t *bits_out)
 try {
@@ -543,9 +550,19 @@ try {
     if (!ids || !bits_out) return fail(c, SHE_EINVAL, "null argument");
     int rc = check_ids(c, ids, count, "she_decrypt");
     if (rc) return rc;
-    std::vector<uint32_t> host;
-    if ((rc = fetch(c, ids, count, host))) return rc;
-    phases_to_bits(c->P, c->hk.lwe_key, host.data(), count, bits_out);
+    if (count > 0xFFFFFFFFu) return fail(c, SHE_EINVAL, "too many ids for one call");
+    const size_t upload = count * 4 + c->P.n, result = (upload + 3) / 4;   // the ids and the key bits; the bits behind them
+    std::vector<uint8_t> host;
+    try { host.resize(upload); } catch (const std::bad_alloc &) { return fail(c, SHE_ENOMEM, "host staging"); }
+    std::memcpy(host.data(), ids, count * 4);
+    std::memcpy(host.data() + count * 4, c->hk.lwe_key.data(), c->P.n);
+    if ((rc = ensure_stage(c, result + (count + 3) / 4))) return rc;
+    uint8_t *d_bits = reinterpret_cast<uint8_t *>(c->d_stage + result);
+    HIP_TRY(c, hipMemcpyAsync(c->d_stage, host.data(), upload, hipMemcpyHostToDevice, c->stream));
+    HIP_TRY(c, launch_phase_bits(space(c), c->d_stage, reinterpret_cast<const uint8_t *>(c->d_stage + count), c->P.n, count,
+                                 d_bits, c->stream));
+    HIP_TRY(c, hipMemcpyAsync(bits_out, d_bits, count, hipMemcpyDeviceToHost, c->stream));
+    HIP_TRY(c, hipStreamSynchronize(c->stream));
     return SHE_OK;
 } SHE_NOTHROW(c)
 

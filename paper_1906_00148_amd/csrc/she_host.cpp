@@ -1,6 +1,7 @@
 // Client-side pieces: random streams, key generation, fresh encryptions, decryption.
 // (SHE, arXiv 1906.00148, Section 2: the client owns the private key, encrypts its data
-// and decrypts the result.)  Host code only; none of it is on the timed path.
+// and decrypts the result.)  Host code only; fresh encryptions and decryptions of samples in
+// the pool run on the device (k_fresh_samples, k_phase_bits), from the same streams.
 //
 // Random streams.  Every generated object has its own stream addressed by
 // (seed, tag, index); word c of a stream is mix(key + (c+1)*GOLDEN) with
@@ -136,13 +137,11 @@ void generate_keys(const she_params &P, uint64_t seed, HostKeys &K)
     });
 }
 
-void fresh_samples(const she_params &P, const std::vector<uint8_t> &lwe_key, const uint8_t *bits, size_t nbits,
-                   uint64_t enc_seed, uint32_t *out)
+uint64_t fresh_stream_base(uint64_t enc_seed) { return finalise(finalise(enc_seed) + kTagFresh); }
+
+uint32_t fresh_error(const she_params &P, uint64_t enc_seed, uint64_t k)
 {
-    parallel_for(nbits, [&](size_t k) {
-        const uint32_t msg = bits[k] ? (1u << 29) : 0u - (1u << 29);
-        tlwe_sample(P.n, lwe_key.data(), msg, P.lwe_std, Stream(enc_seed, kTagFresh, k), out + k * (P.n + 1));
-    });
+    return Stream(enc_seed, kTagFresh, k).gaussian(P.n, P.lwe_std);
 }
 
 void fresh_trgsw(const she_params &P, const std::vector<uint8_t> &ring_key, const uint8_t *bits, size_t count,
@@ -205,17 +204,6 @@ void pack_ks_bytes(const she_params &P, const std::vector<uint32_t> &ks, uint32_
                     }
                 }
             }
-    });
-}
-
-void phases_to_bits(const she_params &P, const std::vector<uint8_t> &lwe_key, const uint32_t *cts, size_t count,
-                    uint8_t *bits)
-{
-    parallel_for(count, [&](size_t k) {
-        const uint32_t *ct = cts + k * (P.n + 1);
-        uint32_t phase = ct[P.n];
-        for (uint32_t i = 0; i < P.n; i++) phase -= lwe_key[i] ? ct[i] : 0u;
-        bits[k] = (int32_t)phase > 0;
     });
 }
 

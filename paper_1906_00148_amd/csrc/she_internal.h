@@ -75,10 +75,14 @@ hipError_t launch_mux_combine(const she_params &P, const DeviceKeys &K, const Ct
                               size_t muxes, const LevelWork &W, hipStream_t st);
 hipError_t launch_key_switch(const she_params &P, const DeviceKeys &K, const CtSpace &cs, const uint32_t *d_out,
                              size_t gates, const LevelWork &W, hipStream_t st);
-hipError_t launch_scatter(const CtSpace &cs, const uint32_t *d_src /* [count][n+1] */, const uint32_t *d_ids,
-                          size_t count, uint32_t n, hipStream_t st);
-hipError_t launch_gather(const CtSpace &cs, uint32_t *d_dst /* [count][n+1] */, const uint32_t *d_ids, size_t count,
-                         uint32_t n, hipStream_t st);
+// fresh encryptions of d_bits under the key bits d_key into the slots d_ids (stream_base: fresh_stream_base); samples whose
+// error the host has to add (fresh_error) are listed in d_retry, *d_retry_count of them (zeroed by the caller)
+hipError_t launch_fresh_samples(const CtSpace &cs, const uint32_t *d_ids, const uint8_t *d_bits, const uint8_t *d_key,
+                                uint32_t n, uint64_t stream_base, double sigma, size_t count, uint32_t *d_retry_count,
+                                uint32_t *d_retry, hipStream_t st);
+// decryptions: d_bits[k] = sign of the phase of slot d_ids[k]
+hipError_t launch_phase_bits(const CtSpace &cs, const uint32_t *d_ids, const uint8_t *d_key, uint32_t n, size_t count,
+                             uint8_t *d_bits, hipStream_t st);
 // diagnostic: `blocks` workgroups of 256 threads, each thread 64*iters dependent-free FP64 instructions of one form
 hipError_t launch_fp64_probe(int form, double *d_out, uint32_t blocks, int iters, const double2 *src, uint32_t src_rows,
                              hipStream_t st);
@@ -97,8 +101,9 @@ struct HostKeys {
     std::vector<uint32_t> ks;    // [N][t][base-1][n+1]
 };
 void generate_keys(const she_params &P, uint64_t seed, HostKeys &out);
-void fresh_samples(const she_params &P, const std::vector<uint8_t> &lwe_key, const uint8_t *bits, size_t nbits,
-                   uint64_t enc_seed, uint32_t *out /* [nbits][n+1] */);
+// fresh encryptions: sample k's stream has the key finalise(fresh_stream_base + k); fresh_error is its rounded error
+uint64_t fresh_stream_base(uint64_t enc_seed);
+uint32_t fresh_error(const she_params &P, uint64_t enc_seed, uint64_t k);
 // key-switching key as signed byte planes for the MFMA kernel: out[i][plane][col][j*4+v]
 void pack_ks_bytes(const she_params &P, const std::vector<uint32_t> &ks, uint32_t cols_p, std::vector<int8_t> &out);
 // leveled mode: fresh TRGSW samples of bits [count][2][l][2][N], fresh TRLWE samples of mu[count][N] as [count][2][N]
@@ -109,8 +114,6 @@ void fresh_trlwe(const she_params &P, const std::vector<uint8_t> &ring_key, cons
                  uint64_t seed, uint32_t *out);
 void trlwe_phases(const she_params &P, const std::vector<uint8_t> &ring_key, const uint32_t *cts, size_t count,
                   uint32_t *phases);
-void phases_to_bits(const she_params &P, const std::vector<uint8_t> &lwe_key, const uint32_t *cts, size_t count,
-                    uint8_t *bits);
 
 // ---- netlists of the layer operators (she_circuits.cpp) ----
 constexpr uint32_t WIRE_NEG = 0x80000000u;   // flag on a wire reference: the complement of that wire

@@ -1328,18 +1328,6 @@ __global__ __launch_bounds__(64 * KSM_WAVES, 3) void k_key_switch_mfma(CtSpace c
 // ------------------------------------------------------------------------------------------
 // Pool plumbing
 // ------------------------------------------------------------------------------------------
-__global__ void k_scatter(CtSpace cs, const uint32_t *__restrict__ src, const uint32_t *__restrict__ ids, uint32_t n)
-{
-    uint32_t *dst = ct_ptr(cs, ids[blockIdx.x]);
-    const uint32_t *s = src + (size_t)blockIdx.x * (n + 1);
-    for (uint32_t i = threadIdx.x; i <= n; i += blockDim.x) dst[i] = s[i];
-}
-__global__ void k_gather(CtSpace cs, uint32_t *__restrict__ dst, const uint32_t *__restrict__ ids, uint32_t n)
-{
-    const uint32_t *s = ct_ptr(cs, ids[blockIdx.x]);
-    uint32_t *d = dst + (size_t)blockIdx.x * (n + 1);
-    for (uint32_t i = threadIdx.x; i <= n; i += blockDim.x) d[i] = s[i];
-}
 // dst <- src, or its complement (word-wise negation) when the source id carries WIRE_NEG
 __global__ void k_copy_ct(CtSpace cs, const uint32_t *__restrict__ src_ids, const uint32_t *__restrict__ dst_ids,
                           uint32_t n)
@@ -1349,6 +1337,81 @@ __global__ void k_copy_ct(CtSpace cs, const uint32_t *__restrict__ src_ids, cons
     const uint32_t *s = ct_ptr(cs, ref & ~WIRE_NEG);
     uint32_t *d = ct_ptr(cs, dst_ids[blockIdx.x]);
     for (uint32_t i = threadIdx.x; i <= n; i += blockDim.x) d[i] = neg ? 0u - s[i] : s[i];
+}
+
+// ------------------------------------------------------------------------------------------
+// Client side: fresh encryptions and phases of samples in the pool, one wavefront per sample.  The random words of a
+// sample's stream are addressed (she_host.cpp has the definition), so every lane makes its own.  Bound by the pool's
+// memory and the call itself (47 and 38 us for 6272 samples of n = 630, the key bits uploaded with each call); on the host's
+// threads, with the pool filled from and read into a staged copy, 1.4 and 1.5 ms.
+// ------------------------------------------------------------------------------------------
+constexpr int CLIENT_WAVES = 4;
+
+__device__ __forceinline__ uint64_t stream_mix(uint64_t z)
+{
+    z = (z ^ (z >> 30)) * 0xBF58476D1CE4E5B9ull;
+    z = (z ^ (z >> 27)) * 0x94D049BB133111EBull;
+    return z ^ (z >> 31);
+}
+__device__ __forceinline__ uint64_t stream_word(uint64_t key, uint64_t c) { return stream_mix(key + (c + 1) * 0x9E3779B97F4A7C15ull); }
+
+// sum over the lanes whose key bit is set
+__device__ __forceinline__ uint32_t wave_sum(uint32_t v)
+{
+#pragma unroll
+    for (int d = 32; d > 0; d >>= 1) v += (uint32_t)__shfl_xor((int)v, d, 64);
+    return v;
+}
+
+// The error is computed as she_host.cpp computes it, with this card's log and cos.  Both sides' functions are accurate to
+// a few units in the last place, so that the unrounded values differ by less than 2^-48 of their size: where the value is
+// further than 2^-44 of its size (and 2^-40) from halfway between two integers, both round to the same one.  Where it is
+// not, the sample's number goes into `retry` (its first word counts them), no error is added, and the host adds its own.
+__global__ __launch_bounds__(64 * CLIENT_WAVES) void k_fresh_samples(CtSpace cs, const uint32_t *__restrict__ ids,
+                                                                     const uint8_t *__restrict__ bits,
+                                                                     const uint8_t *__restrict__ lwe_key, uint32_t n,
+                                                                     uint64_t stream_base, double sigma, uint32_t count,
+                                                                     uint32_t *retry_count, uint32_t *__restrict__ retry)
+{
+#pragma clang fp contract(off)
+    const uint32_t k = blockIdx.x * CLIENT_WAVES + (threadIdx.x >> 6), lane = threadIdx.x & 63;
+    if (k >= count) return;
+    const uint64_t key = stream_mix(stream_base + k);
+    uint32_t *dst = ct_ptr(cs, ids[k]);
+    uint32_t sum = 0;
+    for (uint32_t i = lane; i < n; i += 64) {
+        const uint32_t a = (uint32_t)(stream_word(key, i) >> 32);
+        dst[i] = a;
+        sum += lwe_key[i] ? a : 0u;
+    }
+    sum = wave_sum(sum);
+    if (lane) return;
+    const double unit = 1.0 / 9007199254740992.0;                             // 2^-53
+    const double u1 = (double)((stream_word(key, n) >> 11) + 1) * unit;
+    const double u2 = (double)(stream_word(key, (uint64_t)n + 1) >> 11) * unit;
+    const double radius = sqrt(-2.0 * log(u1));
+    const double normal = radius * cos(6.283185307179586476925286766559 * u2);
+    const double scaled = normal * sigma * 4294967296.0, rounded = rint(scaled);
+    const double to_half = 0.5 - fabs(scaled - rounded);
+    uint32_t error = (uint32_t)(int64_t)rounded;
+    if (!(to_half > fabs(scaled) * 0x1p-44 + 0x1p-40)) {
+        retry[atomicAdd(retry_count, 1u)] = k;
+        error = 0;
+    }
+    dst[n] = (bits[k] ? (1u << 29) : 0u - (1u << 29)) + sum + error;
+}
+
+__global__ __launch_bounds__(64 * CLIENT_WAVES) void k_phase_bits(CtSpace cs, const uint32_t *__restrict__ ids,
+                                                                  const uint8_t *__restrict__ lwe_key, uint32_t n,
+                                                                  uint32_t count, uint8_t *__restrict__ bits)
+{
+    const uint32_t k = blockIdx.x * CLIENT_WAVES + (threadIdx.x >> 6), lane = threadIdx.x & 63;
+    if (k >= count) return;
+    const uint32_t *ct = ct_ptr(cs, ids[k]);
+    uint32_t sum = 0;
+    for (uint32_t i = lane; i < n; i += 64) sum += lwe_key[i] ? ct[i] : 0u;
+    sum = wave_sum(sum);
+    if (lane == 0) bits[k] = (int32_t)(ct[n] - sum) > 0;
 }
 
 // ------------------------------------------------------------------------------------------
@@ -1613,18 +1676,21 @@ hipError_t launch_key_switch(const she_params &P, const DeviceKeys &K, const CtS
     return hipGetLastError();
 }
 
-hipError_t launch_scatter(const CtSpace &cs, const uint32_t *d_src, const uint32_t *d_ids, size_t count, uint32_t n,
-                          hipStream_t st)
+hipError_t launch_fresh_samples(const CtSpace &cs, const uint32_t *d_ids, const uint8_t *d_bits, const uint8_t *d_key,
+                                uint32_t n, uint64_t stream_base, double sigma, size_t count, uint32_t *d_retry_count,
+                                uint32_t *d_retry, hipStream_t st)
 {
     if (!count) return hipSuccess;
-    hipLaunchKernelGGL(k_scatter, dim3((unsigned)count), dim3(128), 0, st, cs, d_src, d_ids, n);
+    hipLaunchKernelGGL(k_fresh_samples, dim3((unsigned)((count + CLIENT_WAVES - 1) / CLIENT_WAVES)), dim3(64 * CLIENT_WAVES),
+                       0, st, cs, d_ids, d_bits, d_key, n, stream_base, sigma, (uint32_t)count, d_retry_count, d_retry);
     return hipGetLastError();
 }
-hipError_t launch_gather(const CtSpace &cs, uint32_t *d_dst, const uint32_t *d_ids, size_t count, uint32_t n,
-                         hipStream_t st)
+hipError_t launch_phase_bits(const CtSpace &cs, const uint32_t *d_ids, const uint8_t *d_key, uint32_t n, size_t count,
+                             uint8_t *d_bits, hipStream_t st)
 {
     if (!count) return hipSuccess;
-    hipLaunchKernelGGL(k_gather, dim3((unsigned)count), dim3(128), 0, st, cs, d_dst, d_ids, n);
+    hipLaunchKernelGGL(k_phase_bits, dim3((unsigned)((count + CLIENT_WAVES - 1) / CLIENT_WAVES)), dim3(64 * CLIENT_WAVES), 0,
+                       st, cs, d_ids, d_key, n, (uint32_t)count, d_bits);
     return hipGetLastError();
 }
 hipError_t launch_copy_ct(const CtSpace &cs, const uint32_t *d_src_ids, const uint32_t *d_dst_ids, size_t count,
