@@ -273,10 +273,13 @@ __global__ __launch_bounds__(64 * BR_WAVES, 2) void k_blind_rotate(
 // ------------------------------------------------------------------------------------------
 // Workgroup barrier for LDS traffic only: earlier LDS operations of this wavefront are complete
 // (they finish in issue order, the counter reaches zero when the last one has), global loads
-// stay in flight.
+// stay in flight.  The wait is written out: the one that the fence stands for has been seen to
+// disappear where the barrier opens a loop whose entry has nothing outstanding, though the way
+// round the loop has (stores of one step read by another wavefront before they had landed).
 __device__ __forceinline__ void lds_barrier()
 {
     __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
+    __builtin_amdgcn_s_waitcnt(0xC07F);                                     // lgkmcnt(0)
     __builtin_amdgcn_s_barrier();
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
 }
