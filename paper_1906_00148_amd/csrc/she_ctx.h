@@ -27,6 +27,7 @@ struct LeveledPools {         // leveled mode: TRGSW selectors (spectral form) a
     uint32_t trgsw_cap = 0, trlwe_cap = 0;
     uint32_t *d_ids = nullptr;      // device staging of the id arrays of one call (4 x ids_cap)
     size_t ids_cap = 0;
+    hipEvent_t around[2] = {nullptr, nullptr};   // recorded around a level's kernel
 };
 // Layer operators recorded between she_defer_begin and she_defer_run: one netlist for all of them, so that the
 // scheduler can overlap the tail of one operator with the head of the next.
