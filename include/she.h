@@ -91,11 +91,14 @@ void she_free(she_ctx *ctx);
 /* Section 2 (encryption function) / Section 3.2 (bit-by-bit encryption).  Encrypts
  * bits[0..nbits) (each 0 or 1) as fresh TLWE samples; sample k uses the noise stream
  * (enc_seed, k) and is stored in slot dst_ids[k].  Errors: SHE_ERANGE for an id outside
- * the pool, SHE_EINVAL for a bit other than 0/1 or null pointers. */
+ * the pool, SHE_EINVAL for a bit other than 0/1 or null pointers.  The samples are made on
+ * the GPU: the bits and the TLWE key's bits lie in the context's device memory during the
+ * call and are overwritten there before it returns. */
 int she_encrypt_bits(she_ctx *ctx, const uint8_t *bits, size_t nbits, uint64_t enc_seed, const uint32_t *dst_ids);
 
 /* Section 2 (decryption function).  bits_out[k] = 1 iff the phase of slot ids[k] is
- * positive.  Uses the secret key held by the context. */
+ * positive.  Uses the secret key held by the context, on the GPU: the key's bits and the
+ * decrypted bits are overwritten in device memory before the call returns. */
 int she_decrypt(she_ctx *ctx, const uint32_t *ids, size_t count, uint8_t *bits_out);
 
 /* Section 3.1 (2-input homomorphic gates), Section 2 (bootstrapping keeps the noise in

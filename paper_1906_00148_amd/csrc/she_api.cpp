@@ -53,6 +53,42 @@ namespace {
 
 CtSpace space(const she_ctx *c) { return CtSpace{c->pool, c->temp, c->cap, c->stride}; }
 
+// What a client call sends to the staging buffer.  Words [first, last) of the buffer hold the secret key's bits and
+// plaintext bits: both copies of them are overwritten before the call returns, on every way out of it.
+struct Upload {
+    she_ctx *c;
+    size_t first, last;
+    std::vector<uint8_t> host;
+    bool sent = false, cleared = false;
+    Upload(she_ctx *ctx, size_t first_word, size_t last_word) : c(ctx), first(first_word), last(last_word) {}
+    Upload(const Upload &) = delete;
+    hipError_t send()
+    {
+        sent = true;
+        return hipMemcpyAsync(c->d_stage, host.data(), host.size(), hipMemcpyHostToDevice, c->stream);
+    }
+    hipError_t clear()                       // behind the work enqueued so far; 1 to 3 us of a call's 30 to 48
+    {
+        const hipError_t e = launch_clear_words(c->d_stage + first, last - first, c->stream);
+        cleared = e == hipSuccess;
+        return e;
+    }
+    hipError_t wait()
+    {
+        const hipError_t e = hipStreamSynchronize(c->stream);
+        if (cleared && e == hipSuccess) sent = false;
+        return e;
+    }
+    ~Upload()
+    {
+        if (sent) {
+            if (!cleared) clear();
+            hipStreamSynchronize(c->stream);
+        }
+        if (!host.empty()) explicit_bzero(host.data(), host.size());
+    }
+};
+
 int ensure_temp(she_ctx *c, size_t slots)
 {
     if (slots <= c->temp_slots) return SHE_OK;
@@ -511,20 +547,21 @@ try {
     if (nbits > 0xFFFFFFFFu) return fail(c, SHE_EINVAL, "too many bits for one call");
     // one upload: the count of samples to finish here (0), the ids, the bits, the key bits; their list is behind them
     const size_t upload = (1 + nbits) * 4 + nbits + c->P.n, list = (upload + 3) / 4;
-    std::vector<uint8_t> host;
-    try { host.resize(upload); } catch (const std::bad_alloc &) { return fail(c, SHE_ENOMEM, "host staging"); }
-    std::memset(host.data(), 0, 4);
-    std::memcpy(host.data() + 4, dst_ids, nbits * 4);
-    std::memcpy(host.data() + (1 + nbits) * 4, bits, nbits);
-    std::memcpy(host.data() + (1 + nbits) * 4 + nbits, c->hk.lwe_key.data(), c->P.n);
+    Upload up(c, 1 + nbits, list);
+    try { up.host.resize(upload); } catch (const std::bad_alloc &) { return fail(c, SHE_ENOMEM, "host staging"); }
+    std::memset(up.host.data(), 0, 4);
+    std::memcpy(up.host.data() + 4, dst_ids, nbits * 4);
+    std::memcpy(up.host.data() + (1 + nbits) * 4, bits, nbits);
+    std::memcpy(up.host.data() + (1 + nbits) * 4 + nbits, c->hk.lwe_key.data(), c->P.n);
     if ((rc = ensure_stage(c, list + nbits))) return rc;
     const uint8_t *d_bits = reinterpret_cast<const uint8_t *>(c->d_stage + 1 + nbits);
-    HIP_TRY(c, hipMemcpyAsync(c->d_stage, host.data(), upload, hipMemcpyHostToDevice, c->stream));
+    HIP_TRY(c, up.send());
     HIP_TRY(c, launch_fresh_samples(space(c), c->d_stage + 1, d_bits, d_bits + nbits, c->P.n, fresh_stream_base(enc_seed),
                                     c->P.lwe_std, nbits, c->d_stage, c->d_stage + list, c->stream));
+    HIP_TRY(c, up.clear());
     uint32_t unfinished = 0;
     HIP_TRY(c, hipMemcpyAsync(&unfinished, c->d_stage, 4, hipMemcpyDeviceToHost, c->stream));
-    HIP_TRY(c, hipStreamSynchronize(c->stream));
+    HIP_TRY(c, up.wait());
     if (unfinished) {
         std::vector<uint32_t> samples(unfinished), bodies(unfinished);
         HIP_TRY(c, hipMemcpyAsync(samples.data(), c->d_stage + list, unfinished * 4, hipMemcpyDeviceToHost, c->stream));
@@ -552,17 +589,19 @@ try {
     if (rc) return rc;
     if (count > 0xFFFFFFFFu) return fail(c, SHE_EINVAL, "too many ids for one call");
     const size_t upload = count * 4 + c->P.n, result = (upload + 3) / 4;   // the ids and the key bits; the bits behind them
-    std::vector<uint8_t> host;
-    try { host.resize(upload); } catch (const std::bad_alloc &) { return fail(c, SHE_ENOMEM, "host staging"); }
-    std::memcpy(host.data(), ids, count * 4);
-    std::memcpy(host.data() + count * 4, c->hk.lwe_key.data(), c->P.n);
-    if ((rc = ensure_stage(c, result + (count + 3) / 4))) return rc;
+    const size_t words = result + (count + 3) / 4;
+    Upload up(c, count, words);
+    try { up.host.resize(upload); } catch (const std::bad_alloc &) { return fail(c, SHE_ENOMEM, "host staging"); }
+    std::memcpy(up.host.data(), ids, count * 4);
+    std::memcpy(up.host.data() + count * 4, c->hk.lwe_key.data(), c->P.n);
+    if ((rc = ensure_stage(c, words))) return rc;
     uint8_t *d_bits = reinterpret_cast<uint8_t *>(c->d_stage + result);
-    HIP_TRY(c, hipMemcpyAsync(c->d_stage, host.data(), upload, hipMemcpyHostToDevice, c->stream));
+    HIP_TRY(c, up.send());
     HIP_TRY(c, launch_phase_bits(space(c), c->d_stage, reinterpret_cast<const uint8_t *>(c->d_stage + count), c->P.n, count,
                                  d_bits, c->stream));
     HIP_TRY(c, hipMemcpyAsync(bits_out, d_bits, count, hipMemcpyDeviceToHost, c->stream));
-    HIP_TRY(c, hipStreamSynchronize(c->stream));
+    HIP_TRY(c, up.clear());
+    HIP_TRY(c, up.wait());
     return SHE_OK;
 } SHE_NOTHROW(c)
 

@@ -83,6 +83,8 @@ hipError_t launch_fresh_samples(const CtSpace &cs, const uint32_t *d_ids, const 
 // decryptions: d_bits[k] = sign of the phase of slot d_ids[k]
 hipError_t launch_phase_bits(const CtSpace &cs, const uint32_t *d_ids, const uint8_t *d_key, uint32_t n, size_t count,
                              uint8_t *d_bits, hipStream_t st);
+// zeroes `words` (< 2^32 - 2^18) words
+hipError_t launch_clear_words(uint32_t *d_dst, size_t words, hipStream_t st);
 // diagnostic: `blocks` workgroups of 256 threads, each thread 64*iters dependent-free FP64 instructions of one form
 hipError_t launch_fp64_probe(int form, double *d_out, uint32_t blocks, int iters, const double2 *src, uint32_t src_rows,
                              hipStream_t st);

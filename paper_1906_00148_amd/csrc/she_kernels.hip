@@ -1345,7 +1345,8 @@ __global__ void k_copy_ct(CtSpace cs, const uint32_t *__restrict__ src_ids, cons
 // ------------------------------------------------------------------------------------------
 // Client side: fresh encryptions and phases of samples in the pool, one wavefront per sample.  The random words of a
 // sample's stream are addressed (she_host.cpp has the definition), so every lane makes its own.  Bound by the pool's
-// memory and the call itself (47 and 38 us for 6272 samples of n = 630, the key bits uploaded with each call); on the host's
+// memory and the call itself (48 and 41 us for 6272 samples of n = 630, the key bits uploaded with each call and cleared
+// again at its end, 2 to 3 us of that); on the host's
 // threads, with the pool filled from and read into a staged copy, 1.4 and 1.5 ms.
 // ------------------------------------------------------------------------------------------
 constexpr int CLIENT_WAVES = 4;
@@ -1415,6 +1416,13 @@ __global__ __launch_bounds__(64 * CLIENT_WAVES) void k_phase_bits(CtSpace cs, co
     for (uint32_t i = lane; i < n; i += 64) sum += lwe_key[i] ? ct[i] : 0u;
     sum = wave_sum(sum);
     if (lane == 0) bits[k] = (int32_t)(ct[n] - sum) > 0;
+}
+
+// The words of the staging buffer that held the key's bits and plaintext bits, cleared at the end of a client call.  The
+// launch is all it costs (hipMemsetAsync in its place: 5 to 8 us of the call instead of 1 to 3).
+__global__ __launch_bounds__(256) void k_clear_words(uint32_t *__restrict__ dst, uint32_t words)
+{
+    for (uint32_t w = blockIdx.x * 256 + threadIdx.x; w < words; w += gridDim.x * 256) dst[w] = 0;
 }
 
 // ------------------------------------------------------------------------------------------
@@ -1694,6 +1702,13 @@ hipError_t launch_phase_bits(const CtSpace &cs, const uint32_t *d_ids, const uin
     if (!count) return hipSuccess;
     hipLaunchKernelGGL(k_phase_bits, dim3((unsigned)((count + CLIENT_WAVES - 1) / CLIENT_WAVES)), dim3(64 * CLIENT_WAVES), 0,
                        st, cs, d_ids, d_key, n, (uint32_t)count, d_bits);
+    return hipGetLastError();
+}
+hipError_t launch_clear_words(uint32_t *d_dst, size_t words, hipStream_t st)
+{
+    if (!words) return hipSuccess;
+    const size_t blocks = std::min<size_t>((words + 255) / 256, 1024);
+    hipLaunchKernelGGL(k_clear_words, dim3((unsigned)blocks), dim3(256), 0, st, d_dst, (uint32_t)words);
     return hipGetLastError();
 }
 hipError_t launch_copy_ct(const CtSpace &cs, const uint32_t *d_src_ids, const uint32_t *d_dst_ids, size_t count,
