@@ -145,6 +145,24 @@ try {
     return upload_trlwe(c, samples, count, dst_ids);
 } SHE_NOTHROW(c)
 
+// Samples read without device memory of their own: copied as they lie, reordered on the host.
+static int read_in_place(she_ctx *c, const uint32_t *ids, size_t count, uint32_t *samples)
+{
+    const uint32_t N = c->P.N;
+    const size_t words = (size_t)2 * N;
+    for (size_t k = 0; k < count; k++)
+        HIP_TRY(c, hipMemcpyAsync(samples + k * words, c->lev.trlwe + ids[k] * words, words * 4, hipMemcpyDeviceToHost, c->stream));
+    HIP_TRY(c, hipStreamSynchronize(c->stream));
+    std::vector<uint32_t> dev(words);
+    for (size_t k = 0; k < count; k++) {
+        uint32_t *s = samples + k * words;
+        std::copy(s, s + words, dev.begin());
+        for (uint32_t comp = 0; comp < 2; comp++)
+            for (uint32_t j = 0; j < N; j++) s[comp * N + j] = dev[comp * N + device_pos(N, j)];
+    }
+    return SHE_OK;
+}
+
 int she_trlwe_read(she_ctx *c, const uint32_t *ids, size_t count, uint32_t *samples)
 try {
     if (!c) return SHE_EINVAL;
@@ -155,9 +173,15 @@ try {
     if ((rc = check_range(c, ids, count, c->lev.trlwe_cap, "she_trlwe_read"))) return rc;
     const uint32_t N = c->P.N;
     const size_t words = (size_t)2 * N;
-    // gathered and reordered on the device, then one copy per chunk
+    // gathered and reordered on the device, then one copy per chunk; with the pools filling the memory there may be no room
+    // for that, and a copy per sample has to do
     const size_t step = std::min(count, kReadChunk);
-    if ((rc = ensure_stage(c, step * words + step))) return rc;
+    rc = ensure_stage(c, step * words + step);
+    if (rc == SHE_ENOMEM) {
+        (void)hipGetLastError();                                              // not for the next launch to find
+        return read_in_place(c, ids, count, samples);
+    }
+    if (rc) return rc;
     uint32_t *d_ids = c->d_stage + step * words;
     for (size_t off = 0; off < count; off += step) {
         const size_t cnt = std::min(step, count - off);

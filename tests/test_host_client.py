@@ -21,3 +21,7 @@ def run_on_fake_device(check, tmp_path):
 
 def test_client_calls_leave_no_secret_behind(tmp_path):
     run_on_fake_device("client_check.cpp", tmp_path)
+
+
+def test_samples_are_read_without_device_memory_to_spare(tmp_path):
+    run_on_fake_device("read_check.cpp", tmp_path)
