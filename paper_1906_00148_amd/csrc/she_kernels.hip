@@ -1605,20 +1605,29 @@ static hipError_t blind_rotate_t(const she_params &P, const DeviceKeys &K, size_
         }
     }
     if (split) {
-        // One gate (two wavefronts) or two gates per workgroup.  Measured at n=630, N=1024 on 256 compute units, in ms
-        // for 256 / 512 / 768 / 1024 / 1280 / 1536 gates: one per workgroup 3.4 / 5.1 / 5.3 / 6.2 / 9.2 / 12.1, two per
-        // workgroup 4.2 / 4.2 / 6.2 / 6.3 / 10.1 / 9.8 (the unsplit kernel: 6.5 up to 1024 gates, 10.4 to 11.1 beyond).
-        // What counts is the wavefronts on the fullest compute unit; two workgroups of one gate share a SIMD pair badly.
+        // One gate (two wavefronts) or two gates per workgroup.  What counts is the wavefronts on the fullest compute unit;
+        // two workgroups of one gate share a SIMD pair badly.  Measured at n=630 on 256 compute units, in ms for 256 / 512
+        // / 768 / 1024 / 1280 / 1536 gates, one per workgroup, two per workgroup, and one wavefront per gate:
+        //   N=1024, l=2  2.6 / 3.8 / 4.0 / 4.6 / 6.6 / 8.8   3.2 / 3.2 / 5.0 / 5.0 / 7.5 / 7.4   4.7 to 1024, then 7.2 / 7.3
+        //   N=512, l=3   1.9 / 2.6 / 2.8 / 3.3 / 4.6 / 6.2   2.3 / 2.3 / 3.7 / 3.7 / 5.5 / 5.5   3.8 to 1024, then 5.9
+        //   N=256, l=3   1.4 / 1.8 / 2.1 / 2.5 / 3.1 / 3.7   1.6 / 1.6 / 2.5 / 2.6 / 3.6 / 3.6   3.4 to 1024, then 4.8
+        // (at N=512, l=2 one per workgroup stays ahead at 1536: 3.8 against 4.0).  At N=1024 with l=3 launches of up to two
+        // gates per compute unit run on four wavefronts each and those of five to six go to the mixed kernel, so one per
+        // workgroup is the only form: 513 to 1024 gates, and above them, with SHE_OPT_SPLIT_BELOW raised, what the mixed
+        // kernel does not take.
         const size_t per_cu = (gates + K.cus - 1) / std::max<uint32_t>(K.cus, 1);
-        const bool two = per_cu == 2 || per_cu == 6;
+        const bool triple = P.l == 3;
+        constexpr bool quads = PL::N == HalfPlan::N;
+        const bool two = (per_cu == 2 || per_cu == 6) && !(quads && triple);
         const dim3 grid((unsigned)(two ? (gates + 1) / 2 : gates)), block(two ? 256 : 128);
 #define SHE_LAUNCH_SPLIT(TRACK, GB, LR)                                                                               \
     hipLaunchKernelGGL((k_blind_rotate_split<PL, TRACK, GB, LR>), grid, block, 0, st, W.bar, W.bar_stride, P.n, P.l,  \
                        P.bg_bit, K.bk_hat, K.twiddles, ks_bits, W.ext_b, W.ksd, (uint32_t)gates, d_round_err, cs,     \
                        d_out, raw_ext)
-        const bool triple = P.l == 3;
         if (triple) {
-            if (d_round_err) { if (two) SHE_LAUNCH_SPLIT(true, 2, 3); else SHE_LAUNCH_SPLIT(true, 1, 3); }
+            if constexpr (quads) {
+                if (d_round_err) SHE_LAUNCH_SPLIT(true, 1, 3); else SHE_LAUNCH_SPLIT(false, 1, 3);
+            } else if (d_round_err) { if (two) SHE_LAUNCH_SPLIT(true, 2, 3); else SHE_LAUNCH_SPLIT(true, 1, 3); }
             else { if (two) SHE_LAUNCH_SPLIT(false, 2, 3); else SHE_LAUNCH_SPLIT(false, 1, 3); }
         } else {
             if (d_round_err) { if (two) SHE_LAUNCH_SPLIT(true, 2, 0); else SHE_LAUNCH_SPLIT(true, 1, 0); }
