@@ -95,15 +95,16 @@ def test_cfg2_level_larger_sample_real(real_keys):
 
 def test_repeated_levels_give_identical_words_real():
     """The arithmetic is exact integers, so a level evaluated again must give the same ciphertext words, whatever the
-    order in which wavefronts and workgroups happen to run: full and ragged gate levels through both blind-rotation
-    kernels and the key switch that shares its key bytes through LDS, and a CMux level longer than its grid."""
+    order in which wavefronts and workgroups happen to run: full and ragged gate levels through every blind-rotation
+    kernel (one wavefront per gate, mixed, two, four) and the key switch that shares its key bytes through LDS, and a CMux
+    level longer than its grid."""
     pkg = she()
     G = 4096
     bits, codes = S.cfg2_real_level(G)
     with pkg.Context(pkg.REAL, S.KEY_SEED, 3 * G) as ctx:
         ids = np.arange(2 * G, dtype=np.uint32)
         ctx.encrypt_bits(bits, S.data_seed(2), ids)
-        for n, repeats in ((4096, 3), (2049, 3), (257, 5), (33, 5)):
+        for n, repeats in ((4096, 3), (2049, 3), (700, 5), (257, 5), (33, 5)):
             out = np.arange(2 * G, 2 * G + n, dtype=np.uint32)
             ctx.eval_gates(codes[:n], ids[0:2 * n:2], ids[1:2 * n:2], out)
             first = ctx.read_cts(out)

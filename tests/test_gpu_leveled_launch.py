@@ -8,7 +8,8 @@ import torch
 pytestmark = pytest.mark.gpu
 
 
-@pytest.mark.parametrize("N,l,bg_bit", [(1024, 3, 7), (1024, 2, 8), (1024, 1, 10), (2048, 3, 7), (2048, 2, 8)])
+@pytest.mark.parametrize("N,l,bg_bit", [(1024, 3, 7), (1024, 2, 8), (1024, 1, 10), (1024, 5, 6), (1024, 8, 3),
+                                         (2048, 3, 7), (2048, 2, 8), (2048, 4, 7), (2048, 8, 3)])
 @pytest.mark.parametrize("tracking", [False, True])
 def test_small_levels_of_cmuxes_give_the_same_words(N, l, bg_bit, tracking):
     import paper_1906_00148_amd as pkg

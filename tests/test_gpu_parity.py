@@ -190,7 +190,7 @@ def test_cfg2_real_level(real_ctx, real_keys):
     torch.cuda.synchronize()
     assert np.array_equal(real_ctx.read_cts(out_ids[sub]), pool[out_ids[sub]])
     assert np.array_equal(real_ctx.decrypt(out_ids), want_bits)
-    # the production kernels (tracking off) give the same words: one wavefront per gate, then two
+    # the production kernels (tracking off) give the same words: one wavefront per gate, then four
     pkg = she()
     default_split = real_ctx.get_option(pkg.OPT_SPLIT_BELOW)
     assert default_split >= 1024          # six per compute unit
@@ -199,7 +199,7 @@ def test_cfg2_real_level(real_ctx, real_keys):
             real_ctx.set_option(pkg.OPT_SPLIT_BELOW, split_below)
             real_ctx.eval_gates(codes[sub], in_ids[0::2][sub], in_ids[1::2][sub], out_ids[sub])
             assert np.array_equal(real_ctx.read_cts(out_ids[sub]), pool[out_ids[sub]]), split_below
-        # and the split kernel with tracking on, on a launch that puts two gates in a workgroup
+        # and four wavefronts per gate with tracking on (launches that put two on a gate: test_gpu_launch_sizes.py)
         real_ctx.set_round_tracking(True)
         real_ctx.get_round_error(reset=True)
         first = np.arange(300)
@@ -367,6 +367,7 @@ def test_folded_operators_match_folded_oracle_netlists_toy(toy_ctx, toy_keys):
 
 
 # ------------------------------------------------------------------ native MUX
+# one wavefront per rotation; then two (toy) and four (real parameters, 16 rotations)
 @pytest.mark.parametrize("split_below", [0, 1 << 30])
 def test_eval_mux_bit_exact_toy_and_real(toy_ctx, toy_keys, real_ctx, real_keys, split_below):
     pkg = she()
