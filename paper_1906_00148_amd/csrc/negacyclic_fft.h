@@ -326,17 +326,18 @@ __host__ __device__ __forceinline__ void node_pass_inverse(double (&xr)[P], doub
 // eight consecutive values of a key row in the order that Plan<3, 3> leaves its spectra in, whole 128-byte lines.
 struct HalfPlan {
     static constexpr int P = 4, L = 64, M = 512, N = 1024;
-    static constexpr int XSLOTS = 4 * 68;                       // exchange slots of 16 bytes per wavefront
+    static constexpr int ST1 = 68, LD1 = 4, ST2 = 65, LD2 = 1;  // slots from one register to the next: stores, loads
+    static constexpr int XSLOTS = 4 * ST1;                      // exchange slots of 16 bytes per wavefront
     static constexpr int ROW = 64;                              // plain rows [register][lane] for whole-wavefront hand-overs
     // Slots of the two exchanges: stored at [register][lane], read where the partner bits are.  Sixteen neighbouring
     // lanes read sixteen slots that differ modulo 16 (rows of 68; rows of 65 with the upper lanes moved by one).
-    __host__ __device__ static constexpr int store1(int m, int t) { return m * 68 + t; }
-    __host__ __device__ static constexpr int load1(int m, int t) { return ((t >> 2) & 3) * 68 + (t & 0x33) + 4 * m; }
-    __host__ __device__ static constexpr int store2(int m, int t) { return m * 65 + t + (t >> 5); }
+    __host__ __device__ static constexpr int store1(int m, int t) { return m * ST1 + t; }
+    __host__ __device__ static constexpr int load1(int m, int t) { return ((t >> 2) & 3) * ST1 + (t & 0x33) + LD1 * m; }
+    __host__ __device__ static constexpr int store2(int m, int t) { return m * ST2 + t + (t >> 5); }
     __host__ __device__ static constexpr int load2(int m, int t)
     {
-        return (2 * ((t >> 2) & 1) + (t >> 5)) * 65 + 33 * ((t >> 3) & 1) + 16 * ((t >> 4) & 1) + 8 * (t & 1) +
-               4 * ((t >> 1) & 1) + m;
+        return (2 * ((t >> 2) & 1) + (t >> 5)) * ST2 + 33 * ((t >> 3) & 1) + 16 * ((t >> 4) & 1) + 8 * (t & 1) +
+               4 * ((t >> 1) & 1) + LD2 * m;
     }
     // Twiddle table: two entries (cos, tan) per pass and lane group, [half][entry][group]; passes B (lanes that share
     // k1 k2), C (k1..k4), D (every lane).  Pass A's are the same for the whole wavefront.
@@ -634,20 +635,20 @@ __device__ __forceinline__ void half_pass_b(const HalfCtx &hc, double (&xr)[4], 
     node_pass<4>(xr, xi, e);
     wave_lds_fence();
 #pragma unroll
-    for (int m = 0; m < 4; m++) hc.xch[hc.t + 68 * m] = make_double2(xr[m], xi[m]);
+    for (int m = 0; m < 4; m++) hc.xch[HalfPlan::store1(m, hc.t)] = make_double2(xr[m], xi[m]);
     wave_lds_fence();
 #pragma unroll
-    for (int m = 0; m < 4; m++) { const double2 v = hc.xch[hc.ld1 + 4 * m]; xr[m] = v.x; xi[m] = v.y; }
+    for (int m = 0; m < 4; m++) { const double2 v = hc.xch[hc.ld1 + HalfPlan::LD1 * m]; xr[m] = v.x; xi[m] = v.y; }
 }
 __device__ __forceinline__ void half_pass_c(const HalfCtx &hc, double (&xr)[4], double (&xi)[4], const CosTan (&e)[2])
 {
     node_pass<4>(xr, xi, e);
     wave_lds_fence();
 #pragma unroll
-    for (int m = 0; m < 4; m++) hc.xch[hc.st2 + 65 * m] = make_double2(xr[m], xi[m]);
+    for (int m = 0; m < 4; m++) hc.xch[hc.st2 + HalfPlan::ST2 * m] = make_double2(xr[m], xi[m]);
     wave_lds_fence();
 #pragma unroll
-    for (int m = 0; m < 4; m++) { const double2 v = hc.xch[hc.ld2 + m]; xr[m] = v.x; xi[m] = v.y; }
+    for (int m = 0; m < 4; m++) { const double2 v = hc.xch[hc.ld2 + HalfPlan::LD2 * m]; xr[m] = v.x; xi[m] = v.y; }
 }
 
 // The mirror; out: 256 times the half's values at position 64 m + t.
@@ -657,17 +658,17 @@ __device__ __forceinline__ void inverse_half(const HalfCtx &hc, double (&xr)[4],
     node_pass_inverse<4>(xr, xi, ed);
     wave_lds_fence();
 #pragma unroll
-    for (int m = 0; m < 4; m++) hc.xch[hc.ld2 + m] = make_double2(xr[m], xi[m]);
+    for (int m = 0; m < 4; m++) hc.xch[hc.ld2 + HalfPlan::LD2 * m] = make_double2(xr[m], xi[m]);
     wave_lds_fence();
 #pragma unroll
-    for (int m = 0; m < 4; m++) { const double2 v = hc.xch[hc.st2 + 65 * m]; xr[m] = v.x; xi[m] = v.y; }
+    for (int m = 0; m < 4; m++) { const double2 v = hc.xch[hc.st2 + HalfPlan::ST2 * m]; xr[m] = v.x; xi[m] = v.y; }
     node_pass_inverse<4>(xr, xi, ec);
     wave_lds_fence();
 #pragma unroll
-    for (int m = 0; m < 4; m++) hc.xch[hc.ld1 + 4 * m] = make_double2(xr[m], xi[m]);
+    for (int m = 0; m < 4; m++) hc.xch[hc.ld1 + HalfPlan::LD1 * m] = make_double2(xr[m], xi[m]);
     wave_lds_fence();
 #pragma unroll
-    for (int m = 0; m < 4; m++) { const double2 v = hc.xch[hc.t + 68 * m]; xr[m] = v.x; xi[m] = v.y; }
+    for (int m = 0; m < 4; m++) { const double2 v = hc.xch[HalfPlan::store1(m, hc.t)]; xr[m] = v.x; xi[m] = v.y; }
     node_pass_inverse<4>(xr, xi, eb);
     swap_registers_with_lane_bits54(xr);
     swap_registers_with_lane_bits54(xi);

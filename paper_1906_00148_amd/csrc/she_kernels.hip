@@ -1359,7 +1359,7 @@ __device__ __forceinline__ uint64_t stream_mix(uint64_t z)
 }
 __device__ __forceinline__ uint64_t stream_word(uint64_t key, uint64_t c) { return stream_mix(key + (c + 1) * 0x9E3779B97F4A7C15ull); }
 
-// sum over the lanes whose key bit is set
+// sum over the wavefront's lanes
 __device__ __forceinline__ uint32_t wave_sum(uint32_t v)
 {
 #pragma unroll

@@ -255,7 +255,7 @@ def s4_ctx():
 
 @pytest.mark.parametrize("count", [1, 5, 301])
 def test_cmux_level_bit_exact_ring_degree_2048(s4_ctx, section4_keys, count):
-    """One level of CMuxes at N-bar = 2048 (16 points per lane, node-ordered transforms on two halves), ragged counts;
+    """One level of CMuxes at N-bar = 2048 (four wavefronts per CMux, each half of a transform on its own), ragged counts;
     every TRLWE word against the oracle, the kernel's largest distance from an integer recorded."""
     P = section4_keys.params
     rng = np.random.default_rng(2048 + count)
