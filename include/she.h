@@ -228,12 +228,15 @@ enum { SHE_OPT_FOLD_CONSTANTS = 1, SHE_OPT_NATIVE_MUX = 2, SHE_OPT_SPLIT_BELOW =
 int she_set_option(she_ctx *ctx, int option, int value);
 int she_get_option(she_ctx *ctx, int option, int *value);   /* SHE_EINVAL for an unknown option or a null pointer */
 /* SHE_OPT_SPLIT_BELOW (default: 6 x the device's compute units, 1536 on MI355X): a kernel launch of at
- * most this many blind rotations spreads each one over two wavefronts (one per accumulator component) or four
- * (one per component and half of the spectrum),
+ * most this many blind rotations spreads each one over two wavefronts (one per accumulator component),
  * which shortens the serial chain per CMux when the level is too small to fill the chip; larger launches
- * keep one wavefront per rotation, except that the rotations beyond full rounds of the chip (4 per compute unit), if
- * they are at most two per compute unit and at most this many, run on four each.  0 never splits.  Every ciphertext comes out the same word for word
- * either way (both kernels round exact integers). */
+ * keep one wavefront per rotation.  0 never splits.  At N = 1024 with l = 3 there are two more forms:
+ *  - a launch of at most this many rotations and at most two per compute unit spreads each one over four
+ *    wavefronts (one per component and half of the spectrum);
+ *  - a launch of more than four per compute unit, larger than this option or not, keeps full rounds of four per
+ *    compute unit on one wavefront each and runs the rest on four each, if the rest is at most two per compute
+ *    unit and at most this many rotations.
+ * Every ciphertext comes out the same word for word either way (all kernels round exact integers). */
 /* SHE_OPT_COLUMN_ADDER (default 0; needs SHE_OPT_FOLD_CONSTANTS and SHE_OPT_GATE3_CELLS, else she_shift_acc returns
  * SHE_EINVAL): she_shift_acc sums by column compression instead of adder trees and a subtraction (Section 3.3: adders
  * only as wide as the bits they receive).  Every bit of every shifted term sits in the column of its weight; a

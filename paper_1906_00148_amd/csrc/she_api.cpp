@@ -85,7 +85,7 @@ struct Upload {
             if (!cleared) clear();
             hipStreamSynchronize(c->stream);
         }
-        if (!host.empty()) explicit_bzero(host.data(), host.size());
+        if (host.size() > 4 * first) explicit_bzero(host.data() + 4 * first, host.size() - 4 * first);
     }
 };
 

@@ -261,7 +261,9 @@ __global__ __launch_bounds__(64 * BR_WAVES, 2) void k_blind_rotate(
 }
 
 // ------------------------------------------------------------------------------------------
-// Blind rotation of a small level: one gate per workgroup of two wavefronts.
+// Blind rotation of a small level on two wavefronts per gate, one or two gates per workgroup: at N = 1024 with l = 3 levels
+// of more than two and at most four gates per compute unit (k_blind_rotate_quad has the smaller ones,
+// k_blind_rotate_mixed most of the larger), at other parameters levels of up to six (SHE_OPT_SPLIT_BELOW's default).
 // A level of a few hundred gates leaves most SIMDs with one wavefront or none, and the time of
 // the kernel above is then the latency of one wavefront's serial chain of 6 forward and 2
 // inverse transforms per CMux.  Here wavefront c of a gate owns accumulator component c: it
@@ -1061,7 +1063,8 @@ __global__ __launch_bounds__(256, 2) void k_cmux_quad(const double2 *__restrict_
         dlo[2 * q + 1] = (u[q].z - v[q].z + dec_off) ^ flip; dhi[2 * q + 1] = (u[q].w - v[q].w + dec_off) ^ flip;
     }
     // Selector values of a row: output c ^ 1 is requested a row ahead, output c as well where registers allow (four points
-    // per lane), else once the transform has run (held through it with eight points, 55 registers are spilled).
+    // per lane), else once the transform has run (held through it with eight points, 55 registers are spilled;
+    // as it is, 24: 100 bytes of scratch per lane).
     constexpr bool BOTH_AHEAD = P <= 4;
     double2 km[P], ko[P];
     auto request = [&](double2 (&k)[P], uint32_t p, int o) {
@@ -1346,8 +1349,8 @@ __global__ void k_copy_ct(CtSpace cs, const uint32_t *__restrict__ src_ids, cons
 // Client side: fresh encryptions and phases of samples in the pool, one wavefront per sample.  The random words of a
 // sample's stream are addressed (she_host.cpp has the definition), so every lane makes its own.  Bound by the pool's
 // memory and the call itself (48 and 41 us for 6272 samples of n = 630, the key bits uploaded with each call and cleared
-// again at its end, 2 to 3 us of that); on the host's
-// threads, with the pool filled from and read into a staged copy, 1.4 and 1.5 ms.
+// again at its end, 2 to 3 us of that); on the host's threads, with the pool filled from and read into a staged copy, 1.4
+// and 1.5 ms.
 // ------------------------------------------------------------------------------------------
 constexpr int CLIENT_WAVES = 4;
 
@@ -1501,7 +1504,7 @@ static hipError_t cmux_t(const she_params &P, const DeviceKeys &K, const double2
             return hipGetLastError();
         }
     }
-    // persistent: at most the workgroups per compute unit that fit (two; one at N = 2048), each wavefront loops over its share
+    // persistent: at most the workgroups per compute unit that fit (two), each wavefront loops over its share
     const size_t wgs = (count + BR_WAVES - 1) / BR_WAVES;
     const size_t per_cu = 2;
     const dim3 grid((unsigned)std::min<size_t>(wgs, per_cu * std::max<uint32_t>(K.cus, 1))), block(64 * BR_WAVES);
@@ -1582,7 +1585,8 @@ static hipError_t blind_rotate_t(const she_params &P, const DeviceKeys &K, size_
     const uint32_t ks_bits = P.ks_t * P.ks_basebit;
     const bool split = gates <= split_below;
     if constexpr (PL::N == HalfPlan::N) {
-        // full rounds on one wavefront per gate, the rest on four (measured beside the kernel)
+        // full rounds on one wavefront per gate, the rest on four (measured beside the kernel); this kernel and the next are
+        // built for three digits per coefficient only
         const size_t round = BR_WAVES * (size_t)K.cus, rest = gates % round;
         if (P.l == 3 && gates > round && rest && rest <= std::min<size_t>(2 * (size_t)K.cus, split_below)) {
             const size_t wave_blocks = (gates - rest) / BR_WAVES;
