@@ -675,6 +675,119 @@ __device__ __forceinline__ void inverse_half(const HalfCtx &hc, double (&xr)[4],
     node_pass_inverse<4>(xr, xi, hc.ea);
 }
 
+// ---- half transforms whose last exchange stays in the registers ------------------------------------------------------
+// The same passes as HalfCtx with other bits of the position in the lane index (highest lane bit first):
+//   pass A  lane = b5 b4 b0 b1 b2 b3, register = b7 b6
+//   swap    lane bits 5, 4 <-> register (v_permlane32_swap, v_permlane16_swap)
+//   pass B  lane = k1 k2 b0 b1 b2 b3, register = b5 b4 -> k3 k4
+//   LDS     lane bits 0, 1 <-> register
+//   pass C  lane = k1 k2 b0 b1 k4 k3, register = b3 b2 -> k5 k6
+//   DPP     lane bits 2, 3 <-> register (row shifts that write every other bank of four lanes)
+//   pass D  lane = k1 k2 k6 k5 k4 k3, register = b1 b0 -> k7 k8
+// Eight consecutive lanes still read eight consecutive values of a key row.  The DPP exchange takes 48 instructions (160
+// cycles) of one SIMD; through LDS it takes 60 cycles of the compute unit's LDS pipe (which stores 88 bytes a clock) and a
+// round trip.  Which is better depends on what a kernel is short of: with twelve wavefronts per compute unit it is LDS.
+template <int CTRL, int BANKS> __device__ __forceinline__ double dpp_merge(double old, double from)
+{
+    const int lo = __builtin_amdgcn_update_dpp(__double2loint(old), __double2loint(from), CTRL, 0xF, BANKS, false);
+    const int hi = __builtin_amdgcn_update_dpp(__double2hiint(old), __double2hiint(from), CTRL, 0xF, BANKS, false);
+    return __hiloint2double(hi, lo);
+}
+// lane bit 2 (or 3) <-> register: lanes with the bit set take b of the lane below into a, the others a of the lane above into b
+__device__ __forceinline__ void swap_lane_bit2(double &a, double &b)
+{
+    const double a0 = a;
+    a = dpp_merge<0x114, 0xA>(a, b);              // row_shr:4 into lanes 4-7 and 12-15
+    b = dpp_merge<0x104, 0x5>(b, a0);             // row_shl:4 into lanes 0-3 and 8-11
+}
+__device__ __forceinline__ void swap_lane_bit3(double &a, double &b)
+{
+    const double a0 = a;
+    a = dpp_merge<0x118, 0xC>(a, b);              // row_shr:8 into lanes 8-15
+    b = dpp_merge<0x108, 0x3>(b, a0);             // row_shl:8 into lanes 0-7
+}
+__device__ __forceinline__ void swap_registers_with_lane_bits23(double (&x)[4])
+{
+    swap_lane_bit2(x[0], x[2]); swap_lane_bit2(x[1], x[3]);
+    swap_lane_bit3(x[0], x[1]); swap_lane_bit3(x[2], x[3]);
+}
+
+struct HalfLanes {
+    using HP = HalfPlan;
+    static constexpr int ROW = 65;                   // exchange: stored at [register][lane], read where the partner bits are
+    static constexpr int XSLOTS = 4 * ROW;
+    int t, h, ld;
+    double2 *xch;
+    const double2 *tw;
+    CosTan ea[2];
+    // position of lane t within 64, and the lanes of HalfPlan that hold the same frequency bits before passes C and D
+    static __host__ __device__ constexpr int position(int t)
+    {
+        return (t & 0x30) | ((t & 1) << 3) | ((t & 2) << 1) | ((t & 4) >> 1) | ((t & 8) >> 3);
+    }
+    static __host__ __device__ constexpr int plan_lane_c(int t) { return (t & 0x30) | ((t & 1) << 3) | ((t & 2) << 1); }
+    static __host__ __device__ constexpr int plan_lane_d(int t)
+    {
+        return (t & 7) | ((t & 8) << 2) | (t & 0x10) | ((t & 0x20) >> 2);
+    }
+    static __host__ __device__ constexpr int load(int m, int t)
+    {
+        return (2 * (t & 1) + ((t >> 1) & 1)) * ROW + (t & 0x3C) + (m >> 1) + 2 * (m & 1);
+    }
+
+    __device__ __forceinline__ void init(int lane, int half, double2 *xbuf, const double2 *table)
+    {
+        t = lane; h = half; xch = xbuf; tw = table;
+        ld = load(0, t);
+        for (int e = 0; e < 2; e++) ea[e] = h ? HP::first_entry(1, e) : HP::first_entry(0, e);
+    }
+    template <int PASS> __device__ __forceinline__ void entries(CosTan (&e)[2]) const
+    {
+        const int lane = PASS == 1 ? t : PASS == 2 ? plan_lane_c(t) : plan_lane_d(t);
+#pragma unroll
+        for (int q = 0; q < 2; q++) { const double2 v = tw[HP::entry(PASS, h, q, lane)]; e[q].c = v.x; e[q].t = v.y; }
+    }
+    __device__ __forceinline__ int key_lane() const { return HP::key_lane(h, plan_lane_d(t)); }
+
+    __device__ __forceinline__ void forward(double (&xr)[4], double (&xi)[4], const CosTan (&eb)[2], const CosTan (&ec)[2],
+                                            const CosTan (&ed)[2]) const
+    {
+        node_pass<4>(xr, xi, ea);
+        swap_registers_with_lane_bits54(xr);
+        swap_registers_with_lane_bits54(xi);
+        node_pass<4>(xr, xi, eb);
+        wave_lds_fence();
+#pragma unroll
+        for (int m = 0; m < 4; m++) xch[m * ROW + t] = make_double2(xr[m], xi[m]);
+        wave_lds_fence();
+#pragma unroll
+        for (int m = 0; m < 4; m++) { const double2 v = xch[ld + (m >> 1) + 2 * (m & 1)]; xr[m] = v.x; xi[m] = v.y; }
+        node_pass<4>(xr, xi, ec);
+        swap_registers_with_lane_bits23(xr);
+        swap_registers_with_lane_bits23(xi);
+        node_pass<4>(xr, xi, ed);
+    }
+    // out: 256 times the half's values at position 64 m + position(t)
+    __device__ __forceinline__ void inverse(double (&xr)[4], double (&xi)[4], const CosTan (&eb)[2], const CosTan (&ec)[2],
+                                            const CosTan (&ed)[2]) const
+    {
+        node_pass_inverse<4>(xr, xi, ed);
+        swap_registers_with_lane_bits23(xr);
+        swap_registers_with_lane_bits23(xi);
+        node_pass_inverse<4>(xr, xi, ec);
+        wave_lds_fence();
+#pragma unroll
+        for (int m = 0; m < 4; m++) xch[ld + (m >> 1) + 2 * (m & 1)] = make_double2(xr[m], xi[m]);
+        wave_lds_fence();
+#pragma unroll
+        for (int m = 0; m < 4; m++) { const double2 v = xch[m * ROW + t]; xr[m] = v.x; xi[m] = v.y; }
+        node_pass_inverse<4>(xr, xi, eb);
+        swap_registers_with_lane_bits54(xr);
+        swap_registers_with_lane_bits54(xi);
+        node_pass_inverse<4>(xr, xi, ea);
+    }
+};
+
 // The halves of a transform for kernels that give each one a wavefront: 2 P0 lanes' worth of points, P0 = POINTS per lane,
 // from the end of stage 0 (position 64 m + t of the half in register m) to the key rows' order and back.
 template <int N> struct HalfTransform;

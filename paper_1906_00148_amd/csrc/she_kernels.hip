@@ -483,8 +483,8 @@ __global__ __launch_bounds__(128 * GB, 2) void k_blind_rotate_split(
 }
 
 // ------------------------------------------------------------------------------------------
-// Blind rotation of a level of at most two gates per compute unit: one gate per workgroup of four wavefronts (N = 1024,
-// l = LR).  What bounds such a level is the length of one gate's chain of n CMuxes, so the chain is cut as far as the
+// Blind rotation of a level of more than one and at most two gates per compute unit, and of the rest of a larger one beyond
+// full rounds (k_blind_rotate_mixed): one gate per workgroup of four wavefronts (N = 1024, l = LR).  What bounds such a level is the length of one gate's chain of n CMuxes, so the chain is cut as far as the
 // transforms allow without a wavefront waiting for another inside one.
 // Wavefront (c, h) owns accumulator component c and half h of the spectrum (HalfPlan): it cuts the digits of all of
 // D_c = X^abar ACC_c - ACC_c, runs the first stage of its LR transforms for half h only and then LR transforms of 256
@@ -694,6 +694,224 @@ __global__ __launch_bounds__(256, 2) void k_blind_rotate_quad(
     __shared__ QuadShared sh;
     rotate_by_quad<TRACK, LR>(sh, blockIdx.x, bar, bar_stride, n, bg_bit, bk_hat, half_table, ks_bits, ext_b, ksd, round_err,
                               cs, out_ids, raw_ext);
+}
+
+// ------------------------------------------------------------------------------------------
+// Blind rotation of a level of at most one gate per compute unit: one gate per workgroup of twelve wavefronts (N = 1024,
+// l = 3), three on a SIMD, so that one's LDS round trips and dependent FP64 instructions are filled by the others.
+// Wavefront (p, c, h) transforms digit p of D_c = X^abar ACC_c - ACC_c for half h of the spectrum and leaves it in LDS.
+// After a barrier the wavefronts with p = 0 (one on each SIMD) form output component c's half from all 2 l rows, read a few
+// values ahead of the products, and transform it back; after a second barrier those with p > 0 join the halves, keep the
+// accumulator (four coefficients per lane) and publish ACC and X^abar ACC for the next step.
+// The key: 96 KB per step and compute unit enter through its one path of 64 bytes a clock, 1500 cycles of a step's 6500,
+// and a wavefront that issues loads faster than that stands still (all 24 between the products: +1100 cycles).  So the
+// wavefronts that multiply hold a step's 24 values in registers and request half of them while the others publish, half
+// at the head of the next transform, where they finish early anyway.  With the values of one output component
+// in flight a step or half a step ahead it matters less, too, whether the key comes from HBM or from the Infinity Cache.
+// Cycles of a step: transforms 3700 (3 x 200 vector instructions on a SIMD, of which 112 FP64, 32 lane exchanges, and half
+// of the LDS pipe's time), products 700, inverse 1250, joining and publishing 700, barriers 300 each.
+// Measured at n = 630, us per call of 1 / 83 gates whose key comes from HBM: 2665 / 2496 with k_blind_rotate_quad,
+// 2051 / 2001 so.  Eight wavefronts (four of them with two digits each) take as long as the four of k_blind_rotate_quad.
+// With more than one gate per compute unit a second workgroup does not fit (118 KB of LDS, 162 registers x 12) and two
+// rounds take longer than k_blind_rotate_quad's one (3.6 ms).
+// ------------------------------------------------------------------------------------------
+struct WideShared {
+    uint32_t rot[2][HalfPlan::N];                                  // X^abar ACC, plain order
+    uint4 base[2][2][2][64];                                       // ACC - offset: [component][half][upper 512][lane], words m
+    double2 xch[12][HalfLanes::XSLOTS];
+    double2 spec[2][3][2][4 * HalfPlan::ROW];                      // [component][digit][half]: a digit's half spectrum
+    double2 tw[HalfPlan::COUNT];
+};
+
+template <bool TRACK>
+__global__ __launch_bounds__(768, 3) void k_blind_rotate_wide(
+    const uint16_t *__restrict__ bar, uint32_t bar_stride, uint32_t n, uint32_t bg_bit,
+    const double2 *__restrict__ bk_hat, const double2 *__restrict__ half_table, uint32_t ks_bits,
+    uint32_t *__restrict__ ext_b, uint16_t *__restrict__ ksd, unsigned *round_err, CtSpace cs,
+    const uint32_t *__restrict__ out_ids, uint32_t *__restrict__ raw_ext)
+{
+    using HP = HalfPlan;
+    constexpr int N = HP::N, L = HP::L, LR = 3, THREADS = 768;
+    __shared__ WideShared sh;
+    const uint32_t g = blockIdx.x;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), t = threadIdx.x & 63;
+    const int p = wave >> 2, c = (wave >> 1) & 1, h = wave & 1;
+    for (int e = threadIdx.x; e < HP::COUNT; e += THREADS) sh.tw[e] = half_table[e];
+    __syncthreads();
+    HalfLanes hc;
+    hc.init(t, h, sh.xch[wave], sh.tw);
+    const uint16_t *mybar = bar + (size_t)g * bar_stride;
+
+    const uint32_t half_bg = 1u << (bg_bit - 1);
+    uint32_t dec_off = 1u << (31 - LR * bg_bit);
+    uint32_t flip = 0;      // top bit of every digit field: field ^ top, read as signed, is field - Bg/2
+#pragma unroll
+    for (int q = 1; q <= LR; q++) { dec_off += half_bg << (32 - q * bg_bit); flip |= half_bg << (32 - q * bg_bit); }
+    const uint32_t digit_sh = 32 - (p + 1) * bg_bit;
+    float worst = 0.f;
+    const double cs1 = h ? -0.70710678118654752440 : 0.70710678118654752440; // +-cos(pi/4) of the first stage
+    CosTan eb[2], ec[2], ed[2];
+    hc.entries<1>(eb); hc.entries<2>(ec); hc.entries<3>(ed);
+
+    // Coefficients kept by a wavefront with p > 0: v[m] at pos + 64 (4h + 2u + m), u = p - 1, v[2 + m] at 512 more.
+    uint32_t v[4];
+    const int u = p - 1, pos = HalfLanes::position(t), own = pos + 256 * h + 128 * u;
+    auto publish = [&](uint32_t abar) {
+        const uint32_t x0 = 4 * ((uint32_t)own + abar);
+        char *const rot = reinterpret_cast<char *>(sh.rot[c]);
+#pragma unroll
+        for (int q = 0; q < 2; q++)
+            reinterpret_cast<uint2 *>(&sh.base[c][h][q][t])[u] = make_uint2(v[2 * q] - dec_off, v[2 * q + 1] - dec_off);
+#pragma unroll
+        for (int q = 0; q < 4; q++) {
+            const uint32_t x = x0 + 256 * (q & 1) + 2048 * (q >> 1);          // 4 * (j + abar): bit 12 is the sign
+            const uint32_t neg = (uint32_t)__builtin_amdgcn_sbfe((int)x, 12, 1);
+            *reinterpret_cast<uint32_t *>(rot + (x & (4 * N - 1))) = (v[q] ^ neg) - neg;
+        }
+    };
+    // digit p of D_c, transformed for half h
+    auto transform = [&](double (&xr)[4], double (&xi)[4]) {
+        uint32_t dlo[8], dhi[8];
+#pragma unroll
+        for (int b = 0; b < 2; b++) {
+            const uint4 lo = sh.base[c][b][0][t], hi = sh.base[c][b][1][t];
+            const uint32_t l4[4] = {lo.x, lo.y, lo.z, lo.w}, h4[4] = {hi.x, hi.y, hi.z, hi.w};
+#pragma unroll
+            for (int m = 0; m < 4; m++) {
+                dlo[4 * b + m] = (sh.rot[c][pos + L * (4 * b + m)] - l4[m]) ^ flip;
+                dhi[4 * b + m] = (sh.rot[c][pos + L * (4 * b + m) + 512] - h4[m]) ^ flip;
+            }
+        }
+#pragma unroll
+        for (int m = 0; m < 4; m++) {
+            const int ar = (int)__builtin_amdgcn_sbfe((int)dlo[m], digit_sh, bg_bit), ai = (int)__builtin_amdgcn_sbfe((int)dhi[m], digit_sh, bg_bit);
+            const int br = (int)__builtin_amdgcn_sbfe((int)dlo[m + 4], digit_sh, bg_bit), bi = (int)__builtin_amdgcn_sbfe((int)dhi[m + 4], digit_sh, bg_bit);
+            xr[m] = __builtin_fma(cs1, (double)(br - bi), (double)ar);
+            xi[m] = __builtin_fma(cs1, (double)(br + bi), (double)ai);
+        }
+        hc.forward(xr, xi, eb, ec, ed);
+#pragma unroll
+        for (int m = 0; m < 4; m++) sh.spec[c][p][h][m * HP::ROW + t] = make_double2(xr[m], xi[m]);
+    };
+    // last stage: (y0 + y1) / 512 for half 0, conj(w) (y0 - y1) / 512 for half 1; adding 1.5*2^52 leaves the rounded
+    // value modulo 2^32 in the low word
+    auto finish = [&]() {
+        constexpr double magic = 6755399441055744.0, scale = 1.0 / 512, rot = 0.70710678118654752440 / 512;
+#pragma unroll
+        for (int m = 0; m < 2; m++) {
+            const double2 y0 = sh.xch[2 * c][(2 * u + m) * HP::ROW + t], y1 = sh.xch[2 * c + 1][(2 * u + m) * HP::ROW + t];
+            double re, im, f;
+            if (h == 0) {
+                re = y0.x + y1.x; im = y0.y + y1.y; f = scale;
+            } else {
+                const double dr = y0.x - y1.x, di = y0.y - y1.y;
+                re = dr + di; im = di - dr; f = rot;
+            }
+            if (TRACK) {
+                worst = fmaxf(worst, (float)fabs(re * f - rint(re * f)));
+                worst = fmaxf(worst, (float)fabs(im * f - rint(im * f)));
+            }
+            v[m] += (uint32_t)__double2loint(__builtin_fma(re, f, magic));
+            v[2 + m] += (uint32_t)__double2loint(__builtin_fma(im, f, magic));
+        }
+    };
+
+    if (p == 0) {
+        // the key values of the own output component, all 2 LR rows, requested a step ahead as their registers become free
+        const double2 *key = bk_hat + c * HP::M + hc.key_lane();
+        constexpr size_t row_elems = (size_t)2 * HP::M;
+        double2 kv[2 * LR][4];
+        auto request = [&](uint32_t step, int r) {
+            const double2 *row = key + ((size_t)step * 2 * LR + (r < LR ? c * LR + r : (c ^ 1) * LR + r - LR)) * row_elems;
+#pragma unroll
+            for (int m = 0; m < 4; m++) kv[r][m] = row[HP::key_reg(m)];
+        };
+        for (uint32_t i = 0; i < n; i++) {
+#pragma unroll
+            for (int r = 0; r < LR; r++) request(i, r);
+            lds_barrier();
+#pragma unroll
+            for (int r = LR; r < 2 * LR; r++) request(i, r);
+            __builtin_amdgcn_sched_barrier(0);
+            double xr[4], xi[4], mr[4], mi[4];
+            transform(xr, xi);
+#pragma unroll
+            for (int m = 0; m < 4; m++) {
+                const double2 b = kv[0][m];
+                mr[m] = __builtin_fma(-xi[m], b.y, xr[m] * b.x);
+                mi[m] = __builtin_fma(xi[m], b.x, xr[m] * b.y);
+            }
+            // the other rows' spectra are read AHEAD values ahead of the products
+            constexpr int AHEAD = 6, VALUES = 4 * (2 * LR - 1);
+            double2 x[AHEAD];
+            auto value = [&](int q) {
+                const int r = 1 + q / 4;
+                return (r < LR ? sh.spec[c][r][h] : sh.spec[c ^ 1][r - LR][h])[(q % 4) * HP::ROW + t];
+            };
+            lds_barrier();
+#pragma unroll
+            for (int q = 0; q < AHEAD; q++) x[q] = value(q);
+#pragma unroll
+            for (int q = 0; q < VALUES; q++) {
+                const int r = 1 + q / 4, m = q % 4;
+                const double2 w = x[q % AHEAD], b = kv[r][m];
+                if (q + AHEAD < VALUES) x[q % AHEAD] = value(q + AHEAD);
+                mr[m] = __builtin_fma(-w.y, b.y, __builtin_fma(w.x, b.x, mr[m]));
+                mi[m] = __builtin_fma(w.y, b.x, __builtin_fma(w.x, b.y, mi[m]));
+            }
+            __builtin_amdgcn_sched_barrier(0);
+            hc.inverse(mr, mi, eb, ec, ed);
+            wave_lds_fence();
+#pragma unroll
+            for (int m = 0; m < 4; m++) hc.xch[m * HP::ROW + t] = make_double2(mr[m], mi[m]);
+            lds_barrier();
+        }
+    } else {
+        // ACC = (0, X^(-bbar) * testv)
+        const uint32_t bbar = mybar[n];
+#pragma unroll
+        for (int q = 0; q < 4; q++) {
+            const uint32_t j = own + 64 * (q & 1) + 512 * (q >> 1);
+            v[q] = c == 0 ? 0u : (((j + bbar) & N) ? 0u - (1u << 29) : (1u << 29));
+        }
+        publish(mybar[0]);
+        for (uint32_t i = 0; i < n; i++) {
+            const uint32_t abar_next = mybar[i + 1];                              // i + 1 == n reads bbar: harmless
+            lds_barrier();
+            double xr[4], xi[4];
+            transform(xr, xi);
+            lds_barrier();
+            lds_barrier();
+            finish();
+            publish(abar_next);
+        }
+    }
+    if (TRACK && p && round_err) atomicMax(round_err, __float_as_uint(worst));
+    lds_barrier();
+
+    // sample extraction by the whole workgroup: a''_0 = A_0, a''_j = -A_{N-j}, b'' = B_0
+    auto word = [&](int comp, int j) {
+        const uint32_t *w = reinterpret_cast<const uint32_t *>(sh.base[comp]);
+        return w[((((j >> 8) & 1) * 2 + (j >> 9)) * 64 + HalfLanes::position(j & 63)) * 4 + ((j >> 6) & 3)] + dec_off;
+    };
+    const uint32_t body = word(1, 0);
+    if (raw_ext) {
+        uint32_t *dst = raw_ext + (size_t)g * (N + 1);
+        for (int j = threadIdx.x; j < N; j += THREADS) dst[j] = (j == 0) ? word(0, 0) : 0u - word(0, N - j);
+        if (threadIdx.x == 0) dst[N] = body;
+    } else {
+        const uint32_t rnd = 1u << (31 - ks_bits), sft = 32 - ks_bits;
+        uint16_t *dst = ksd + ((size_t)(g / KS_GROUP) * N) * KS_GROUP + (g % KS_GROUP);
+        for (int j = threadIdx.x; j < N; j += THREADS) {
+            const uint32_t a = (j == 0) ? word(0, 0) : 0u - word(0, N - j);
+            dst[(size_t)j * KS_GROUP] = (uint16_t)((a + rnd) >> sft);
+        }
+        if (threadIdx.x == 0) ext_b[g] = body;
+        if (out_ids) {                       // the key switch subtracts its rows from (0, b'')
+            uint32_t *o = ct_ptr(cs, out_ids[g]);
+            for (uint32_t w = threadIdx.x; w <= n; w += THREADS) o[w] = (w == n) ? body : 0u;
+        }
+    }
 }
 
 // Both in one launch: workgroups below `wave_blocks` run four gates on a wavefront each, every later one a single gate on
@@ -1596,6 +1814,15 @@ static hipError_t blind_rotate_t(const she_params &P, const DeviceKeys &K, size_
                        W.ksd, (uint32_t)wave_blocks, d_round_err, cs, d_out, raw_ext)
             if (d_round_err) SHE_LAUNCH_MIXED(true); else SHE_LAUNCH_MIXED(false);
 #undef SHE_LAUNCH_MIXED
+            return hipGetLastError();
+        }
+        // up to one gate per compute unit: twelve wavefronts per gate (measured beside the kernel)
+        if (split && P.l == 3 && gates <= K.cus) {
+#define SHE_LAUNCH_WIDE(TRACK)                                                                                         \
+    hipLaunchKernelGGL((k_blind_rotate_wide<TRACK>), dim3((unsigned)gates), dim3(768), 0, st, W.bar, W.bar_stride,   \
+                       P.n, P.bg_bit, K.bk_hat, K.half_twiddles, ks_bits, W.ext_b, W.ksd, d_round_err, cs, d_out, raw_ext)
+            if (d_round_err) SHE_LAUNCH_WIDE(true); else SHE_LAUNCH_WIDE(false);
+#undef SHE_LAUNCH_WIDE
             return hipGetLastError();
         }
         // up to two gates per compute unit: four wavefronts per gate (measured beside the kernel)
