@@ -767,26 +767,82 @@ struct HalfLanes {
         swap_registers_with_lane_bits23(xi);
         node_pass<4>(xr, xi, ed);
     }
-    // out: 256 times the half's values at position 64 m + position(t)
-    __device__ __forceinline__ void inverse(double (&xr)[4], double (&xi)[4], const CosTan (&eb)[2], const CosTan (&ec)[2],
-                                            const CosTan (&ed)[2]) const
+};
+
+// ---- inverse quarter transforms -------------------------------------------------------------------------------------
+// The second stage of the node-ordered transform splits a half into two transforms of 128 points that never meet again:
+// quarter (h, k1) has the frequencies k = h + 2 k1 + 4 k'.  Two points per lane, one stage at a time, and every exchange is
+// one lane bit against the register, in the registers:
+//   lane = k7 k2 k6 k5 k4 k3, register = k8; stage 8; lane bit 5 <-> register; stage 7; bit 3; stage 6; bit 2; stage 5;
+//   bit 1; stage 4; bit 0; stage 3; bit 4; stage 2; then lane = b0 b5 b1 b2 b3 b4, register = b6.
+// lane bit 1 (or 0) <-> register: row shifts cannot pick lanes inside a bank of four, so what a lane sends is selected first
+template <int QUAD_PERM> __device__ __forceinline__ void swap_in_quad(double &a, double &b, bool bit)
+{
+    const int alo = __double2loint(a), ahi = __double2hiint(a), blo = __double2loint(b), bhi = __double2hiint(b);
+    const int rlo = __builtin_amdgcn_mov_dpp(bit ? alo : blo, QUAD_PERM, 0xF, 0xF, true);
+    const int rhi = __builtin_amdgcn_mov_dpp(bit ? ahi : bhi, QUAD_PERM, 0xF, 0xF, true);
+    a = __hiloint2double(bit ? rhi : ahi, bit ? rlo : alo);
+    b = __hiloint2double(bit ? bhi : rhi, bit ? blo : rlo);
+}
+
+struct QuarterInverse {
+    static constexpr int COUNT = 508;                // entry of stage s (2..8), node R < 2^s, at 2^s - 4 + R
+    // slot of a half's spectrum (register m * 64 + lane, HalfLanes' last order), register 0; 64 more for register 1
+    static __host__ __device__ constexpr int spectrum_slot(int k1, int t) { return 128 * (t >> 5) + 32 * k1 + (t & 31); }
+    // place in a key row's component, register 0; 256 more for register 1
+    static __host__ __device__ constexpr int key_place(int h, int k1, int t)
     {
-        node_pass_inverse<4>(xr, xi, ed);
-        swap_registers_with_lane_bits23(xr);
-        swap_registers_with_lane_bits23(xi);
-        node_pass_inverse<4>(xr, xi, ec);
-        wave_lds_fence();
+        return (t & 7) + 8 * h + 16 * k1 + 32 * ((t >> 4) & 1) + 64 * ((t >> 3) & 1) + 128 * (t >> 5);
+    }
+    static __host__ __device__ constexpr int node(int h, int k1, int t)
+    {
+        return h + 2 * k1 + 4 * ((t >> 4) & 1) + 8 * (t & 7) + 64 * ((t >> 3) & 1) + 128 * (t >> 5);
+    }
+    // position in the quarter of register 0; 64 more for register 1
+    static __host__ __device__ constexpr int position(int t)
+    {
+        return ((t >> 5) & 1) | ((t >> 2) & 2) | (t & 4) | ((t & 2) << 2) | ((t & 1) << 4) | ((t & 16) << 1);
+    }
+
+    CosTan e[7];                                     // of stages 2..8
+    bool bit0, bit1;
+    __device__ __forceinline__ void init(int h, int k1, int t, const double2 *tw)
+    {
+        const int R = node(h, k1, t);
 #pragma unroll
-        for (int m = 0; m < 4; m++) xch[ld + (m >> 1) + 2 * (m & 1)] = make_double2(xr[m], xi[m]);
-        wave_lds_fence();
-#pragma unroll
-        for (int m = 0; m < 4; m++) { const double2 v = xch[m * ROW + t]; xr[m] = v.x; xi[m] = v.y; }
-        node_pass_inverse<4>(xr, xi, eb);
-        swap_registers_with_lane_bits54(xr);
-        swap_registers_with_lane_bits54(xi);
-        node_pass_inverse<4>(xr, xi, ea);
+        for (int s = 2; s <= 8; s++) { const double2 v = tw[(1 << s) - 4 + (R & ((1 << s) - 1))]; e[s - 2].c = v.x; e[s - 2].t = v.y; }
+        bit0 = t & 1; bit1 = t & 2;
+    }
+    // out: 128 times the quarter's values
+    __device__ __forceinline__ void run(double (&xr)[2], double (&xi)[2]) const
+    {
+        auto stage = [&](int s) { node_butterfly_inverse<false>(xr[0], xi[0], xr[1], xi[1], e[s - 2].c, e[s - 2].t); };
+        stage(8);
+        swap_lane_bit5(xr[0], xr[1]); swap_lane_bit5(xi[0], xi[1]);
+        stage(7);
+        swap_lane_bit3(xr[0], xr[1]); swap_lane_bit3(xi[0], xi[1]);
+        stage(6);
+        swap_lane_bit2(xr[0], xr[1]); swap_lane_bit2(xi[0], xi[1]);
+        stage(5);
+        swap_in_quad<0x4E>(xr[0], xr[1], bit1); swap_in_quad<0x4E>(xi[0], xi[1], bit1);        // quad_perm 2 3 0 1
+        stage(4);
+        swap_in_quad<0xB1>(xr[0], xr[1], bit0); swap_in_quad<0xB1>(xi[0], xi[1], bit0);        // quad_perm 1 0 3 2
+        stage(3);
+        swap_lane_bit4(xr[0], xr[1]); swap_lane_bit4(xi[0], xi[1]);
+        stage(2);
     }
 };
+
+inline void make_quarter_twiddles(double *out /* [QuarterInverse::COUNT][2] */)
+{
+    const long double pi = 3.14159265358979323846264338327950288L;
+    for (int s = 2; s <= 8; s++)
+        for (int R = 0; R < 1 << s; R++) {
+            double *o = out + 2 * (size_t)((1 << s) - 4 + R);
+            o[0] = (double)cosl(pi * node_angle(s, R));
+            o[1] = (double)tanl(pi * node_angle(s, R));
+        }
+}
 
 // The halves of a transform for kernels that give each one a wavefront: 2 P0 lanes' worth of points, P0 = POINTS per lane,
 // from the end of stage 0 (position 64 m + t of the half in register m) to the key rows' order and back.

@@ -700,27 +700,28 @@ __global__ __launch_bounds__(256, 2) void k_blind_rotate_quad(
 // Blind rotation of a level of at most one gate per compute unit: one gate per workgroup of twelve wavefronts (N = 1024,
 // l = 3), three on a SIMD, so that one's LDS round trips and dependent FP64 instructions are filled by the others.
 // Wavefront (p, c, h) transforms digit p of D_c = X^abar ACC_c - ACC_c for half h of the spectrum and leaves it in LDS.
-// After a barrier the wavefronts with p = 0 (one on each SIMD) form output component c's half from all 2 l rows, read a few
-// values ahead of the products, and transform it back; after a second barrier those with p > 0 join the halves, keep the
-// accumulator (four coefficients per lane) and publish ACC and X^abar ACC for the next step.
-// The key: 96 KB per step and compute unit enter through its one path of 64 bytes a clock, 1500 cycles of a step's 6500,
-// and a wavefront that issues loads faster than that stands still (all 24 between the products: +1100 cycles).  So the
-// wavefronts that multiply hold a step's 24 values in registers and request half of them while the others publish, half
-// at the head of the next transform, where they finish early anyway.  With the values of one output component
-// in flight a step or half a step ahead it matters less, too, whether the key comes from HBM or from the Infinity Cache.
-// Cycles of a step: transforms 3700 (3 x 200 vector instructions on a SIMD, of which 112 FP64, 32 lane exchanges, and half
-// of the LDS pipe's time), products 700, inverse 1250, joining and publishing 700, barriers 300 each.
-// Measured at n = 630, us per call of 1 / 83 gates whose key comes from HBM: 2665 / 2496 with k_blind_rotate_quad,
-// 2051 / 2001 so.  Eight wavefronts (four of them with two digits each) take as long as the four of k_blind_rotate_quad.
-// With more than one gate per compute unit a second workgroup does not fit (118 KB of LDS, 162 registers x 12) and two
-// rounds take longer than k_blind_rotate_quad's one (3.6 ms).
+// After a barrier the eight with p < 2 form output component c's quarter (h, k1 = p) from all 2 l rows, read a few values
+// ahead of the products, and transform it back (QuarterInverse); after a second barrier the eight with p > 0 join the
+// quarters, keep the accumulator (four coefficients per lane) and publish ACC and X^abar ACC for the next step.
+// The key: 96 KB per step and compute unit enter through its one path of 64 bytes a clock, 1500 cycles of a step's 6000,
+// and a wavefront that issues loads faster than that stands still.  So a step's twelve values per multiplying wavefront wait
+// in registers, requested by one half of them while the others publish and by the other half at the head of the next
+// transform; it matters less so, too, whether the key comes from HBM or from the Infinity Cache.
+// Cycles of a step: transforms 3300 (3 x 200 vector instructions on a SIMD, 900 cycles each, of which 112 are FP64 and 48
+// exchange lanes), products 700, inverse 700, joining and publishing 850, barriers.  The vector ALU is busy in about three
+// quarters of them.
+// Measured at n = 630, us per call of 1 / 83 gates whose key comes from HBM: 2665 / 2496 with k_blind_rotate_quad, 1939 /
+// 1896 so (2051 / 2001 with the inverse transforms in four wavefronts, a half each; eight wavefronts in all, four of them
+// with two digits, take as long as the four of k_blind_rotate_quad).
+// With more than one gate per compute unit a second workgroup does not fit (126 KB of LDS, 162 registers x 12) and two
+// rounds take as long as k_blind_rotate_quad's one (3.6 ms).
 // ------------------------------------------------------------------------------------------
 struct WideShared {
     uint32_t rot[2][HalfPlan::N];                                  // X^abar ACC, plain order
-    uint4 base[2][2][2][64];                                       // ACC - offset: [component][half][upper 512][lane], words m
+    uint4 base[2][2][2][64];                                       // ACC - offset: [component][block of 256][upper 512][lane], word 2u + m: + 64u + 128m
     double2 xch[12][HalfLanes::XSLOTS];
     double2 spec[2][3][2][4 * HalfPlan::ROW];                      // [component][digit][half]: a digit's half spectrum
-    double2 tw[HalfPlan::COUNT];
+    double2 tw[HalfPlan::COUNT + QuarterInverse::COUNT];
 };
 
 template <bool TRACK>
@@ -736,7 +737,7 @@ __global__ __launch_bounds__(768, 3) void k_blind_rotate_wide(
     const uint32_t g = blockIdx.x;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), t = threadIdx.x & 63;
     const int p = wave >> 2, c = (wave >> 1) & 1, h = wave & 1;
-    for (int e = threadIdx.x; e < HP::COUNT; e += THREADS) sh.tw[e] = half_table[e];
+    for (int e = threadIdx.x; e < HP::COUNT + QuarterInverse::COUNT; e += THREADS) sh.tw[e] = half_table[e];
     __syncthreads();
     HalfLanes hc;
     hc.init(t, h, sh.xch[wave], sh.tw);
@@ -753,9 +754,9 @@ __global__ __launch_bounds__(768, 3) void k_blind_rotate_wide(
     CosTan eb[2], ec[2], ed[2];
     hc.entries<1>(eb); hc.entries<2>(ec); hc.entries<3>(ed);
 
-    // Coefficients kept by a wavefront with p > 0: v[m] at pos + 64 (4h + 2u + m), u = p - 1, v[2 + m] at 512 more.
+    // Coefficients kept by a wavefront with p > 0: v[m] at pos + 64u + 128m + 256h, u = p - 1, v[2 + m] at 512 more.
     uint32_t v[4];
-    const int u = p - 1, pos = HalfLanes::position(t), own = pos + 256 * h + 128 * u;
+    const int u = p - 1, pos = HalfLanes::position(t), own = pos + 64 * u + 256 * h;
     auto publish = [&](uint32_t abar) {
         const uint32_t x0 = 4 * ((uint32_t)own + abar);
         char *const rot = reinterpret_cast<char *>(sh.rot[c]);
@@ -764,7 +765,7 @@ __global__ __launch_bounds__(768, 3) void k_blind_rotate_wide(
             reinterpret_cast<uint2 *>(&sh.base[c][h][q][t])[u] = make_uint2(v[2 * q] - dec_off, v[2 * q + 1] - dec_off);
 #pragma unroll
         for (int q = 0; q < 4; q++) {
-            const uint32_t x = x0 + 256 * (q & 1) + 2048 * (q >> 1);          // 4 * (j + abar): bit 12 is the sign
+            const uint32_t x = x0 + 512 * (q & 1) + 2048 * (q >> 1);          // 4 * (j + abar): bit 12 is the sign
             const uint32_t neg = (uint32_t)__builtin_amdgcn_sbfe((int)x, 12, 1);
             *reinterpret_cast<uint32_t *>(rot + (x & (4 * N - 1))) = (v[q] ^ neg) - neg;
         }
@@ -775,7 +776,7 @@ __global__ __launch_bounds__(768, 3) void k_blind_rotate_wide(
 #pragma unroll
         for (int b = 0; b < 2; b++) {
             const uint4 lo = sh.base[c][b][0][t], hi = sh.base[c][b][1][t];
-            const uint32_t l4[4] = {lo.x, lo.y, lo.z, lo.w}, h4[4] = {hi.x, hi.y, hi.z, hi.w};
+            const uint32_t l4[4] = {lo.x, lo.z, lo.y, lo.w}, h4[4] = {hi.x, hi.z, hi.y, hi.w};
 #pragma unroll
             for (int m = 0; m < 4; m++) {
                 dlo[4 * b + m] = (sh.rot[c][pos + L * (4 * b + m)] - l4[m]) ^ flip;
@@ -793,18 +794,26 @@ __global__ __launch_bounds__(768, 3) void k_blind_rotate_wide(
 #pragma unroll
         for (int m = 0; m < 4; m++) sh.spec[c][p][h][m * HP::ROW + t] = make_double2(xr[m], xi[m]);
     };
-    // last stage: (y0 + y1) / 512 for half 0, conj(w) (y0 - y1) / 512 for half 1; adding 1.5*2^52 leaves the rounded
-    // value modulo 2^32 in the low word
+    // The last two stages for the positions pos + 64u and 128 more of block h; adding 1.5*2^52 leaves the rounded value
+    // modulo 2^32 in the low word.
     auto finish = [&]() {
         constexpr double magic = 6755399441055744.0, scale = 1.0 / 512, rot = 0.70710678118654752440 / 512;
+        double ar[2], ai[2], br[2], bi[2];                                      // of half 0 and half 1: positions without and with 128
+#pragma unroll
+        for (int e = 0; e < 2; e++) {
+            const double2 y0 = sh.xch[2 * c + e][64 * u + pos], y1 = sh.xch[4 + 2 * c + e][64 * u + pos];
+            const CosTan w = HP::first_entry(e, 0);
+            ar[e] = y0.x; ai[e] = y0.y; br[e] = y1.x; bi[e] = y1.y;
+            node_butterfly_inverse<false>(ar[e], ai[e], br[e], bi[e], w.c, w.t);
+        }
 #pragma unroll
         for (int m = 0; m < 2; m++) {
-            const double2 y0 = sh.xch[2 * c][(2 * u + m) * HP::ROW + t], y1 = sh.xch[2 * c + 1][(2 * u + m) * HP::ROW + t];
+            const double(&zr)[2] = m ? br : ar, (&zi)[2] = m ? bi : ai;
             double re, im, f;
             if (h == 0) {
-                re = y0.x + y1.x; im = y0.y + y1.y; f = scale;
+                re = zr[0] + zr[1]; im = zi[0] + zi[1]; f = scale;
             } else {
-                const double dr = y0.x - y1.x, di = y0.y - y1.y;
+                const double dr = zr[0] - zr[1], di = zi[0] - zi[1];
                 re = dr + di; im = di - dr; f = rot;
             }
             if (TRACK) {
@@ -816,72 +825,71 @@ __global__ __launch_bounds__(768, 3) void k_blind_rotate_wide(
         }
     };
 
-    if (p == 0) {
-        // the key values of the own output component, all 2 LR rows, requested a step ahead as their registers become free
-        const double2 *key = bk_hat + c * HP::M + hc.key_lane();
-        constexpr size_t row_elems = (size_t)2 * HP::M;
-        double2 kv[2 * LR][4];
-        auto request = [&](uint32_t step, int r) {
-            const double2 *row = key + ((size_t)step * 2 * LR + (r < LR ? c * LR + r : (c ^ 1) * LR + r - LR)) * row_elems;
+    // The key values of output component c at this wavefront's quarter, all 2 LR rows.
+    double2 kv[2 * LR][2];
+    const double2 *key = bk_hat + c * HP::M + QuarterInverse::key_place(h, p & 1, t);
+    auto request = [&](uint32_t step) {
 #pragma unroll
-            for (int m = 0; m < 4; m++) kv[r][m] = row[HP::key_reg(m)];
-        };
-        for (uint32_t i = 0; i < n; i++) {
+        for (int r = 0; r < 2 * LR; r++) {
+            const double2 *row = key + ((size_t)step * 2 * LR + r) * 2 * HP::M;
 #pragma unroll
-            for (int r = 0; r < LR; r++) request(i, r);
-            lds_barrier();
-#pragma unroll
-            for (int r = LR; r < 2 * LR; r++) request(i, r);
-            __builtin_amdgcn_sched_barrier(0);
-            double xr[4], xi[4], mr[4], mi[4];
-            transform(xr, xi);
-#pragma unroll
-            for (int m = 0; m < 4; m++) {
-                const double2 b = kv[0][m];
-                mr[m] = __builtin_fma(-xi[m], b.y, xr[m] * b.x);
-                mi[m] = __builtin_fma(xi[m], b.x, xr[m] * b.y);
-            }
-            // the other rows' spectra are read AHEAD values ahead of the products
-            constexpr int AHEAD = 6, VALUES = 4 * (2 * LR - 1);
-            double2 x[AHEAD];
-            auto value = [&](int q) {
-                const int r = 1 + q / 4;
-                return (r < LR ? sh.spec[c][r][h] : sh.spec[c ^ 1][r - LR][h])[(q % 4) * HP::ROW + t];
-            };
-            lds_barrier();
-#pragma unroll
-            for (int q = 0; q < AHEAD; q++) x[q] = value(q);
-#pragma unroll
-            for (int q = 0; q < VALUES; q++) {
-                const int r = 1 + q / 4, m = q % 4;
-                const double2 w = x[q % AHEAD], b = kv[r][m];
-                if (q + AHEAD < VALUES) x[q % AHEAD] = value(q + AHEAD);
-                mr[m] = __builtin_fma(-w.y, b.y, __builtin_fma(w.x, b.x, mr[m]));
-                mi[m] = __builtin_fma(w.y, b.x, __builtin_fma(w.x, b.y, mi[m]));
-            }
-            __builtin_amdgcn_sched_barrier(0);
-            hc.inverse(mr, mi, eb, ec, ed);
-            wave_lds_fence();
-#pragma unroll
-            for (int m = 0; m < 4; m++) hc.xch[m * HP::ROW + t] = make_double2(mr[m], mi[m]);
-            lds_barrier();
+            for (int m = 0; m < 2; m++) kv[r][m] = row[256 * m];
         }
-    } else {
+    };
+    QuarterInverse qi;
+    const int slot = QuarterInverse::spectrum_slot(p & 1, t);
+    if (p < 2) qi.init(h, p, t, sh.tw + HP::COUNT);
+    if (p == 0) request(0);
+    if (p > 0) {
         // ACC = (0, X^(-bbar) * testv)
         const uint32_t bbar = mybar[n];
 #pragma unroll
         for (int q = 0; q < 4; q++) {
-            const uint32_t j = own + 64 * (q & 1) + 512 * (q >> 1);
+            const uint32_t j = own + 128 * (q & 1) + 512 * (q >> 1);
             v[q] = c == 0 ? 0u : (((j + bbar) & N) ? 0u - (1u << 29) : (1u << 29));
         }
         publish(mybar[0]);
-        for (uint32_t i = 0; i < n; i++) {
-            const uint32_t abar_next = mybar[i + 1];                              // i + 1 == n reads bbar: harmless
-            lds_barrier();
+    }
+    for (uint32_t i = 0; i < n; i++) {
+        const uint32_t abar_next = mybar[i + 1];                                  // i + 1 == n reads bbar: harmless
+        lds_barrier();
+        if (p == 1) request(i);
+        __builtin_amdgcn_sched_barrier(0);
+        {
             double xr[4], xi[4];
             transform(xr, xi);
-            lds_barrier();
-            lds_barrier();
+        }
+        lds_barrier();
+        if (p < 2) {
+            // the rows' spectra are read AHEAD values ahead of the products
+            constexpr int AHEAD = 6, VALUES = 4 * LR;
+            double2 x[AHEAD];
+            double mr[2] = {0, 0}, mi[2] = {0, 0};
+            auto value = [&](int q) { return sh.spec[q / 2 / LR][q / 2 % LR][h][slot + 64 * (q % 2)]; };
+#pragma unroll
+            for (int q = 0; q < AHEAD; q++) x[q] = value(q);
+#pragma unroll
+            for (int q = 0; q < VALUES; q++) {
+                const int m = q % 2;
+                const double2 w = x[q % AHEAD], b = kv[q / 2][m];
+                if (q + AHEAD < VALUES) x[q % AHEAD] = value(q + AHEAD);
+                if (q < 2) {
+                    mr[m] = __builtin_fma(-w.y, b.y, w.x * b.x);
+                    mi[m] = __builtin_fma(w.y, b.x, w.x * b.y);
+                } else {
+                    mr[m] = __builtin_fma(-w.y, b.y, __builtin_fma(w.x, b.x, mr[m]));
+                    mi[m] = __builtin_fma(w.y, b.x, __builtin_fma(w.x, b.y, mi[m]));
+                }
+            }
+            __builtin_amdgcn_sched_barrier(0);
+            qi.run(mr, mi);
+#pragma unroll
+            for (int m = 0; m < 2; m++) hc.xch[QuarterInverse::position(t) + 64 * m] = make_double2(mr[m], mi[m]);
+        }
+        lds_barrier();
+        if (p == 0) {
+            request(std::min(i + 1, n - 1));                                      // the last step's again at the end
+        } else {
             finish();
             publish(abar_next);
         }
@@ -892,7 +900,7 @@ __global__ __launch_bounds__(768, 3) void k_blind_rotate_wide(
     // sample extraction by the whole workgroup: a''_0 = A_0, a''_j = -A_{N-j}, b'' = B_0
     auto word = [&](int comp, int j) {
         const uint32_t *w = reinterpret_cast<const uint32_t *>(sh.base[comp]);
-        return w[((((j >> 8) & 1) * 2 + (j >> 9)) * 64 + HalfLanes::position(j & 63)) * 4 + ((j >> 6) & 3)] + dec_off;
+        return w[((((j >> 8) & 1) * 2 + (j >> 9)) * 64 + HalfLanes::position(j & 63)) * 4 + 2 * ((j >> 6) & 1) + ((j >> 7) & 1)] + dec_off;
     };
     const uint32_t body = word(1, 0);
     if (raw_ext) {
@@ -1679,8 +1687,12 @@ void fill_twiddles(uint32_t N, double *out)
     }
 }
 
-size_t half_twiddle_doubles(uint32_t N) { return N == HalfPlan::N ? 2 * (size_t)HalfPlan::COUNT : 0; }
-void fill_half_twiddles(double *out) { make_half_twiddles(out); }
+size_t half_twiddle_doubles(uint32_t N) { return N == HalfPlan::N ? 2 * (size_t)(HalfPlan::COUNT + QuarterInverse::COUNT) : 0; }
+void fill_half_twiddles(double *out)
+{
+    make_half_twiddles(out);
+    make_quarter_twiddles(out + 2 * HalfPlan::COUNT);
+}
 
 size_t bk_hat_elems(const she_params &P) { return (size_t)P.n * 2 * P.l * 2 * (P.N / 2); }
 
