@@ -680,7 +680,8 @@ __device__ __forceinline__ void inverse_half(const HalfCtx &hc, double (&xr)[4],
 //   pass A  lane = b5 b4 b0 b1 b2 b3, register = b7 b6
 //   swap    lane bits 5, 4 <-> register (v_permlane32_swap, v_permlane16_swap)
 //   pass B  lane = k1 k2 b0 b1 b2 b3, register = b5 b4 -> k3 k4
-//   LDS     lane bits 0, 1 <-> register
+//   LDS     lane bits 0, 1 <-> register (stored at [register][lane ^ register]: sixteen neighbouring lanes read sixteen
+//           slots that differ modulo 16, with no padding)
 //   pass C  lane = k1 k2 b0 b1 k4 k3, register = b3 b2 -> k5 k6
 //   DPP     lane bits 2, 3 <-> register (row shifts that write every other bank of four lanes)
 //   pass D  lane = k1 k2 k6 k5 k4 k3, register = b1 b0 -> k7 k8
@@ -714,11 +715,9 @@ __device__ __forceinline__ void swap_registers_with_lane_bits23(double (&x)[4])
 
 struct HalfLanes {
     using HP = HalfPlan;
-    static constexpr int ROW = 65;                   // exchange: stored at [register][lane], read where the partner bits are
-    static constexpr int XSLOTS = 4 * ROW;
-    int t, h, ld;
-    double2 *xch;
-    const double2 *tw;
+    static constexpr int XSLOTS = 256;
+    int t, h;
+    const double2 *tw;                               // HalfPlan's table
     CosTan ea[2];
     // position of lane t within 64, and the lanes of HalfPlan that hold the same frequency bits before passes C and D
     static __host__ __device__ constexpr int position(int t)
@@ -730,15 +729,16 @@ struct HalfLanes {
     {
         return (t & 7) | ((t & 8) << 2) | (t & 0x10) | ((t & 0x20) >> 2);
     }
+    static __host__ __device__ constexpr int store(int m, int t) { return 64 * m + (t ^ m); }
     static __host__ __device__ constexpr int load(int m, int t)
     {
-        return (2 * (t & 1) + ((t >> 1) & 1)) * ROW + (t & 0x3C) + (m >> 1) + 2 * (m & 1);
+        const int r = 2 * (t & 1) + ((t >> 1) & 1);   // the register that this lane's bits name
+        return 64 * r + ((t & 0x3C) | (((m >> 1) + 2 * (m & 1)) ^ r));
     }
 
-    __device__ __forceinline__ void init(int lane, int half, double2 *xbuf, const double2 *table)
+    __device__ __forceinline__ void init(int lane, int half, const double2 *table)
     {
-        t = lane; h = half; xch = xbuf; tw = table;
-        ld = load(0, t);
+        t = lane; h = half; tw = table;
         for (int e = 0; e < 2; e++) ea[e] = h ? HP::first_entry(1, e) : HP::first_entry(0, e);
     }
     template <int PASS> __device__ __forceinline__ void entries(CosTan (&e)[2]) const
@@ -747,10 +747,10 @@ struct HalfLanes {
 #pragma unroll
         for (int q = 0; q < 2; q++) { const double2 v = tw[HP::entry(PASS, h, q, lane)]; e[q].c = v.x; e[q].t = v.y; }
     }
-    __device__ __forceinline__ int key_lane() const { return HP::key_lane(h, plan_lane_d(t)); }
 
-    __device__ __forceinline__ void forward(double (&xr)[4], double (&xi)[4], const CosTan (&eb)[2], const CosTan (&ec)[2],
-                                            const CosTan (&ed)[2]) const
+    // in `xch` (this wavefront's, XSLOTS slots) the spectrum is left, register m of lane t at 64 m + t
+    __device__ __forceinline__ void forward(double2 *xch, double (&xr)[4], double (&xi)[4], const CosTan (&eb)[2],
+                                            const CosTan (&ec)[2], const CosTan (&ed)[2]) const
     {
         node_pass<4>(xr, xi, ea);
         swap_registers_with_lane_bits54(xr);
@@ -758,14 +758,17 @@ struct HalfLanes {
         node_pass<4>(xr, xi, eb);
         wave_lds_fence();
 #pragma unroll
-        for (int m = 0; m < 4; m++) xch[m * ROW + t] = make_double2(xr[m], xi[m]);
+        for (int m = 0; m < 4; m++) xch[store(m, t)] = make_double2(xr[m], xi[m]);
         wave_lds_fence();
 #pragma unroll
-        for (int m = 0; m < 4; m++) { const double2 v = xch[ld + (m >> 1) + 2 * (m & 1)]; xr[m] = v.x; xi[m] = v.y; }
+        for (int m = 0; m < 4; m++) { const double2 v = xch[load(m, t)]; xr[m] = v.x; xi[m] = v.y; }
         node_pass<4>(xr, xi, ec);
         swap_registers_with_lane_bits23(xr);
         swap_registers_with_lane_bits23(xi);
         node_pass<4>(xr, xi, ed);
+        wave_lds_fence();
+#pragma unroll
+        for (int m = 0; m < 4; m++) xch[64 * m + t] = make_double2(xr[m], xi[m]);
     }
 };
 
@@ -809,8 +812,9 @@ struct QuarterInverse {
     __device__ __forceinline__ void init(int h, int k1, int t, const double2 *tw)
     {
         const int R = node(h, k1, t);
+        { const double2 v = tw[h + 2 * k1]; e[0].c = v.x; e[0].t = v.y; }               // the same for the whole wavefront
 #pragma unroll
-        for (int s = 2; s <= 8; s++) { const double2 v = tw[(1 << s) - 4 + (R & ((1 << s) - 1))]; e[s - 2].c = v.x; e[s - 2].t = v.y; }
+        for (int s = 3; s <= 8; s++) { const double2 v = tw[(1 << s) - 4 + (R & ((1 << s) - 1))]; e[s - 2].c = v.x; e[s - 2].t = v.y; }
         bit0 = t & 1; bit1 = t & 2;
     }
     // out: 128 times the quarter's values

@@ -710,18 +710,20 @@ __global__ __launch_bounds__(256, 2) void k_blind_rotate_quad(
 // Cycles of a step: transforms 3300 (3 x 200 vector instructions on a SIMD, 900 cycles each, of which 112 are FP64 and 48
 // exchange lanes), products 700, inverse 700, joining and publishing 850, barriers.  The vector ALU is busy in about three
 // quarters of them.
-// Measured at n = 630, us per call of 1 / 83 gates whose key comes from HBM: 2665 / 2496 with k_blind_rotate_quad, 1939 /
-// 1896 so (2051 / 2001 with the inverse transforms in four wavefronts, a half each; eight wavefronts in all, four of them
-// with two digits, take as long as the four of k_blind_rotate_quad).
-// With more than one gate per compute unit a second workgroup does not fit (126 KB of LDS, 162 registers x 12) and two
-// rounds take as long as k_blind_rotate_quad's one (3.6 ms).
+// Measured at n = 630, us per call of 1 / 83 gates whose key comes from HBM: 2665 / 2496 with k_blind_rotate_quad, 1974 /
+// 1896 so, and from the Infinity Cache 2350 / 2345 and 1740 / 1745.  (With the inverse transforms in four wavefronts, a half each, 2051 / 2001; eight wavefronts in all, four of them
+// with two digits, take as long as the four of k_blind_rotate_quad.  A register more than there are costs 500 cycles of
+// every step where the wait for it is on the way; another order of the wavefronts' priorities, or the second half of the
+// key requested any later, 2 to 12 %.)
+// With more than one gate per compute unit a second workgroup does not fit (166 registers x 12), two rounds take longer
+// than k_blind_rotate_quad's one (3.7 against 3.5 ms), and so do pairs of gates that share the key values (3.8).
 // ------------------------------------------------------------------------------------------
+// (what is addressed by lane alone first: an LDS instruction's own offset reaches 64 KB)
 struct WideShared {
-    uint32_t rot[2][HalfPlan::N];                                  // X^abar ACC, plain order
+    uint32_t rot[2][HalfPlan::N];                               // X^abar ACC, plain order
     uint4 base[2][2][2][64];                                       // ACC - offset: [component][block of 256][upper 512][lane], word 2u + m: + 64u + 128m
-    double2 xch[12][HalfLanes::XSLOTS];
-    double2 spec[2][3][2][4 * HalfPlan::ROW];                      // [component][digit][half]: a digit's half spectrum
-    double2 tw[HalfPlan::COUNT + QuarterInverse::COUNT];
+    double2 y[2][2][2][128];                                       // [component][half][quarter]: transformed back
+    double2 xch[2][3][2][HalfLanes::XSLOTS];                       // [component][digit][half]: exchange, then the half spectrum
 };
 
 template <bool TRACK>
@@ -737,10 +739,8 @@ __global__ __launch_bounds__(768, 3) void k_blind_rotate_wide(
     const uint32_t g = blockIdx.x;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), t = threadIdx.x & 63;
     const int p = wave >> 2, c = (wave >> 1) & 1, h = wave & 1;
-    for (int e = threadIdx.x; e < HP::COUNT + QuarterInverse::COUNT; e += THREADS) sh.tw[e] = half_table[e];
-    __syncthreads();
-    HalfLanes hc;
-    hc.init(t, h, sh.xch[wave], sh.tw);
+    HalfLanes hl;
+    hl.init(t, h, half_table);
     const uint16_t *mybar = bar + (size_t)g * bar_stride;
 
     const uint32_t half_bg = 1u << (bg_bit - 1);
@@ -752,7 +752,7 @@ __global__ __launch_bounds__(768, 3) void k_blind_rotate_wide(
     float worst = 0.f;
     const double cs1 = h ? -0.70710678118654752440 : 0.70710678118654752440; // +-cos(pi/4) of the first stage
     CosTan eb[2], ec[2], ed[2];
-    hc.entries<1>(eb); hc.entries<2>(ec); hc.entries<3>(ed);
+    hl.entries<1>(eb); hl.entries<2>(ec); hl.entries<3>(ed);
 
     // Coefficients kept by a wavefront with p > 0: v[m] at pos + 64u + 128m + 256h, u = p - 1, v[2 + m] at 512 more.
     uint32_t v[4];
@@ -771,7 +771,7 @@ __global__ __launch_bounds__(768, 3) void k_blind_rotate_wide(
         }
     };
     // digit p of D_c, transformed for half h
-    auto transform = [&](double (&xr)[4], double (&xi)[4]) {
+    auto transform = [&]() {
         uint32_t dlo[8], dhi[8];
 #pragma unroll
         for (int b = 0; b < 2; b++) {
@@ -783,6 +783,7 @@ __global__ __launch_bounds__(768, 3) void k_blind_rotate_wide(
                 dhi[4 * b + m] = (sh.rot[c][pos + L * (4 * b + m) + 512] - h4[m]) ^ flip;
             }
         }
+        double xr[4], xi[4];
 #pragma unroll
         for (int m = 0; m < 4; m++) {
             const int ar = (int)__builtin_amdgcn_sbfe((int)dlo[m], digit_sh, bg_bit), ai = (int)__builtin_amdgcn_sbfe((int)dhi[m], digit_sh, bg_bit);
@@ -790,18 +791,17 @@ __global__ __launch_bounds__(768, 3) void k_blind_rotate_wide(
             xr[m] = __builtin_fma(cs1, (double)(br - bi), (double)ar);
             xi[m] = __builtin_fma(cs1, (double)(br + bi), (double)ai);
         }
-        hc.forward(xr, xi, eb, ec, ed);
-#pragma unroll
-        for (int m = 0; m < 4; m++) sh.spec[c][p][h][m * HP::ROW + t] = make_double2(xr[m], xi[m]);
+        hl.forward(sh.xch[c][p][h], xr, xi, eb, ec, ed);
     };
     // The last two stages for the positions pos + 64u and 128 more of block h; adding 1.5*2^52 leaves the rounded value
     // modulo 2^32 in the low word.
     auto finish = [&]() {
         constexpr double magic = 6755399441055744.0, scale = 1.0 / 512, rot = 0.70710678118654752440 / 512;
+        const double sign = h ? -1.0 : 1.0, turn = h ? 1.0 : 0.0, f = h ? rot : scale;
         double ar[2], ai[2], br[2], bi[2];                                      // of half 0 and half 1: positions without and with 128
 #pragma unroll
         for (int e = 0; e < 2; e++) {
-            const double2 y0 = sh.xch[2 * c + e][64 * u + pos], y1 = sh.xch[4 + 2 * c + e][64 * u + pos];
+            const double2 y0 = sh.y[c][e][0][64 * u + pos], y1 = sh.y[c][e][1][64 * u + pos];
             const CosTan w = HP::first_entry(e, 0);
             ar[e] = y0.x; ai[e] = y0.y; br[e] = y1.x; bi[e] = y1.y;
             node_butterfly_inverse<false>(ar[e], ai[e], br[e], bi[e], w.c, w.t);
@@ -809,13 +809,8 @@ __global__ __launch_bounds__(768, 3) void k_blind_rotate_wide(
 #pragma unroll
         for (int m = 0; m < 2; m++) {
             const double(&zr)[2] = m ? br : ar, (&zi)[2] = m ? bi : ai;
-            double re, im, f;
-            if (h == 0) {
-                re = zr[0] + zr[1]; im = zi[0] + zi[1]; f = scale;
-            } else {
-                const double dr = zr[0] - zr[1], di = zi[0] - zi[1];
-                re = dr + di; im = di - dr; f = rot;
-            }
+            const double sr = __builtin_fma(sign, zr[1], zr[0]), si = __builtin_fma(sign, zi[1], zi[0]);
+            const double re = __builtin_fma(turn, si, sr), im = __builtin_fma(-turn, sr, si);
             if (TRACK) {
                 worst = fmaxf(worst, (float)fabs(re * f - rint(re * f)));
                 worst = fmaxf(worst, (float)fabs(im * f - rint(im * f)));
@@ -838,7 +833,7 @@ __global__ __launch_bounds__(768, 3) void k_blind_rotate_wide(
     };
     QuarterInverse qi;
     const int slot = QuarterInverse::spectrum_slot(p & 1, t);
-    if (p < 2) qi.init(h, p, t, sh.tw + HP::COUNT);
+    if (p < 2) qi.init(h, p, t, half_table + HP::COUNT);
     if (p == 0) request(0);
     if (p > 0) {
         // ACC = (0, X^(-bbar) * testv)
@@ -855,17 +850,14 @@ __global__ __launch_bounds__(768, 3) void k_blind_rotate_wide(
         lds_barrier();
         if (p == 1) request(i);
         __builtin_amdgcn_sched_barrier(0);
-        {
-            double xr[4], xi[4];
-            transform(xr, xi);
-        }
+        transform();
         lds_barrier();
         if (p < 2) {
             // the rows' spectra are read AHEAD values ahead of the products
             constexpr int AHEAD = 6, VALUES = 4 * LR;
             double2 x[AHEAD];
-            double mr[2] = {0, 0}, mi[2] = {0, 0};
-            auto value = [&](int q) { return sh.spec[q / 2 / LR][q / 2 % LR][h][slot + 64 * (q % 2)]; };
+            double mr[2], mi[2];
+            auto value = [&](int q) { return sh.xch[q / 2 / LR][q / 2 % LR][h][slot + 64 * (q % 2)]; };
 #pragma unroll
             for (int q = 0; q < AHEAD; q++) x[q] = value(q);
 #pragma unroll
@@ -884,7 +876,7 @@ __global__ __launch_bounds__(768, 3) void k_blind_rotate_wide(
             __builtin_amdgcn_sched_barrier(0);
             qi.run(mr, mi);
 #pragma unroll
-            for (int m = 0; m < 2; m++) hc.xch[QuarterInverse::position(t) + 64 * m] = make_double2(mr[m], mi[m]);
+            for (int m = 0; m < 2; m++) sh.y[c][h][p][QuarterInverse::position(t) + 64 * m] = make_double2(mr[m], mi[m]);
         }
         lds_barrier();
         if (p == 0) {
@@ -1830,7 +1822,7 @@ static hipError_t blind_rotate_t(const she_params &P, const DeviceKeys &K, size_
         }
         // up to one gate per compute unit: twelve wavefronts per gate (measured beside the kernel)
         if (split && P.l == 3 && gates <= K.cus) {
-#define SHE_LAUNCH_WIDE(TRACK)                                                                                         \
+#define SHE_LAUNCH_WIDE(TRACK)                                                                                        \
     hipLaunchKernelGGL((k_blind_rotate_wide<TRACK>), dim3((unsigned)gates), dim3(768), 0, st, W.bar, W.bar_stride,   \
                        P.n, P.bg_bit, K.bk_hat, K.half_twiddles, ks_bits, W.ext_b, W.ksd, d_round_err, cs, d_out, raw_ext)
             if (d_round_err) SHE_LAUNCH_WIDE(true); else SHE_LAUNCH_WIDE(false);
