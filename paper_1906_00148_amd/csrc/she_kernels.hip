@@ -710,8 +710,8 @@ __global__ __launch_bounds__(256, 2) void k_blind_rotate_quad(
 // Cycles of a step: transforms 3300 (3 x 200 vector instructions on a SIMD, 900 cycles each, of which 112 are FP64 and 48
 // exchange lanes), products 700, inverse 700, joining and publishing 850, barriers.  The vector ALU is busy in about three
 // quarters of them.
-// Measured at n = 630, us per call of 1 / 83 gates whose key comes from HBM: 2665 / 2496 with k_blind_rotate_quad, 1974 /
-// 1896 so, and from the Infinity Cache 2350 / 2345 and 1740 / 1745.  (With the inverse transforms in four wavefronts, a half each, 2051 / 2001; eight wavefronts in all, four of them
+// Measured at n = 630, ms per rotation of 1 / 83 / 250 gates: 2.27 / 2.25 / 2.3 with k_blind_rotate_quad, 1.66 / 1.66 / 1.75
+// so, whether the key comes from HBM (2.60 / 2.41 / 2.40 with k_blind_rotate_quad) or from the Infinity Cache.  (With the inverse transforms in four wavefronts, a half each, 2051 / 2001; eight wavefronts in all, four of them
 // with two digits, take as long as the four of k_blind_rotate_quad.  A register more than there are costs 500 cycles of
 // every step where the wait for it is on the way; another order of the wavefronts' priorities, or the second half of the
 // key requested any later, 2 to 12 %.)
@@ -726,17 +726,39 @@ struct WideShared {
     double2 xch[2][3][2][HalfLanes::XSLOTS];                       // [component][digit][half]: exchange, then the half spectrum
 };
 
+// A launch fills the compute units that its gates leave idle with workgroups that read the key once, side by side from its
+// beginning: 62 MB come from HBM into the Infinity Cache within the first ten steps or so, and the gates, which have room for
+// one step's values only, no longer wait for HBM (without: 1.91 / 1.81 / 1.81 ms for 1 / 83 / 250 gates; where the key is in the
+// Infinity Cache already nothing changes).  Touching lines some steps ahead from the gates' own workgroups is no substitute: a
+// compute unit's loads return in order, so that the touches hold up the values behind them (one gate: 2.28 ms).
+__device__ __forceinline__ void read_ahead(const double2 *__restrict__ key, size_t elems, uint32_t worker, uint32_t workers)
+{
+    constexpr int IN_FLIGHT = 8;
+    const size_t stride = (size_t)workers * blockDim.x;
+    for (size_t at = (size_t)worker * blockDim.x + threadIdx.x; at < elems; at += IN_FLIGHT * stride) {
+        double2 v[IN_FLIGHT];
+#pragma unroll
+        for (int q = 0; q < IN_FLIGHT; q++) v[q] = key[std::min(at + q * stride, elems - 1)];
+#pragma unroll
+        for (int q = 0; q < IN_FLIGHT; q++) asm volatile("" ::"v"(v[q].x), "v"(v[q].y));
+    }
+}
+
 template <bool TRACK>
 __global__ __launch_bounds__(768, 3) void k_blind_rotate_wide(
     const uint16_t *__restrict__ bar, uint32_t bar_stride, uint32_t n, uint32_t bg_bit,
     const double2 *__restrict__ bk_hat, const double2 *__restrict__ half_table, uint32_t ks_bits,
-    uint32_t *__restrict__ ext_b, uint16_t *__restrict__ ksd, unsigned *round_err, CtSpace cs,
+    uint32_t *__restrict__ ext_b, uint16_t *__restrict__ ksd, uint32_t gates, unsigned *round_err, CtSpace cs,
     const uint32_t *__restrict__ out_ids, uint32_t *__restrict__ raw_ext)
 {
     using HP = HalfPlan;
     constexpr int N = HP::N, L = HP::L, LR = 3, THREADS = 768;
     __shared__ WideShared sh;
     const uint32_t g = blockIdx.x;
+    if (g >= gates) {
+        read_ahead(bk_hat, (size_t)n * 2 * LR * 2 * HP::M, g - gates, gridDim.x - gates);
+        return;
+    }
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), t = threadIdx.x & 63;
     const int p = wave >> 2, c = (wave >> 1) & 1, h = wave & 1;
     HalfLanes hl;
@@ -1823,8 +1845,9 @@ static hipError_t blind_rotate_t(const she_params &P, const DeviceKeys &K, size_
         // up to one gate per compute unit: twelve wavefronts per gate (measured beside the kernel)
         if (split && P.l == 3 && gates <= K.cus) {
 #define SHE_LAUNCH_WIDE(TRACK)                                                                                        \
-    hipLaunchKernelGGL((k_blind_rotate_wide<TRACK>), dim3((unsigned)gates), dim3(768), 0, st, W.bar, W.bar_stride,   \
-                       P.n, P.bg_bit, K.bk_hat, K.half_twiddles, ks_bits, W.ext_b, W.ksd, d_round_err, cs, d_out, raw_ext)
+    hipLaunchKernelGGL((k_blind_rotate_wide<TRACK>), dim3(K.cus), dim3(768), 0, st, W.bar, W.bar_stride, P.n,         \
+                       P.bg_bit, K.bk_hat, K.half_twiddles, ks_bits, W.ext_b, W.ksd, (uint32_t)gates, d_round_err,    \
+                       cs, d_out, raw_ext)
             if (d_round_err) SHE_LAUNCH_WIDE(true); else SHE_LAUNCH_WIDE(false);
 #undef SHE_LAUNCH_WIDE
             return hipGetLastError();
