@@ -680,14 +680,15 @@ __device__ __forceinline__ void inverse_half(const HalfCtx &hc, double (&xr)[4],
 //   pass A  lane = b5 b4 b0 b1 b2 b3, register = b7 b6
 //   swap    lane bits 5, 4 <-> register (v_permlane32_swap, v_permlane16_swap)
 //   pass B  lane = k1 k2 b0 b1 b2 b3, register = b5 b4 -> k3 k4
-//   LDS     lane bits 0, 1 <-> register (stored at [register][lane ^ register]: sixteen neighbouring lanes read sixteen
-//           slots that differ modulo 16, with no padding)
+//   LDS     lane bits 0, 1 <-> register (rows of 65: sixteen neighbouring lanes read sixteen slots that differ modulo 16)
 //   pass C  lane = k1 k2 b0 b1 k4 k3, register = b3 b2 -> k5 k6
 //   DPP     lane bits 2, 3 <-> register (row shifts that write every other bank of four lanes)
 //   pass D  lane = k1 k2 k6 k5 k4 k3, register = b1 b0 -> k7 k8
-// Eight consecutive lanes still read eight consecutive values of a key row.  The DPP exchange takes 48 instructions (160
-// cycles) of one SIMD; through LDS it takes 60 cycles of the compute unit's LDS pipe (which stores 88 bytes a clock) and a
-// round trip.  Which is better depends on what a kernel is short of: with twelve wavefronts per compute unit it is LDS.
+// Eight consecutive lanes still read eight consecutive values of a key row.  The DPP exchange takes 48 vector instructions;
+// through LDS it is eight LDS instructions, 60 cycles of the compute unit's LDS pipe (which stores 88 bytes a clock), and a
+// round trip.  Measured in k_blind_rotate_wide: this exchange through LDS + 9 % of the kernel's time, the other one through
+// the registers too + 7 %; two instructions a pair instead of three, v_cndmask with a cross-lane operand, + 24 % (the mask
+// has to be moved into vcc each time).
 template <int CTRL, int BANKS> __device__ __forceinline__ double dpp_merge(double old, double from)
 {
     const int lo = __builtin_amdgcn_update_dpp(__double2loint(old), __double2loint(from), CTRL, 0xF, BANKS, false);
@@ -715,7 +716,7 @@ __device__ __forceinline__ void swap_registers_with_lane_bits23(double (&x)[4])
 
 struct HalfLanes {
     using HP = HalfPlan;
-    static constexpr int XSLOTS = 256;
+    static constexpr int ROW = 65, XSLOTS = 4 * ROW;
     int t, h;
     const double2 *tw;                               // HalfPlan's table
     CosTan ea[2];
@@ -729,11 +730,10 @@ struct HalfLanes {
     {
         return (t & 7) | ((t & 8) << 2) | (t & 0x10) | ((t & 0x20) >> 2);
     }
-    static __host__ __device__ constexpr int store(int m, int t) { return 64 * m + (t ^ m); }
+    static __host__ __device__ constexpr int store(int m, int t) { return ROW * m + t; }
     static __host__ __device__ constexpr int load(int m, int t)
     {
-        const int r = 2 * (t & 1) + ((t >> 1) & 1);   // the register that this lane's bits name
-        return 64 * r + ((t & 0x3C) | (((m >> 1) + 2 * (m & 1)) ^ r));
+        return ROW * (2 * (t & 1) + ((t >> 1) & 1)) + (t & 0x3C) + (m >> 1) + 2 * (m & 1);
     }
 
     __device__ __forceinline__ void init(int lane, int half, const double2 *table)
@@ -748,27 +748,47 @@ struct HalfLanes {
         for (int q = 0; q < 2; q++) { const double2 v = tw[HP::entry(PASS, h, q, lane)]; e[q].c = v.x; e[q].t = v.y; }
     }
 
-    // in `xch` (this wavefront's, XSLOTS slots) the spectrum is left, register m of lane t at 64 m + t
-    __device__ __forceinline__ void forward(double2 *xch, double (&xr)[4], double (&xi)[4], const CosTan (&eb)[2],
-                                            const CosTan (&ec)[2], const CosTan (&ed)[2]) const
+    // The passes, each with the exchange that follows it; `xch`: this wavefront's buffer of XSLOTS slots.
+    __device__ __forceinline__ void pass_a(double (&xr)[4], double (&xi)[4]) const
     {
         node_pass<4>(xr, xi, ea);
         swap_registers_with_lane_bits54(xr);
         swap_registers_with_lane_bits54(xi);
-        node_pass<4>(xr, xi, eb);
+    }
+    __device__ __forceinline__ void pass_b(double2 *xch, double (&xr)[4], double (&xi)[4], const CosTan (&e)[2]) const
+    {
+        node_pass<4>(xr, xi, e);
         wave_lds_fence();
 #pragma unroll
         for (int m = 0; m < 4; m++) xch[store(m, t)] = make_double2(xr[m], xi[m]);
         wave_lds_fence();
 #pragma unroll
         for (int m = 0; m < 4; m++) { const double2 v = xch[load(m, t)]; xr[m] = v.x; xi[m] = v.y; }
-        node_pass<4>(xr, xi, ec);
+    }
+    __device__ __forceinline__ void pass_c(double (&xr)[4], double (&xi)[4], const CosTan (&e)[2]) const
+    {
+        node_pass<4>(xr, xi, e);
         swap_registers_with_lane_bits23(xr);
         swap_registers_with_lane_bits23(xi);
-        node_pass<4>(xr, xi, ed);
+    }
+    // The mirror of all four; out: 256 times the half's values at position 64 m + position(t).
+    __device__ __forceinline__ void inverse(double2 *xch, double (&xr)[4], double (&xi)[4], const CosTan (&eb)[2],
+                                            const CosTan (&ec)[2], const CosTan (&ed)[2]) const
+    {
+        node_pass_inverse<4>(xr, xi, ed);
+        swap_registers_with_lane_bits23(xr);
+        swap_registers_with_lane_bits23(xi);
+        node_pass_inverse<4>(xr, xi, ec);
         wave_lds_fence();
 #pragma unroll
-        for (int m = 0; m < 4; m++) xch[64 * m + t] = make_double2(xr[m], xi[m]);
+        for (int m = 0; m < 4; m++) xch[load(m, t)] = make_double2(xr[m], xi[m]);
+        wave_lds_fence();
+#pragma unroll
+        for (int m = 0; m < 4; m++) { const double2 v = xch[store(m, t)]; xr[m] = v.x; xi[m] = v.y; }
+        node_pass_inverse<4>(xr, xi, eb);
+        swap_registers_with_lane_bits54(xr);
+        swap_registers_with_lane_bits54(xi);
+        node_pass_inverse<4>(xr, xi, ea);
     }
 };
 

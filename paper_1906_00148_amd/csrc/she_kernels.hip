@@ -484,9 +484,10 @@ __global__ __launch_bounds__(128 * GB, 2) void k_blind_rotate_split(
 
 // ------------------------------------------------------------------------------------------
 // Blind rotation of a level of more than one and at most two gates per compute unit, and of the rest of a larger one beyond
-// full rounds (k_blind_rotate_mixed): one gate per workgroup of four wavefronts (N = 1024, l = LR).  What bounds such a level is the length of one gate's chain of n CMuxes, so the chain is cut as far as the
-// transforms allow without a wavefront waiting for another inside one.
-// Wavefront (c, h) owns accumulator component c and half h of the spectrum (HalfPlan): it cuts the digits of all of
+// full rounds (k_blind_rotate_mixed): one gate per workgroup of four wavefronts (N = 1024, l = LR).  What bounds such a level
+// is the length of one gate's chain of n CMuxes, so the chain is cut as far as the transforms allow without a wavefront
+// waiting for another inside one.
+// Wavefront (c, h) owns accumulator component c and half h of the spectrum (HalfLanes): it cuts the digits of all of
 // D_c = X^abar ACC_c - ACC_c, runs the first stage of its LR transforms for half h only and then LR transforms of 256
 // points, multiplies with rows c*LR.. of the key for both outputs, hands the other component's partial half spectrum to
 // wavefront (c^1, h), transforms its own component's half back, swaps the result with wavefront (c, h^1) and finishes
@@ -494,15 +495,17 @@ __global__ __launch_bounds__(128 * GB, 2) void k_blind_rotate_split(
 // Nobody reads the accumulator with computed addresses: its owner writes ACC - (decomposition offset) in place and
 // X^abar ACC already rotated (8 computed addresses and signs per lane instead of 16), so D_c is one subtraction of two
 // words at fixed offsets.
-// A CMux takes 3.5 us (8300 cycles): 600 FP64 instructions per wavefront at the 2.5 ns that a wavefront alone on its SIMD
-// issues them, 190 integer ones at 2 ns, 64 lane swaps at 3.6 ns, and the LDS pipe is busy 1.3 us with the four
-// wavefronts' 40 stores and 49 loads of 1 KB each; the two overlap little, since the wavefronts run in step.
-// Measured at n = 630, ms per launch of 1 / 83 / 256 / 512 gates: 2.2 / 2.2 / 2.3 / 3.6 against 3.2 / 3.2 / 3.2 / 4.0 of
-// k_blind_rotate_split; beyond two gates per compute unit that kernel is the faster one (700 gates: 5.2 against 4.9).
+// A CMux takes a gate alone 3.5 us (8300 cycles): 600 FP64 instructions per wavefront at the 2.5 ns that a wavefront alone
+// on its SIMD issues them, 190 integer ones, 260 for exchanges through the registers, and LDS traffic of the four
+// wavefronts (24 stores and 33 loads of 1 KB each); they overlap little, since the wavefronts run in step.  Two gates on a
+// compute unit take 5.4 us: the vector ALU is busy 60 % of it, and wavefronts wait to issue LDS instructions a fifth of it.
+// Measured at n = 630, ms per launch of 300 / 512 gates: 3.4 / 3.65 (3.45 / 3.85 with the last exchange through LDS as well)
+// against 3.9 / 4.0 of k_blind_rotate_split; beyond two gates per compute unit that kernel is the faster one (700 gates:
+// 5.2 against 4.9; three quads per compute unit on 168 registers 5.1).
 // ------------------------------------------------------------------------------------------
 struct QuadShared {
     uint32_t rot[2][HalfPlan::N], base[2][HalfPlan::N];
-    double2 xch[4][HalfPlan::XSLOTS], hand[4][4 * HalfPlan::ROW];
+    double2 xch[4][HalfLanes::XSLOTS], hand[4][4 * HalfPlan::ROW];
     double2 tw[HalfPlan::COUNT];
 };
 
@@ -522,8 +525,9 @@ __device__ __forceinline__ void rotate_by_quad(
     const int c = wave >> 1, h = wave & 1;
     for (int e = threadIdx.x; e < HP::COUNT; e += 256) s_tw[e] = half_table[e];
     __syncthreads();
-    HalfCtx hc;
-    hc.init(t, h, s_xch[wave], s_tw);
+    HalfLanes hl;
+    hl.init(t, h, s_tw);
+    double2 *const xch = s_xch[wave];
     const double2 *from_other = s_hand[wave ^ 2], *from_half = s_xch[wave ^ 1];
     const uint16_t *mybar = bar + (size_t)g * bar_stride;
 
@@ -534,9 +538,9 @@ __device__ __forceinline__ void rotate_by_quad(
     for (int p = 1; p <= LR; p++) { dec_off += half_bg << (32 - p * bg_bit); flip |= half_bg << (32 - p * bg_bit); }
     float worst = 0.f;
 
-    // own coefficients: v[m] at t + 64 (4h + m), v[4 + m] at t + 64 (4h + m) + 512; ACC = (0, X^(-bbar) * testv)
+    // own coefficients: v[m] at pos + 64 (4h + m), v[4 + m] at 512 more; ACC = (0, X^(-bbar) * testv)
     uint32_t v[8];
-    const int own = t + 256 * h;
+    const int pos = HalfLanes::position(t), own = pos + 256 * h;
     {
         const uint32_t bbar = mybar[n];
 #pragma unroll
@@ -561,7 +565,7 @@ __device__ __forceinline__ void rotate_by_quad(
     // of the component before them free their registers.  (All 24 of a step held at once, requested at other points of
     // the step, is no faster: 2.2 to 2.4 ms.)
     const size_t row_elems = (size_t)2 * HP::M;
-    const int key_lane = HP::key_lane(h, t);
+    const int key_lane = HP::key_lane(h, HalfLanes::plan_lane_d(t));
     double2 kv[LR][4];
     auto request = [&](uint32_t step, int o, int p) {
         const double2 *row = bk_hat + ((size_t)step * 2 * LR + c * LR + p) * row_elems + (o ? c : c ^ 1) * HP::M;
@@ -574,18 +578,18 @@ __device__ __forceinline__ void rotate_by_quad(
     uint32_t abar_next = mybar[1];                                            // n == 1 reads bbar: harmless
     const double cs1 = h ? -0.70710678118654752440 : 0.70710678118654752440; // +-cos(pi/4) of the first stage
     CosTan eb[2], ec[2], ed[2];
-    hc.entries<1>(eb); hc.entries<2>(ec); hc.entries<3>(ed);
+    hl.entries<1>(eb); hl.entries<2>(ec); hl.entries<3>(ed);
     for (uint32_t i = 0; i < n; i++) {
         lds_barrier();                                                        // both arrays of both components are written
         uint32_t dlo[8], dhi[8];
 #pragma unroll
         for (int m = 0; m < 8; m++) {
-            dlo[m] = (s_rot[c][t + L * m] - s_base[c][t + L * m]) ^ flip;
-            dhi[m] = (s_rot[c][t + L * m + 512] - s_base[c][t + L * m + 512]) ^ flip;
+            dlo[m] = (s_rot[c][pos + L * m] - s_base[c][pos + L * m]) ^ flip;
+            dhi[m] = (s_rot[c][pos + L * m + 512] - s_base[c][pos + L * m + 512]) ^ flip;
         }
         double xr[LR][4], xi[LR][4];
         double mr[4], mi[4], orr[4], oi[4];                                   // half spectra: own component, the other one
-        // first stage: a +- exp(i pi/4) b with a, b the positions 64 m + t and 64 m + t + 256; (1 + i) b in integers
+        // first stage: a +- exp(i pi/4) b with a, b the positions 64 m + pos and 64 m + pos + 256; (1 + i) b in integers
         auto head = [&](int p) {
 #pragma unroll
             for (int m = 0; m < 4; m++) {
@@ -595,7 +599,7 @@ __device__ __forceinline__ void rotate_by_quad(
                 xr[p][m] = __builtin_fma(cs1, (double)(br - bi), (double)ar);
                 xi[p][m] = __builtin_fma(cs1, (double)(br + bi), (double)ai);
             }
-            half_pass_a(hc, xr[p], xi[p]);
+            hl.pass_a(xr[p], xi[p]);
         };
         auto products = [&](int p, double (&ar)[4], double (&ai)[4]) {
 #pragma unroll
@@ -614,8 +618,8 @@ __device__ __forceinline__ void rotate_by_quad(
         // side the four wavefronts, which run in step, wait for the LDS pipe together (2.59 against 2.49 ms).
 #pragma unroll
         for (int s = 0; s < LR + 2; s++) {
-            if (s < LR) { head(s); half_pass_b(hc, xr[s], xi[s], eb); }
-            if (s >= 1 && s - 1 < LR) half_pass_c(hc, xr[s - 1], xi[s - 1], ec);
+            if (s < LR) { head(s); hl.pass_b(xch, xr[s], xi[s], eb); }
+            if (s >= 1 && s - 1 < LR) hl.pass_c(xr[s - 1], xi[s - 1], ec);
             if (s >= 2) {
                 node_pass<4>(xr[s - 2], xi[s - 2], ed);
                 products(s - 2, orr, oi);
@@ -631,11 +635,11 @@ __device__ __forceinline__ void rotate_by_quad(
         lds_barrier();
 #pragma unroll
         for (int m = 0; m < 4; m++) { const double2 w = from_other[m * HP::ROW + t]; mr[m] += w.x; mi[m] += w.y; }
-        inverse_half(hc, mr, mi, eb, ec, ed);
+        hl.inverse(xch, mr, mi, eb, ec, ed);
         // the exchange buffer is free again; the partner has read it before it meets the barrier at the loop's top
         wave_lds_fence();
 #pragma unroll
-        for (int m = 0; m < 4; m++) hc.xch[m * HP::ROW + t] = make_double2(mr[m], mi[m]);
+        for (int m = 0; m < 4; m++) xch[m * HP::ROW + t] = make_double2(mr[m], mi[m]);
         lds_barrier();
         // last stage: (y0 + y1) / 512 for half 0, conj(w) (y0 - y1) / 512 for half 1; adding 1.5*2^52 leaves the rounded
         // value modulo 2^32 in the low word
@@ -813,7 +817,14 @@ __global__ __launch_bounds__(768, 3) void k_blind_rotate_wide(
             xr[m] = __builtin_fma(cs1, (double)(br - bi), (double)ar);
             xi[m] = __builtin_fma(cs1, (double)(br + bi), (double)ai);
         }
-        hl.forward(sh.xch[c][p][h], xr, xi, eb, ec, ed);
+        double2 *const xch = sh.xch[c][p][h];
+        hl.pass_a(xr, xi);
+        hl.pass_b(xch, xr, xi, eb);
+        hl.pass_c(xr, xi, ec);
+        node_pass<4>(xr, xi, ed);
+        wave_lds_fence();
+#pragma unroll
+        for (int m = 0; m < 4; m++) xch[L * m + t] = make_double2(xr[m], xi[m]);
     };
     // The last two stages for the positions pos + 64u and 128 more of block h; adding 1.5*2^52 leaves the rounded value
     // modulo 2^32 in the low word.
