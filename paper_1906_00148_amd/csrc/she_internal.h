@@ -56,6 +56,13 @@ hipError_t launch_bk_transform(const she_params &P, const uint32_t *d_bk_int, co
 // leveled mode: spectra of `samples` TRGSW samples d_int[s][2l][2][N] into slots d_ids[s] of trgsw_hat; CMux batch
 hipError_t launch_trgsw_transform(const she_params &P, const DeviceKeys &K, const uint32_t *d_int, double2 *trgsw_hat,
                                   const uint32_t *d_ids, size_t samples, hipStream_t st);
+// Levels of so few CMuxes have their id lists in the kernel's arguments: the four pointers are then host pointers, read
+// before launch_cmux returns.  (3 KB of arguments; HIP takes 4.)
+constexpr size_t CMUX_ARG_IDS = 192;
+inline bool cmux_ids_in_arguments(uint32_t N, size_t count, uint32_t cus)
+{
+    return (N == 1024 || N == 2048) && count <= CMUX_ARG_IDS && count <= 2 * (size_t)cus;
+}
 hipError_t launch_cmux(const she_params &P, const DeviceKeys &K, const double2 *trgsw_hat, uint32_t *trlwe,
                        const uint32_t *d_sel, const uint32_t *d_in1, const uint32_t *d_in0, const uint32_t *d_out,
                        size_t count, unsigned *d_round_err, hipStream_t st);

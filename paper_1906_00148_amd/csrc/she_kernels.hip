@@ -10,6 +10,7 @@
 // construction itself is the cited TFHE gate bootstrapping.)
 #include "negacyclic_fft.h"
 #include "she_internal.h"
+#include <algorithm>
 #include <mutex>
 #pragma clang fp contract(fast)
 
@@ -1273,11 +1274,9 @@ __global__ __launch_bounds__(64 * BR_WAVES, 2) void k_cmux(const double2 *__rest
 // round of workgroups starts and k_cmux is as fast or faster (768: 18.7 against 17.9, 37.6 against 40.2).
 // ------------------------------------------------------------------------------------------
 template <int N, bool TRACK>
-__global__ __launch_bounds__(256, 2) void k_cmux_quad(const double2 *__restrict__ trgsw_hat, uint32_t *trlwe,
-                                                      const uint32_t *__restrict__ sel, const uint32_t *__restrict__ in1,
-                                                      const uint32_t *__restrict__ in0, const uint32_t *__restrict__ out,
-                                                      uint32_t l, uint32_t bg_bit, const double2 *__restrict__ table,
-                                                      unsigned *round_err)
+__device__ __forceinline__ void cmux_by_quad(const double2 *__restrict__ trgsw_hat, uint32_t *trlwe, uint32_t sel, uint32_t in1,
+                                             uint32_t in0, uint32_t out, uint32_t l, uint32_t bg_bit,
+                                             const double2 *__restrict__ table, unsigned *round_err)
 {
     using HT = HalfTransform<N>;
     constexpr int P = HT::POINTS, M = N / 2, L = 64;
@@ -1286,9 +1285,8 @@ __global__ __launch_bounds__(256, 2) void k_cmux_quad(const double2 *__restrict_
 
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), t = threadIdx.x & 63;
     const int c = wave >> 1, h = wave & 1;
-    const uint32_t g = blockIdx.x;
-    const uint32_t *d1 = trlwe + (size_t)in1[g] * 2 * N, *d0 = trlwe + (size_t)in0[g] * 2 * N;
-    const double2 *rows = trgsw_hat + ((size_t)sel[g] * 2 + c) * l * 2 * M;     // rows of this component, [l][2][M]
+    const uint32_t *d1 = trlwe + (size_t)in1 * 2 * N, *d0 = trlwe + (size_t)in0 * 2 * N;
+    const double2 *rows = trgsw_hat + ((size_t)sel * 2 + c) * l * 2 * M;        // rows of this component, [l][2][M]
     // every word of d1 - d0's component c, before the table is waited for (16-byte words as in k_cmux)
     uint4 u[P], v[P];
 #pragma unroll
@@ -1394,11 +1392,39 @@ __global__ __launch_bounds__(256, 2) void k_cmux_quad(const double2 *__restrict_
         lo[m] = (uint32_t)__double2loint(__builtin_fma(re, f, magic));
         hi[m] = (uint32_t)__double2loint(__builtin_fma(im, f, magic));
     }
-    uint4 *dst = reinterpret_cast<uint4 *>(trlwe + (size_t)out[g] * 2 * N + c * N) + t;
+    uint4 *dst = reinterpret_cast<uint4 *>(trlwe + (size_t)out * 2 * N + c * N) + t;
 #pragma unroll
     for (int q = 0; q < P / 2; q++)
         dst[(P / 2 * h + q) * L] = make_uint4(base[q].x + lo[2 * q], base[q].y + hi[2 * q], base[q].z + lo[2 * q + 1], base[q].w + hi[2 * q + 1]);
     if (TRACK && round_err) atomicMax(round_err, __float_as_uint(worst));
+}
+
+template <int N, bool TRACK>
+__global__ __launch_bounds__(256, 2) void k_cmux_quad(const double2 *__restrict__ trgsw_hat, uint32_t *trlwe,
+                                                      const uint32_t *__restrict__ sel, const uint32_t *__restrict__ in1,
+                                                      const uint32_t *__restrict__ in0, const uint32_t *__restrict__ out,
+                                                      uint32_t l, uint32_t bg_bit, const double2 *__restrict__ table,
+                                                      unsigned *round_err)
+{
+    const uint32_t g = blockIdx.x;
+    cmux_by_quad<N, TRACK>(trgsw_hat, trlwe, sel[g], in1[g], in0[g], out[g], l, bg_bit, table, round_err);
+}
+
+// The same with the level's ids in the kernel's arguments: no copy to the device precedes the launch (a call of 1 / 33 / 132
+// CMuxes 23.9 / 25.0 / 25.8 -> 20.2 / 20.5 / 21.0 us at N = 1024, 29.4 / 31.4 / 34.0 -> 25.8 / 26.8 / 29.5 at N = 2048), and
+// the ids are not read behind a pointer (0.5 us of the kernel's 9).
+struct CmuxIds { uint32_t id[4][CMUX_ARG_IDS]; };                   // sel, in1, in0, out
+template <int N, bool TRACK>
+__global__ __launch_bounds__(256, 2) void k_cmux_quad_args(CmuxIds, const double2 *__restrict__ trgsw_hat, uint32_t *trlwe,
+                                                           uint32_t l, uint32_t bg_bit, const double2 *__restrict__ table,
+                                                           unsigned *round_err)
+{
+    // the ids are the first argument; read where they lie, since an array among the arguments that is indexed at run time
+    // would be copied to scratch memory first
+    const __attribute__((address_space(4))) uint32_t *ids =
+        (const __attribute__((address_space(4))) uint32_t *)__builtin_amdgcn_kernarg_segment_ptr() + blockIdx.x;
+    cmux_by_quad<N, TRACK>(trgsw_hat, trlwe, ids[0], ids[CMUX_ARG_IDS], ids[2 * CMUX_ARG_IDS], ids[3 * CMUX_ARG_IDS], l, bg_bit,
+                           table, round_err);
 }
 
 // TRLWE samples from the pool into consecutive places, in the order of their coefficients, for one copy to the host (33
@@ -1751,6 +1777,17 @@ static hipError_t cmux_t(const she_params &P, const DeviceKeys &K, const double2
         // up to two CMuxes per compute unit: four wavefronts each (measured beside the kernel)
         if (count <= 2 * (size_t)K.cus) {
             const double2 *table = PL::N == HalfPlan::N ? K.half_twiddles : K.twiddles;
+            if (cmux_ids_in_arguments(P.N, count, K.cus)) {
+                CmuxIds ids;
+                const uint32_t *const lists[4] = {d_sel, d_in1, d_in0, d_out};
+                for (int q = 0; q < 4; q++) std::copy(lists[q], lists[q] + count, ids.id[q]);
+#define SHE_LAUNCH_CMUX_QUAD(TRACK)                                                                                   \
+    hipLaunchKernelGGL((k_cmux_quad_args<PL::N, TRACK>), dim3((unsigned)count), dim3(256), 0, st, ids, trgsw_hat,     \
+                       trlwe, P.l, P.bg_bit, table, d_round_err)
+                if (d_round_err) SHE_LAUNCH_CMUX_QUAD(true); else SHE_LAUNCH_CMUX_QUAD(false);
+#undef SHE_LAUNCH_CMUX_QUAD
+                return hipGetLastError();
+            }
 #define SHE_LAUNCH_CMUX_QUAD(TRACK)                                                                                   \
     hipLaunchKernelGGL((k_cmux_quad<PL::N, TRACK>), dim3((unsigned)count), dim3(256), 0, st, trgsw_hat, trlwe, d_sel, \
                        d_in1, d_in0, d_out, P.l, P.bg_bit, table, d_round_err)

@@ -250,11 +250,14 @@ try {
     } catch (const std::bad_alloc &) {
         return fail(c, SHE_ENOMEM, "host staging");
     }
-    if ((rc = ensure_ids(c, count))) return rc;
-    // one upload for the four lists (four take 8 us more of a call that is 28 to 44 us long for 1 to 500 CMuxes, 8 to 22 of
-    // them in the kernel), and the same two events for every level (0.3 us less than making and destroying two)
-    uint32_t *d = c->lev.d_ids;
-    HIP_TRY(c, hipMemcpyAsync(d, staged.data(), 4 * count * sizeof(uint32_t), hipMemcpyHostToDevice, c->stream));
+    // small levels' lists travel as arguments of the kernel; otherwise one upload for all four (four take 8 us more)
+    const uint32_t *d = staged.data();
+    if (!cmux_ids_in_arguments(c->P.N, count, c->dk.cus)) {
+        if ((rc = ensure_ids(c, count))) return rc;
+        d = c->lev.d_ids;
+        HIP_TRY(c, hipMemcpyAsync(c->lev.d_ids, staged.data(), 4 * count * sizeof(uint32_t), hipMemcpyHostToDevice, c->stream));
+    }
+    // the same two events for every level (0.3 us less than making and destroying two)
     if (c->timing) {
         for (hipEvent_t &e : c->lev.around)
             if (!e) HIP_TRY(c, hipEventCreate(&e));
