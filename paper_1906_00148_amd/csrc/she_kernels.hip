@@ -1281,7 +1281,9 @@ __device__ __forceinline__ void cmux_by_quad(const double2 *__restrict__ trgsw_h
     using HT = HalfTransform<N>;
     constexpr int P = HT::POINTS, M = N / 2, L = 64;
     __shared__ double2 s_xch[4][HT::XSLOTS], s_hand[4][P * L];
-    __shared__ double2 s_tw[HT::COUNT];
+    // with four points per lane a lane's entries go straight to registers, with no copy and no barrier (8.2 -> 7.6 us)
+    constexpr bool TABLE_IN_LDS = P > 4;
+    __shared__ double2 s_tw[TABLE_IN_LDS ? HT::COUNT : 1];
 
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), t = threadIdx.x & 63;
     const int c = wave >> 1, h = wave & 1;
@@ -1294,10 +1296,14 @@ __device__ __forceinline__ void cmux_by_quad(const double2 *__restrict__ trgsw_h
         u[q] = (reinterpret_cast<const uint4 *>(d1 + c * N) + t)[q * L];
         v[q] = (reinterpret_cast<const uint4 *>(d0 + c * N) + t)[q * L];
     }
-    for (int e = threadIdx.x; e < HT::COUNT; e += 256) s_tw[e] = table[e];
-    __syncthreads();
     HT ht;
-    ht.init(t, h, s_xch[wave], s_tw);
+    if constexpr (TABLE_IN_LDS) {
+        for (int e = threadIdx.x; e < HT::COUNT; e += 256) s_tw[e] = table[e];
+        __syncthreads();
+        ht.init(t, h, s_xch[wave], s_tw);
+    } else {
+        ht.init(t, h, s_xch[wave], table);
+    }
 
     const uint32_t half_bg = 1u << (bg_bit - 1);
     uint32_t dec_off = 1u << (31 - l * bg_bit);
