@@ -230,9 +230,11 @@ int she_get_option(she_ctx *ctx, int option, int *value);   /* SHE_EINVAL for an
 /* SHE_OPT_SPLIT_BELOW (default: 6 x the device's compute units, 1536 on MI355X): a kernel launch of at
  * most this many blind rotations spreads each one over two wavefronts (one per accumulator component),
  * which shortens the serial chain per CMux when the level is too small to fill the chip; larger launches
- * keep one wavefront per rotation.  0 never splits.  At N = 1024 with l = 3 there are two more forms:
- *  - a launch of at most this many rotations and at most two per compute unit spreads each one over four
- *    wavefronts (one per component and half of the spectrum);
+ * keep one wavefront per rotation.  0 never splits.  At N = 1024 with l = 3 there are three more forms:
+ *  - a launch of at most this many rotations and at most one per compute unit spreads each one over twelve
+ *    wavefronts (one per digit, component and half of the spectrum), and compute units left idle read the key ahead;
+ *  - one of at most this many and at most two per compute unit spreads each over four wavefronts (one per component
+ *    and half of the spectrum);
  *  - a launch of more than four per compute unit, larger than this option or not, keeps full rounds of four per
  *    compute unit on one wavefront each and runs the rest on four each, if the rest is at most two per compute
  *    unit and at most this many rotations.

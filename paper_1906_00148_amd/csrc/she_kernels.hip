@@ -263,8 +263,8 @@ __global__ __launch_bounds__(64 * BR_WAVES, 2) void k_blind_rotate(
 
 // ------------------------------------------------------------------------------------------
 // Blind rotation of a small level on two wavefronts per gate, one or two gates per workgroup: at N = 1024 with l = 3 levels
-// of more than two and at most four gates per compute unit (k_blind_rotate_quad has the smaller ones,
-// k_blind_rotate_mixed most of the larger), at other parameters levels of up to six (SHE_OPT_SPLIT_BELOW's default).
+// of more than two and at most four gates per compute unit (k_blind_rotate_wide and k_blind_rotate_quad have the smaller
+// ones, k_blind_rotate_mixed most of the larger), at other parameters levels of up to six (SHE_OPT_SPLIT_BELOW's default).
 // A level of a few hundred gates leaves most SIMDs with one wavefront or none, and the time of
 // the kernel above is then the latency of one wavefront's serial chain of 6 forward and 2
 // inverse transforms per CMux.  Here wavefront c of a gate owns accumulator component c: it
@@ -712,15 +712,16 @@ __global__ __launch_bounds__(256, 2) void k_blind_rotate_quad(
 // and a wavefront that issues loads faster than that stands still.  So a step's twelve values per multiplying wavefront wait
 // in registers, requested by one half of them while the others publish and by the other half at the head of the next
 // transform; it matters less so, too, whether the key comes from HBM or from the Infinity Cache.
-// Cycles of a step: transforms 3300 (3 x 200 vector instructions on a SIMD, 900 cycles each, of which 112 are FP64 and 48
-// exchange lanes), products 700, inverse 700, joining and publishing 850, barriers.  The vector ALU is busy in about three
-// quarters of them.
-// Measured at n = 630, ms per rotation of 1 / 83 / 250 gates: 2.27 / 2.25 / 2.3 with k_blind_rotate_quad, 1.66 / 1.66 / 1.75
-// so, whether the key comes from HBM (2.60 / 2.41 / 2.40 with k_blind_rotate_quad) or from the Infinity Cache.  (With the inverse transforms in four wavefronts, a half each, 2051 / 2001; eight wavefronts in all, four of them
-// with two digits, take as long as the four of k_blind_rotate_quad.  A register more than there are costs 500 cycles of
-// every step where the wait for it is on the way; another order of the wavefronts' priorities, or the second half of the
-// key requested any later, 2 to 12 %.)
-// With more than one gate per compute unit a second workgroup does not fit (166 registers x 12), two rounds take longer
+// Cycles of a step, 6300 in all: transforms 3300 (three wavefronts on a SIMD with 270 vector instructions each, 120 of them
+// FP64, 48 exchanges through the registers), products 700, inverse 700, joining and publishing 850, barriers.  The vector
+// ALU is busy 80 % of them.
+// Measured at n = 630, ms per rotation of 1 / 83 / 250 gates: 1.66 / 1.66 / 1.75, whether the key comes from HBM or from the
+// Infinity Cache; k_blind_rotate_quad takes 2.27 / 2.25 / 2.3 and 2.60 / 2.41 / 2.40 when it comes from HBM.  With the inverse
+// transforms in four wavefronts, a half each, it was 6 % slower; eight wavefronts in all, four of them with two digits, take
+// as long as the four of k_blind_rotate_quad.  A register more than there are costs 500 cycles of every step where the wait
+// for it is on the way; another order of the wavefronts' priorities, or the second half of the key requested any later, 2 to
+// 12 %.
+// With more than one gate per compute unit a second workgroup does not fit (162 registers x 12), two rounds take longer
 // than k_blind_rotate_quad's one (3.7 against 3.5 ms), and so do pairs of gates that share the key values (3.8).
 // ------------------------------------------------------------------------------------------
 // (what is addressed by lane alone first: an LDS instruction's own offset reaches 64 KB)
@@ -1924,8 +1925,8 @@ static hipError_t blind_rotate_t(const she_params &P, const DeviceKeys &K, size_
         //   N=512, l=3   1.9 / 2.6 / 2.8 / 3.3 / 4.6 / 6.2   2.3 / 2.3 / 3.7 / 3.7 / 5.5 / 5.5   3.8 to 1024, then 5.9
         //   N=256, l=3   1.4 / 1.8 / 2.1 / 2.5 / 3.1 / 3.7   1.6 / 1.6 / 2.5 / 2.6 / 3.6 / 3.6   3.4 to 1024, then 4.8
         // (at N=512, l=2 one per workgroup stays ahead at 1536: 3.8 against 4.0).  At N=1024 with l=3 launches of up to two
-        // gates per compute unit run on four wavefronts each and those of five to six go to the mixed kernel, so one per
-        // workgroup is the only form: 513 to 1024 gates, and above them, with SHE_OPT_SPLIT_BELOW raised, what the mixed
+        // gates per compute unit run on twelve or four wavefronts each and those of five to six go to the mixed kernel, so
+        // one per workgroup is the only form: 513 to 1024 gates, and above them, with SHE_OPT_SPLIT_BELOW raised, what the mixed
         // kernel does not take.
         const size_t per_cu = (gates + K.cus - 1) / std::max<uint32_t>(K.cus, 1);
         const bool triple = P.l == 3;
