@@ -80,6 +80,28 @@ hipError_t launch_blind_rotate(const she_params &P, const DeviceKeys &K, const C
 // MUX m: sample = raw_ext[2m] + raw_ext[2m+1] + (0, 1/8) -> key-switch digits, body and slot initialisation of gate m
 hipError_t launch_mux_combine(const she_params &P, const DeviceKeys &K, const CtSpace &cs, const uint32_t *d_out,
                               size_t muxes, const LevelWork &W, hipStream_t st);
+// Workgroups among which k_key_switch_mfma splits the range of N coefficients (`gate_blocks` x `col_tiles` of them for every
+// split): the power of two with the least estimated time.  Three workgroups fit a compute unit; a step (one coefficient)
+// takes one alone 0.33 us with the key in the caches and 0.52 with the key from memory, two 0.41 / 0.57 and three 0.6 / 0.62,
+// hence 75 and 81 % of a full compute unit's; a round of workgroups costs about four steps more to start and to end; and
+// every split adds its sums to the slots atomically, about a step for 9000 gates x column tiles.
+// The other sides measured, us, the mean of both places of the key, at n = 630 for 512 / 700 / 1100 / 2048 / 2304 / 4096
+// gates: so 64 / 86 / 140 / 175 / 181 / 298, about a thousand workgroups at all sizes 80 / 109 / 150 / 175 / 192 / 298, no
+// more than are resident at once 64 / 86 / 140 / 181 / 181 / 319; at n = 1024 for 1 / 513 / 2048: 49 / 132 / 278, 49 / 132 /
+// 295, 51 / 148 / 319; at n = 4096 for 1 / 513 / 1536: 135 / 400 / 775, 161 / 438 / 864, 170 / 543 / 1077.
+inline uint32_t key_switch_split(uint32_t N, size_t gates, uint32_t gate_blocks, uint32_t col_tiles, uint32_t cus)
+{
+    constexpr uint64_t RESIDENT = 3, STEP[RESIDENT] = {0, 75, 81}, FULL = 100, ROUND = 4 * FULL, PER_ADDED = 9000 / FULL;
+    uint64_t least = ~(uint64_t)0;
+    uint32_t best = 1;
+    for (uint32_t split = 1; split <= 32 && N / split >= 8; split *= 2) {
+        const uint64_t per_cu = ((uint64_t)gate_blocks * col_tiles * split + cus - 1) / (cus ? cus : 1);
+        const uint64_t full = per_cu / RESIDENT, rest = per_cu % RESIDENT;
+        const uint64_t time = N / split * (full * FULL + STEP[rest]) + (full + (rest > 0)) * ROUND + split * gates * col_tiles / PER_ADDED;
+        if (time < least) { least = time; best = split; }
+    }
+    return best;
+}
 hipError_t launch_key_switch(const she_params &P, const DeviceKeys &K, const CtSpace &cs, const uint32_t *d_out,
                              size_t gates, const LevelWork &W, hipStream_t st);
 // fresh encryptions of d_bits under the key bits d_key into the slots d_ids (stream_base: fresh_stream_base); samples whose

@@ -1995,15 +1995,7 @@ hipError_t launch_key_switch(const she_params &P, const DeviceKeys &K, const CtS
         const unsigned per_block = 32 * KSM_TILES * KSM_WAVES;                 // gates per workgroup
         const unsigned gate_blocks = (unsigned)((gates + per_block - 1) / per_block);
         const unsigned col_tiles = K.ks_cols / 32;
-        // Split the i range as long as all workgroups are resident at once (three per compute unit), from ten gate blocks on
-        // until about a thousand of them exist: more splits fetch the key sooner, but every split adds its sums to the
-        // slots atomically.  Measured on 256 compute units at n = 630, us for 300 / 512 / 700 / 1100 / 2100 gates with up to
-        // a thousand at all sizes and so: 69 / 72 / 93 / 126 / 186 and 57 / 58 / 67 / 113 / 180; one half of that many
-        // splits for 83 / 256 gates 41 / 42 instead of 37 / 39; all resident for 4096 gates 315 instead of 272.
-        const unsigned blocks = gate_blocks * col_tiles, resident = 3 * K.cus;
-        unsigned split = 1;
-        while (split < 32 && P.N / (split * 2) >= 8 &&
-               (gate_blocks < 10 ? blocks * split * 2 <= resident : blocks * split < 1024)) split *= 2;
+        const unsigned split = key_switch_split(P.N, gates, gate_blocks, col_tiles, K.cus);
         const dim3 grid(gate_blocks, col_tiles, split);
         hipLaunchKernelGGL(k_key_switch_mfma, grid, dim3(64 * KSM_WAVES), 0, st, cs, K.ks_bytes, K.ks_cols, W.ksd, d_out,
                            P.N, P.n, (uint32_t)gates, P.N / split);              // N / split: a power of two >= 8
