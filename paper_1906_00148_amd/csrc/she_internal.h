@@ -56,16 +56,28 @@ hipError_t launch_bk_transform(const she_params &P, const uint32_t *d_bk_int, co
 // leveled mode: spectra of `samples` TRGSW samples d_int[s][2l][2][N] into slots d_ids[s] of trgsw_hat; CMux batch
 hipError_t launch_trgsw_transform(const she_params &P, const DeviceKeys &K, const uint32_t *d_int, double2 *trgsw_hat,
                                   const uint32_t *d_ids, size_t samples, hipStream_t st);
-// Levels of so few CMuxes have their id lists in the kernel's arguments: the four pointers are then host pointers, read
-// before launch_cmux returns.  (3 KB of arguments; HIP takes 4.)
+// Levels of so few CMuxes have their id lists in the kernel's arguments: 3 KB of the 4 that HIP takes, a round number and not
+// where the gain ends (a call of 192 / 193 entries takes 21.4 / 25.0 us at N = 1024, 32.1 / 36.0 at N = 2048; four lists of
+// about 240 entries would still fit).
 constexpr size_t CMUX_ARG_IDS = 192;
 inline bool cmux_ids_in_arguments(uint32_t N, size_t count, uint32_t cus)
 {
     return (N == 1024 || N == 2048) && count <= CMUX_ARG_IDS && count <= 2 * (size_t)cus;
 }
+struct CmuxIds { uint32_t id[4][CMUX_ARG_IDS]; };                   // sel, in1, in0, out
+// The whole block is handed to the device: places without an entry are cleared, since what the host's memory held there,
+// key bits perhaps, is nothing that a kernel's arguments should keep.
+inline void fill_cmux_ids(CmuxIds &ids, const uint32_t *sel, const uint32_t *in1, const uint32_t *in0, const uint32_t *out,
+                          size_t count)
+{
+    const uint32_t *const lists[4] = {sel, in1, in0, out};
+    for (int q = 0; q < 4; q++)
+        for (size_t k = 0; k < CMUX_ARG_IDS; k++) ids.id[q][k] = k < count ? lists[q][k] : 0;
+}
+// The four lists: host memory, read before the call returns, if cmux_ids_in_arguments(P.N, count, K.cus); device memory if not.
 hipError_t launch_cmux(const she_params &P, const DeviceKeys &K, const double2 *trgsw_hat, uint32_t *trlwe,
-                       const uint32_t *d_sel, const uint32_t *d_in1, const uint32_t *d_in0, const uint32_t *d_out,
-                       size_t count, unsigned *d_round_err, hipStream_t st);
+                       const uint32_t *sel, const uint32_t *in1, const uint32_t *in0, const uint32_t *out, size_t count,
+                       unsigned *d_round_err, hipStream_t st);
 // samples ids[0 .. count) of the pool -> d_dst [count][2][N] in the order of their coefficients
 hipError_t launch_trlwe_gather(const uint32_t *trlwe, uint32_t *d_dst, const uint32_t *d_ids, size_t count, uint32_t N,
                                hipStream_t st);

@@ -1420,7 +1420,6 @@ __global__ __launch_bounds__(256, 2) void k_cmux_quad(const double2 *__restrict_
 // The same with the level's ids in the kernel's arguments: no copy to the device precedes the launch (a call of 1 / 33 / 132
 // CMuxes 23.9 / 25.0 / 25.8 -> 20.2 / 20.5 / 21.0 us at N = 1024, 29.4 / 31.4 / 34.0 -> 25.8 / 26.8 / 29.5 at N = 2048), and
 // the ids are not read behind a pointer (0.5 us of the kernel's 9).
-struct CmuxIds { uint32_t id[4][CMUX_ARG_IDS]; };                   // sel, in1, in0, out
 template <int N, bool TRACK>
 __global__ __launch_bounds__(256, 2) void k_cmux_quad_args(CmuxIds, const double2 *__restrict__ trgsw_hat, uint32_t *trlwe,
                                                            uint32_t l, uint32_t bg_bit, const double2 *__restrict__ table,
@@ -1775,6 +1774,23 @@ static hipError_t trgsw_transform_t(const she_params &P, const DeviceKeys &K, co
     return hipGetLastError();
 }
 
+// Levels with their ids in the kernel's arguments; the lists are host memory.
+template <int N>
+static hipError_t cmux_args_t(const she_params &P, const DeviceKeys &K, const double2 *trgsw_hat, uint32_t *trlwe,
+                              const uint32_t *sel, const uint32_t *in1, const uint32_t *in0, const uint32_t *out, size_t count,
+                              unsigned *d_round_err, hipStream_t st)
+{
+    const double2 *table = N == HalfPlan::N ? K.half_twiddles : K.twiddles;
+    CmuxIds ids;
+    fill_cmux_ids(ids, sel, in1, in0, out, count);
+#define SHE_LAUNCH_CMUX_QUAD(TRACK)                                                                                       \
+    hipLaunchKernelGGL((k_cmux_quad_args<N, TRACK>), dim3((unsigned)count), dim3(256), 0, st, ids, trgsw_hat, trlwe, P.l, \
+                       P.bg_bit, table, d_round_err)
+    if (d_round_err) SHE_LAUNCH_CMUX_QUAD(true); else SHE_LAUNCH_CMUX_QUAD(false);
+#undef SHE_LAUNCH_CMUX_QUAD
+    return hipGetLastError();
+}
+
 template <class PL>
 static hipError_t cmux_t(const she_params &P, const DeviceKeys &K, const double2 *trgsw_hat, uint32_t *trlwe,
                          const uint32_t *d_sel, const uint32_t *d_in1, const uint32_t *d_in0, const uint32_t *d_out,
@@ -1784,17 +1800,6 @@ static hipError_t cmux_t(const she_params &P, const DeviceKeys &K, const double2
         // up to two CMuxes per compute unit: four wavefronts each (measured beside the kernel)
         if (count <= 2 * (size_t)K.cus) {
             const double2 *table = PL::N == HalfPlan::N ? K.half_twiddles : K.twiddles;
-            if (cmux_ids_in_arguments(P.N, count, K.cus)) {
-                CmuxIds ids;
-                const uint32_t *const lists[4] = {d_sel, d_in1, d_in0, d_out};
-                for (int q = 0; q < 4; q++) std::copy(lists[q], lists[q] + count, ids.id[q]);
-#define SHE_LAUNCH_CMUX_QUAD(TRACK)                                                                                   \
-    hipLaunchKernelGGL((k_cmux_quad_args<PL::N, TRACK>), dim3((unsigned)count), dim3(256), 0, st, ids, trgsw_hat,     \
-                       trlwe, P.l, P.bg_bit, table, d_round_err)
-                if (d_round_err) SHE_LAUNCH_CMUX_QUAD(true); else SHE_LAUNCH_CMUX_QUAD(false);
-#undef SHE_LAUNCH_CMUX_QUAD
-                return hipGetLastError();
-            }
 #define SHE_LAUNCH_CMUX_QUAD(TRACK)                                                                                   \
     hipLaunchKernelGGL((k_cmux_quad<PL::N, TRACK>), dim3((unsigned)count), dim3(256), 0, st, trgsw_hat, trlwe, d_sel, \
                        d_in1, d_in0, d_out, P.l, P.bg_bit, table, d_round_err)
@@ -1833,15 +1838,18 @@ hipError_t launch_trgsw_transform(const she_params &P, const DeviceKeys &K, cons
 }
 
 hipError_t launch_cmux(const she_params &P, const DeviceKeys &K, const double2 *trgsw_hat, uint32_t *trlwe,
-                       const uint32_t *d_sel, const uint32_t *d_in1, const uint32_t *d_in0, const uint32_t *d_out,
-                       size_t count, unsigned *d_round_err, hipStream_t st)
+                       const uint32_t *sel, const uint32_t *in1, const uint32_t *in0, const uint32_t *out, size_t count,
+                       unsigned *d_round_err, hipStream_t st)
 {
     if (!count) return hipSuccess;
+    if (cmux_ids_in_arguments(P.N, count, K.cus))
+        return P.N == 1024 ? cmux_args_t<1024>(P, K, trgsw_hat, trlwe, sel, in1, in0, out, count, d_round_err, st)
+                           : cmux_args_t<2048>(P, K, trgsw_hat, trlwe, sel, in1, in0, out, count, d_round_err, st);
     switch (P.N) {
-    case 256: return cmux_t<Plan256>(P, K, trgsw_hat, trlwe, d_sel, d_in1, d_in0, d_out, count, d_round_err, st);
-    case 512: return cmux_t<Plan512>(P, K, trgsw_hat, trlwe, d_sel, d_in1, d_in0, d_out, count, d_round_err, st);
-    case 1024: return cmux_t<Plan1024>(P, K, trgsw_hat, trlwe, d_sel, d_in1, d_in0, d_out, count, d_round_err, st);
-    case 2048: return cmux_t<Plan2048>(P, K, trgsw_hat, trlwe, d_sel, d_in1, d_in0, d_out, count, d_round_err, st);
+    case 256: return cmux_t<Plan256>(P, K, trgsw_hat, trlwe, sel, in1, in0, out, count, d_round_err, st);
+    case 512: return cmux_t<Plan512>(P, K, trgsw_hat, trlwe, sel, in1, in0, out, count, d_round_err, st);
+    case 1024: return cmux_t<Plan1024>(P, K, trgsw_hat, trlwe, sel, in1, in0, out, count, d_round_err, st);
+    case 2048: return cmux_t<Plan2048>(P, K, trgsw_hat, trlwe, sel, in1, in0, out, count, d_round_err, st);
     }
     return hipErrorInvalidValue;
 }
