@@ -10,6 +10,7 @@
 #include <cstdio>
 #include <vector>
 
+#include "largest.h"
 #include "negacyclic_fft.h"
 
 using namespace she;
@@ -103,7 +104,8 @@ int main()
                     re += ur[j] * cosl(ang) - ui[j] * sinl(ang);
                     im += ur[j] * sinl(ang) + ui[j] * cosl(ang);
                 }
-                worst = std::max(worst, std::max(fabsl(re - x.r[t][m]), fabsl(im - x.i[t][m])));
+                keep_largest(worst, fabsl(re - x.r[t][m]));
+                keep_largest(worst, fabsl(im - x.i[t][m]));
                 spec_r[h][m * 64 + t] = x.r[t][m]; spec_i[h][m * 64 + t] = x.i[t][m];
             }
     }
@@ -148,8 +150,9 @@ int main()
             const double *zr = m ? br : ar, *zi = m ? bi : ai;
             const double dr = zr[0] - zr[1], di = zi[0] - zi[1], f = std::sqrt(0.5) / 512;
             const int a = j + 128 * m, b = a + 256;
-            back = std::max({back, fabsl((zr[0] + zr[1]) / 512 - ur[a]), fabsl((zi[0] + zi[1]) / 512 - ui[a]),
-                             fabsl((dr + di) * f - ur[b]), fabsl((di - dr) * f - ui[b])});
+            for (long double e : {fabsl((zr[0] + zr[1]) / 512 - ur[a]), fabsl((zi[0] + zi[1]) / 512 - ui[a]),
+                                  fabsl((dr + di) * f - ur[b]), fabsl((di - dr) * f - ui[b])})
+                keep_largest(back, e);
         }
     }
     CHECK(back < 1e-10L, "inverse(forward(u)) differs from u by %Lg\n", back);
