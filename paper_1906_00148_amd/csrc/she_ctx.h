@@ -98,10 +98,14 @@ void free_leveled(she_ctx *c);                          // releases the leveled-
             return she::fail(ctx, SHE_EINVAL, "a deferred circuit is pending: call she_defer_run first"); \
     } while (0)
 
+// The runtime keeps a failed call's error until someone asks: it is reported here and taken away, or the next launch, this
+// library's or another's, would report it as its own.
 #define HIP_TRY(ctx, expr)                                                                        \
     do {                                                                                          \
         hipError_t e_ = (expr);                                                                   \
-        if (e_ != hipSuccess)                                                                     \
+        if (e_ != hipSuccess) {                                                                   \
+            (void)hipGetLastError();                                                              \
             return she::fail(ctx, e_ == hipErrorOutOfMemory ? SHE_ENOMEM : SHE_EDEVICE,           \
                              std::string(#expr) + ": " + hipGetErrorString(e_));                  \
+        }                                                                                         \
     } while (0)

@@ -177,10 +177,7 @@ try {
     // for that, and a copy per sample has to do
     const size_t step = std::min(count, kReadChunk);
     rc = ensure_stage(c, step * words + step);
-    if (rc == SHE_ENOMEM) {
-        (void)hipGetLastError();                                              // not for the next launch to find
-        return read_in_place(c, ids, count, samples);
-    }
+    if (rc == SHE_ENOMEM) return read_in_place(c, ids, count, samples);
     if (rc) return rc;
     uint32_t *d_ids = c->d_stage + step * words;
     for (size_t off = 0; off < count; off += step) {
