@@ -109,7 +109,8 @@ int ensure_work(she_ctx *c, size_t gates)
 {
     if (gates <= c->work.gates) return SHE_OK;
     HIP_TRY(c, hipStreamSynchronize(c->stream));
-    if (c->work.bar) { hipFree(c->work.bar); hipFree(c->work.ext_b); hipFree(c->work.ksd); c->work = LevelWork{}; }
+    if (c->work.bar) { hipFree(c->work.bar); hipFree(c->work.ext_b); hipFree(c->work.ksd); }
+    c->work.bar = nullptr; c->work.ext_b = nullptr; c->work.ksd = nullptr; c->work.gates = 0;     // raw_ext grows by itself
     const size_t groups = (gates + KS_GROUP - 1) / KS_GROUP;
     c->work.bar_stride = round_up(c->P.n + 1, 2);
     HIP_TRY(c, hipMalloc((void **)&c->work.bar, gates * c->work.bar_stride * sizeof(uint16_t)));

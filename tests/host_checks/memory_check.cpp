@@ -1,5 +1,7 @@
-// The library's host files on a fake device (fake_device.h) that runs out of memory: a call that fails for it says so and
-// leaves no error for the next launch (or the next call of another library in the process) to find.
+// The library's host files on a fake device (fake_device.h):
+//   1. a call that runs out of memory says so and leaves no error for the next launch (or the next call of another library in
+//      the process) to find;
+//   2. a context whose scratch has grown gives everything back.
 #include <cstdint>
 #include <vector>
 
@@ -42,6 +44,17 @@ int main()
     for (uint32_t k = 0; k < 64; k++) { s[k] = 0; a[k] = k % 8; b[k] = 8 + k % 8; out[k] = 16 + k % 48; }
     short_of_memory("she_eval_cmux", [&] { return she_eval_cmux(c, s.data(), a.data(), b.data(), out.data(), 48); });
     she_free(c);
+    CHECK(fake::held == 0, "%zu bytes are still held after she_free\n", fake::held);
+
+    // gate levels grow the scratch that MUX levels share
+    c = context(256, 128);
+    for (uint32_t k = 0; k < 64; k++) { s[k] = k; a[k] = k; b[k] = 63 - k; out[k] = 64 + k; }
+    for (size_t count : {4, 16, 64}) {
+        CHECK(she_eval_mux(c, s.data(), a.data(), b.data(), out.data(), count / 4) == SHE_OK, "%zu MUX gates\n", count / 4);
+        CHECK(she_eval_gates(c, types.data(), a.data(), b.data(), out.data(), count) == SHE_OK, "%zu gates\n", count);
+    }
+    she_free(c);
+    CHECK(fake::held == 0, "%zu bytes are still held after she_free of a context whose scratch grew\n", fake::held);
     std::printf("failures %d\n", failures);
     return failures != 0;
 }

@@ -1,6 +1,6 @@
-"""The C ABI on a fake device that runs out of memory (CPU only; tests/host_checks/memory_check.cpp)."""
+"""The C ABI on a fake device (CPU only; tests/host_checks/memory_check.cpp): calls short of memory, scratch that grows."""
 from test_host_client import run_on_fake_device
 
 
-def test_a_call_short_of_memory_leaves_no_error_behind(tmp_path):
+def test_memory_on_the_fake_device(tmp_path):
     run_on_fake_device("memory_check.cpp", tmp_path)
