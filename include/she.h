@@ -232,7 +232,8 @@ int she_get_option(she_ctx *ctx, int option, int *value);   /* SHE_EINVAL for an
  * which shortens the serial chain per CMux when the level is too small to fill the chip; larger launches
  * keep one wavefront per rotation.  0 never splits.  At N = 1024 with l = 3 there are three more forms:
  *  - a launch of at most this many rotations and at most one per compute unit spreads each one over twelve
- *    wavefronts (one per digit, component and half of the spectrum), and compute units left idle read the key ahead;
+ *    wavefronts (one per digit, component and half of the spectrum), and compute units left idle read the key ahead; such a
+ *    rotation needs a compute unit to itself, so launches of several contexts share the chip by compute units;
  *  - one of at most this many and at most two per compute unit spreads each over four wavefronts (one per component
  *    and half of the spectrum);
  *  - a launch of more than four per compute unit, larger than this option or not, keeps full rounds of four per

@@ -499,7 +499,8 @@ __global__ __launch_bounds__(128 * GB, 2) void k_blind_rotate_split(
 // A CMux takes a gate alone 3.5 us (8300 cycles): 600 FP64 instructions per wavefront at the 2.5 ns that a wavefront alone
 // on its SIMD issues them, 190 integer ones, 260 for exchanges through the registers, and LDS traffic of the four
 // wavefronts (24 stores and 33 loads of 1 KB each); they overlap little, since the wavefronts run in step.  Two gates on a
-// compute unit take 5.4 us: the vector ALU is busy 60 % of it, and wavefronts wait to issue LDS instructions a fifth of it.
+// compute unit take 5.4 us: the vector ALU is busy 72 % of it, and wavefronts wait to issue LDS instructions a tenth of it (a
+// fifth with the last exchange through LDS as well).
 // Measured at n = 630, ms per launch of 300 / 512 gates: 3.4 / 3.65 (3.45 / 3.85 with the last exchange through LDS as well)
 // against 3.9 / 4.0 of k_blind_rotate_split; beyond two gates per compute unit that kernel is the faster one (700 gates:
 // 5.2 against 4.9; three quads per compute unit on 168 registers 5.1).
@@ -714,9 +715,11 @@ __global__ __launch_bounds__(256, 2) void k_blind_rotate_quad(
 // transform; it matters less so, too, whether the key comes from HBM or from the Infinity Cache.
 // Cycles of a step, 6300 in all: transforms 3300 (three wavefronts on a SIMD with 270 vector instructions each, 120 of them
 // FP64, 48 exchanges through the registers), products 700, inverse 700, joining and publishing 850, barriers.  The vector
-// ALU is busy 80 % of them.
-// Measured at n = 630, ms per rotation of 1 / 83 / 250 gates: 1.66 / 1.66 / 1.75, whether the key comes from HBM or from the
-// Infinity Cache; k_blind_rotate_quad takes 2.27 / 2.25 / 2.3 and 2.60 / 2.41 / 2.40 when it comes from HBM.  With the inverse
+// ALU is busy 80 % of them, the LDS pipe 43 %; a sixth of the LDS cycles are bank conflicts (the store to y puts sixteen
+// neighbouring lanes on eight slots modulo 16, and the 8-byte halves of base lie 16 bytes apart).
+// Measured at n = 630, ms per rotation of 1 / 83 / 250 / 256 gates: 1.66 / 1.68 / 1.72 / 1.74 with the key in the Infinity
+// Cache, 1.66 / 1.69 / 1.75 / 1.83 with the key in HBM; k_blind_rotate_quad takes 2.26 / 2.26 / 2.30 / 2.27 and 2.60 / 2.42 /
+// 2.41 / 2.41.  (That is at 2.4 GHz; where the card lowers its clock to 2.0, 250 gates take 2.0 to 2.1 ms.)  With the inverse
 // transforms in four wavefronts, a half each, it was 6 % slower; eight wavefronts in all, four of them with two digits, take
 // as long as the four of k_blind_rotate_quad.  A register more than there are costs 500 cycles of every step where the wait
 // for it is on the way; another order of the wavefronts' priorities, or the second half of the key requested any later, 2 to
@@ -724,7 +727,9 @@ __global__ __launch_bounds__(256, 2) void k_blind_rotate_quad(
 // With more than one gate per compute unit a second workgroup does not fit (162 registers x 12), two rounds take longer
 // than k_blind_rotate_quad's one (3.7 against 3.5 ms), and so do pairs of gates that share the key values (3.8).
 // ------------------------------------------------------------------------------------------
-// (what is addressed by lane alone first: an LDS instruction's own offset reaches 64 KB)
+// (What is addressed by lane alone first: an LDS instruction's own offset reaches 64 KB, so all but the last of the twelve
+// exchange buffers.  Those with exclusive-or slots of 256 in place of k_blind_rotate_quad's rows of 65: 83 / 160 / 250 gates
+// 1.671 / 1.674 / 1.729 ms against 1.679 / 1.684 / 1.730.)
 struct WideShared {
     uint32_t rot[2][HalfPlan::N];                               // X^abar ACC, plain order
     uint4 base[2][2][2][64];                                       // ACC - offset: [component][block of 256][upper 512][lane], word 2u + m: + 64u + 128m
@@ -733,10 +738,15 @@ struct WideShared {
 };
 
 // A launch fills the compute units that its gates leave idle with workgroups that read the key once, side by side from its
-// beginning: 62 MB come from HBM into the Infinity Cache within the first ten steps or so, and the gates, which have room for
-// one step's values only, no longer wait for HBM (without: 1.91 / 1.81 / 1.81 ms for 1 / 83 / 250 gates; where the key is in the
-// Infinity Cache already nothing changes).  Touching lines some steps ahead from the gates' own workgroups is no substitute: a
-// compute unit's loads return in order, so that the touches hold up the values behind them (one gate: 2.28 ms).
+// beginning, so that the gates, which have room for one step's values only, find them in the Infinity Cache.  A reader takes
+// 64 bytes a clock, 150 GB/s, four times the 37 GB/s (96 KB per 2.6 us) at which the gates go through the key, so that a few
+// are enough, and with a gate on every compute unit there is none.  Key in HBM, ms for 1 / 83 / 250 gates with no reader, one,
+// four, and all: 1.91 / 1.82 / 1.82, 1.73 / 1.71 / 1.73, 1.66 / 1.69 / 1.71, 1.66 / 1.69 / 1.70; 255 gates 1.82 and with their
+// one reader 1.73; 256 gates 1.83.  Key in the Infinity Cache: no difference.  A key larger than that cache (402 MB, n = 4096):
+// 12.4 / 11.7 / 11.8, 12.0 / 11.5 / 11.6, 12.1 / 11.6 / 11.6, 12.3 / 11.7 / 11.7 ms, so it needs no rule of its own.  Work of
+// other streams on the chip is held up no longer than by the gates alone (0 and 255 readers measured alike).
+// Touching lines some steps ahead from the gates' own workgroups is no substitute: a compute unit's loads return in order, so
+// that the touches hold up the values behind them (one gate: 2.28 ms).
 __device__ __forceinline__ void read_ahead(const double2 *__restrict__ key, size_t elems, uint32_t worker, uint32_t workers)
 {
     constexpr int IN_FLIGHT = 8;
@@ -1270,9 +1280,11 @@ __global__ __launch_bounds__(64 * BR_WAVES, 2) void k_cmux(const double2 *__rest
 // Leveled CMux of small levels: one CMux per workgroup of four wavefronts, (component c, half h of the spectrum) as in
 // k_blind_rotate_quad.  Such a level takes as long as one CMux does, operands and selector rows fetched from memory: a
 // wavefront's chain of 2l + 2 transforms becomes l + 1 transforms of half the length.  Measured, us per launch of 1 / 33 /
-// 256 / 512 CMuxes, one wavefront against four: N = 1024 12.4 / 16.0 / 16.8 / 17.8 against 7.9 / 9.0 / 10.2 / 14.1, N =
-// 2048 21.9 / 28.0 / 33.4 / 36.4 against 13.8 / 15.2 / 22.1 / 28.5; with more than two CMuxes per compute unit a second
-// round of workgroups starts and k_cmux is as fast or faster (768: 18.7 against 17.9, 37.6 against 40.2).
+// 256 / 512 CMuxes, one wavefront against four: N = 1024 12.4 / 16.0 / 16.8 / 17.8 against 7.5 / 8.0 / 9.2 / 14.2, N =
+// 2048 21.9 / 28.0 / 33.4 / 36.4 against 14.0 / 14.8 / 19.9 / 29.4 (by HIP events; 5.2 / 6.1 / 7.0 / 12.1 and 11.4 / 12.6 /
+// 17.6 / 26.9 in the kernel trace; levels of up to 192 have their ids in the arguments, k_cmux_quad_args); with more than two
+// CMuxes per compute unit a second round of workgroups starts and k_cmux is as fast or faster (768: 18.7 against 17.9, 37.6
+// against 40.2).
 // ------------------------------------------------------------------------------------------
 template <int N, bool TRACK>
 __device__ __forceinline__ void cmux_by_quad(const double2 *__restrict__ trgsw_hat, uint32_t *trlwe, uint32_t sel, uint32_t in1,

@@ -1,7 +1,7 @@
 """Every way a level can be launched gives the same ciphertext words: the launch shapes that depend on the level's size
 against one wavefront per rotation (SHE_OPT_SPLIT_BELOW = 0), whose words are the oracle's.  At N = 1024 and l = 3 on 256
-compute units that is four wavefronts per rotation up to 512 rotations, two up to 1024, and full rounds of 1024 with the
-rest (at most 512) on four each."""
+compute units that is twelve wavefronts per rotation up to 256 rotations, four up to 512, two up to 1024, and full rounds of
+1024 with the rest (at most 512) on four each."""
 import numpy as np
 import pytest
 
@@ -59,7 +59,8 @@ def test_the_reference_levels_are_the_oracles(levels, real_keys):
         assert np.array_equal(levels["mux"][2][m, :n + 1], O.mux(real_keys, words[sel[m]], words[a[m]], words[b[m]])), m
 
 
-# one gate; around one, two and three gates per compute unit (256 of them)
+# one gate; around one, two and three gates per compute unit (256 of them): twelve wavefronts per gate (1, 2, 255), four (257,
+# 511, 512), two (513, 769)
 @pytest.mark.parametrize("tracking", [False, True])
 @pytest.mark.parametrize("count", [1, 2, 255, 257, 511, 512, 513, 769])
 def test_level_sizes_give_the_same_words(level, count, tracking):
@@ -75,8 +76,8 @@ def test_a_rest_beyond_full_rounds_gives_the_same_words(level, count, tracking):
     assert np.array_equal(run(count, default, tracking), want[:count])
 
 
-# MUX levels leave the samples unswitched: twice as many rotations as entries, on four wavefronts (2 to 512), on two (514 to
-# 1024) and mixed (1026, 1400, 1536, 2200)
+# MUX levels leave the samples unswitched: twice as many rotations as entries, on twelve wavefronts (2, 200), on four (512), on
+# two (514, 900, 1024) and mixed (1026, 1400, 1536, 2200)
 @pytest.mark.parametrize("tracking", [False, True])
 @pytest.mark.parametrize("count", [1, 100, 256, 257, 450, 512, 513, 700, 768, 1100])
 def test_mux_levels_give_the_same_words(levels, count, tracking):
@@ -84,8 +85,8 @@ def test_mux_levels_give_the_same_words(levels, count, tracking):
     assert np.array_equal(run(count, default, tracking, mux=True), want[:count])
 
 
-# other gadgets (Bg at its largest, and l = 2, which has no four-wavefront form) and a key switch of another base, before which
-# no output slot is written: four wavefronts, two, mixed, MUX included
+# other gadgets (Bg at its largest, and l = 2, which has two wavefronts or one) and a key switch of another base, before which no
+# output slot is written: twelve wavefronts (2 rotations), four (300), two (514, 1000), mixed (1026, 1100), MUX included
 @pytest.mark.parametrize("l,bg_bit,ks_t,ks_basebit", [(3, 7, 5, 3), (3, 8, 8, 2), (3, 5, 16, 1), (2, 8, 8, 2)])
 def test_other_parameters_give_the_same_words(l, bg_bit, ks_t, ks_basebit):
     import paper_1906_00148_amd as pkg

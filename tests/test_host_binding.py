@@ -14,7 +14,7 @@ def test_an_array_is_passed_by_its_address(dtype, ty):
     a = np.arange(24, dtype=dtype).reshape(4, 6)
     read_only = a.copy()
     read_only.flags.writeable = False
-    for v in (a, a[1:], a[2:3, 1:4], read_only, read_only[0], np.frombuffer(a.tobytes(), dtype)):
+    for v in (a, a[1:], a[2:3, 1:4], a[:, 1:4], a[::2], read_only, read_only[0], np.frombuffer(a.tobytes(), dtype)):
         assert L.memcmp(B._p(v, ty), v.ctypes.data, v.itemsize * v.shape[-1]) == 0
     scratch = np.zeros(4, dtype)
     L.memset.argtypes = [C.POINTER(ty), C.c_int, C.c_size_t]
