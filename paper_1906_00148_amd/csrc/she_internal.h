@@ -84,6 +84,27 @@ hipError_t launch_trlwe_gather(const uint32_t *trlwe, uint32_t *d_dst, const uin
 // d_in2 may be null when no type is a three-input gate
 hipError_t launch_lincomb(const she_params &P, const CtSpace &cs, const uint8_t *d_type, const uint32_t *d_in0,
                           const uint32_t *d_in1, const uint32_t *d_in2, size_t gates, const LevelWork &W, hipStream_t st);
+// Workgroups of 256 threads that k_blind_rotate_mixed runs a launch with, in this order: four gates on a wavefront each, two
+// gates on two wavefronts each (the last pair may have one), one gate on four; none at all: not a launch for that kernel.  Two
+// workgroups are resident on a compute unit.  Whole rounds of four gates per compute unit go to wavefronts; of the rest, up to
+// one gate per compute unit goes to quads and up to two to pairs, one workgroup per compute unit either way, and up to three
+// to a pair and a quad per compute unit, which beyond ONE round would leave most compute units three workgroups of different
+// length (1700 gates: 11.1 ms against 10.0).  The two sides of the other lines are measured beside the kernel.
+struct MixedBlocks { uint32_t waves = 0, pairs = 0, quads = 0; };
+inline MixedBlocks mixed_blocks(size_t gates, uint32_t cus, size_t split_below)
+{
+    const size_t rounds = gates / (4 * (size_t)cus), rest = gates % (4 * (size_t)cus);
+    MixedBlocks b;
+    if (!rest || rest > split_below) return b;
+    if (rounds && rest <= cus) b.quads = (uint32_t)rest;
+    else if (rounds && rest <= 2 * (size_t)cus) b.pairs = (uint32_t)((rest + 1) / 2);
+    else if (rounds != 1 && rest > 2 * (size_t)cus && rest <= 3 * (size_t)cus) {
+        b.pairs = (uint32_t)((rest - cus + 1) / 2);
+        b.quads = (uint32_t)rest - 2 * b.pairs;
+    } else return b;
+    b.waves = (uint32_t)(rounds * cus);
+    return b;
+}
 hipError_t launch_blind_rotate(const she_params &P, const DeviceKeys &K, const CtSpace &cs, const uint32_t *d_out,
                                size_t gates, const LevelWork &W, unsigned *d_round_err /* nullptr = no tracking */,
                                hipStream_t st, bool raw = false /* write W.raw_ext instead of digits and slots */,

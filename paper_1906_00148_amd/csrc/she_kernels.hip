@@ -263,8 +263,8 @@ __global__ __launch_bounds__(64 * BR_WAVES, 2) void k_blind_rotate(
 
 // ------------------------------------------------------------------------------------------
 // Blind rotation of a small level on two wavefronts per gate, one or two gates per workgroup: at N = 1024 with l = 3 levels
-// of more than two and at most four gates per compute unit (k_blind_rotate_wide and k_blind_rotate_quad have the smaller
-// ones, k_blind_rotate_mixed most of the larger), at other parameters levels of up to six (SHE_OPT_SPLIT_BELOW's default).
+// of more than three and at most four gates per compute unit, and two gates at a time k_blind_rotate_mixed's pairs
+// (k_blind_rotate_wide and k_blind_rotate_quad have the smaller levels, k_blind_rotate_mixed the others), at other parameters levels of up to six (SHE_OPT_SPLIT_BELOW's default).
 // A level of a few hundred gates leaves most SIMDs with one wavefront or none, and the time of
 // the kernel above is then the latency of one wavefront's serial chain of 6 forward and 2
 // inverse transforms per CMux.  Here wavefront c of a gate owns accumulator component c: it
@@ -288,26 +288,33 @@ __device__ __forceinline__ void lds_barrier()
 }
 
 constexpr int largest_divisor_up_to(int v, int cap) { int d = cap < v ? cap : v; while (d > 1 && v % d) d--; return d < 1 ? 1 : d; }
-constexpr int SPLIT_KD = 16;       // key values in flight per wavefront of the split kernel (measured: 8 is slower)
+// Key values in flight per wavefront of the split kernel.  With 16 it spills 21 registers at N = 1024 (36 in the mixed kernel),
+// with 12 none: 700 / 900 / 1400 gates 4.45 / 5.78 / 7.85 ms with 16, 3.96 / 5.65 / 7.40 with 12, 4.00 / 5.68 / 7.47 with 8.
+constexpr int SPLIT_KD = 12;
 // LR > 0: the gadget has LR levels (l == LR) and a wavefront transforms its LR digit polynomials side by side
 // (forward_pipelined), streaming the key rows through SPLIT_KD values in flight; LR == 0: any l, one at a time.
+template <class PL, int GB> struct SplitShared {       // the LDS arrays of one workgroup
+    uint32_t acc[2 * GB][PL::N];
+    double2 xch[2 * GB][PL::XSLOTS];
+    double2 tw[TwTable<PL>::COUNT];
+};
+
 template <class PL, bool TRACK, int GB, int LR>
-__global__ __launch_bounds__(128 * GB, 2) void k_blind_rotate_split(
+__device__ __forceinline__ void rotate_by_component(
+    SplitShared<PL, GB> &sh, uint32_t first_gate,
     const uint16_t *__restrict__ bar, uint32_t bar_stride, uint32_t n, uint32_t l, uint32_t bg_bit,
     const double2 *__restrict__ bk_hat, const double2 *__restrict__ tw_table, uint32_t ks_bits,
-    uint32_t *__restrict__ ext_b, uint16_t *__restrict__ ksd, uint32_t gates, unsigned *round_err, CtSpace cs,
+    uint32_t *__restrict__ ext_b, uint16_t *__restrict__ ksd, uint32_t gates, unsigned *round_err, const CtSpace &cs,
     const uint32_t *__restrict__ out_ids, uint32_t *__restrict__ raw_ext)
 {
     constexpr int P = PL::P, L = PL::L, M = PL::M, N = PL::N;
     static_assert(PL::GPW == 1, "one transform per wavefront");
-    __shared__ uint32_t s_acc[2 * GB][N];
-    __shared__ double2 s_xch[2 * GB][PL::XSLOTS];
-    __shared__ double2 s_tw[TwTable<PL>::COUNT];
+    auto &s_acc = sh.acc; auto &s_xch = sh.xch; auto &s_tw = sh.tw;
 
     const int wave = threadIdx.x >> 6, t = threadIdx.x & 63;
     const int c = wave & 1;                                               // component owned
     // a wavefront pair past the end shadows the last gate and stores nothing: it still meets every barrier
-    const uint32_t g_raw = blockIdx.x * GB + (wave >> 1);
+    const uint32_t g_raw = first_gate + (wave >> 1);
     const bool live = g_raw < gates;
     const uint32_t g = live ? g_raw : gates - 1;
     load_twiddles<PL>(s_tw, tw_table);
@@ -481,6 +488,18 @@ __global__ __launch_bounds__(128 * GB, 2) void k_blind_rotate_split(
             for (uint32_t w = t; w <= n; w += L) o[w] = (w == n) ? body : 0u;
         }
     }
+}
+
+template <class PL, bool TRACK, int GB, int LR>
+__global__ __launch_bounds__(128 * GB, 2) void k_blind_rotate_split(
+    const uint16_t *__restrict__ bar, uint32_t bar_stride, uint32_t n, uint32_t l, uint32_t bg_bit,
+    const double2 *__restrict__ bk_hat, const double2 *__restrict__ tw_table, uint32_t ks_bits,
+    uint32_t *__restrict__ ext_b, uint16_t *__restrict__ ksd, uint32_t gates, unsigned *round_err, CtSpace cs,
+    const uint32_t *__restrict__ out_ids, uint32_t *__restrict__ raw_ext)
+{
+    __shared__ SplitShared<PL, GB> sh;
+    rotate_by_component<PL, TRACK, GB, LR>(sh, blockIdx.x * GB, bar, bar_stride, n, l, bg_bit, bk_hat, tw_table, ks_bits,
+                                           ext_b, ksd, gates, round_err, cs, out_ids, raw_ext);
 }
 
 // ------------------------------------------------------------------------------------------
@@ -959,31 +978,42 @@ __global__ __launch_bounds__(768, 3) void k_blind_rotate_wide(
     }
 }
 
-// Both in one launch: workgroups below `wave_blocks` run four gates on a wavefront each, every later one a single gate on
-// four wavefronts.  A level of gates on a wavefront each takes whole rounds: with one gate more than a multiple of four
-// per compute unit, one more workgroup sits on a few compute units for as long as a full round does (its wavefronts run
-// 630 CMuxes of 10 us alone, whatever else is idle).  Here the rest beyond full rounds runs its 630 CMuxes in 3.6 us
-// each, beside the wavefronts of the last round that the hardware let fall behind (of two on a SIMD the older one goes
-// first: 6.9 ms against 10.7).  Measured at n = 630 on 256 compute units, in ms, one wavefront per gate (or the split
-// kernel, up to 1536) against mixed: 1100 gates 8.4 / 6.2, 1280 8.4 / 7.0, 1536 9.7 / 8.8, 2100 16.1 / 12.3, 2304 16.1 /
-// 12.1, 2500 16.0 / 14.4, 3300 20.2 / 16.0, 4352 25.3 / 21.0, 4608 25.5 / 23.3, 6500 34.6 / 33.0, 8600 44.1 / 42.5.  A
-// rest of more than two gates per compute unit gains nothing (3600: 20.3 / 20.4, 5000: 25.1 / 26.6, 13001: 62.8 / 63.0).
-template <bool TRACK, int LR>
+// Three forms in one launch, in the order of mixed_blocks: workgroups of four gates on a wavefront each, of two gates on two
+// wavefronts each, of a single gate on four.
+// A level of gates on a wavefront each takes whole rounds: with one gate more than a multiple of four per compute unit, one
+// more workgroup sits on a few compute units for as long as a full round does (its wavefronts run 630 CMuxes of 10 us alone,
+// whatever else is idle).  Here the rest beyond full rounds runs its 630 CMuxes in 3.6 us (quad) or 6 us (pair) each, beside
+// the wavefronts of the last round that the hardware let fall behind (of two on a SIMD the older one goes first: 6.9 ms
+// against 10.7).  A level of more than two and at most three gates per compute unit has a pair and a quad on each: eight
+// wavefronts, two on every SIMD, where k_blind_rotate_split's six leave two SIMDs with one.
+// Measured at n = 630 on 256 compute units, ms, on one box per line:
+//   gates on a wavefront each, or k_blind_rotate_split up to 1536, against rounds and quads: 1100 gates 8.4 / 6.2, 1280 8.4 /
+//   7.0, 2100 16.1 / 12.3, 2304 16.1 / 12.1, 3300 20.2 / 16.0, 4352 25.3 / 21.0;
+//   a rest of up to two gates per compute unit, quads against pairs: 1300 gates 8.8 / 7.2, 1536 8.5 / 7.65, 2400 13.9 / 13.8,
+//   2560 13.8 / 13.7, 3584 19.4 / 17.7, 4608 22.8 / 22.6, 5600 28.0 / 27.0;
+//   up to three, as before (k_blind_rotate_split, or wavefronts) against a pair and a quad each: 514 gates 4.94 / 3.95, 768
+//   4.93 / 4.00, 2700 16.0 / 14.5, 3840 20.1 / 19.4, 4700 24.9 / 23.6, 13001 62.4 / 61.4.
+// A rest of more than three gates per compute unit gains nothing (3900: 20.1 / 21.5).
+template <bool TRACK, int LR, bool PAIRS>
 __global__ __launch_bounds__(256, 2) void k_blind_rotate_mixed(
     const uint16_t *__restrict__ bar, uint32_t bar_stride, uint32_t n, uint32_t bg_bit,
     const double2 *__restrict__ bk_hat, const double2 *__restrict__ tw_table, const double2 *__restrict__ half_table,
-    uint32_t ks_bits, uint32_t *__restrict__ ext_b, uint16_t *__restrict__ ksd, uint32_t wave_blocks, unsigned *round_err,
-    CtSpace cs, const uint32_t *__restrict__ out_ids, uint32_t *__restrict__ raw_ext)
+    uint32_t ks_bits, uint32_t *__restrict__ ext_b, uint16_t *__restrict__ ksd, uint32_t gates, MixedBlocks blocks,
+    unsigned *round_err, CtSpace cs, const uint32_t *__restrict__ out_ids, uint32_t *__restrict__ raw_ext)
 {
     using PL = Plan<3, 3>;
-    static_assert(PL::N == HalfPlan::N && PL::GPW == 1 && BR_WAVES == 4, "both forms on 256 threads at the same ring degree");
-    __shared__ union { WaveShared<PL> wave; QuadShared quad; } sh;
-    if (blockIdx.x < wave_blocks)
-        rotate_by_wavefront<PL, TRACK, LR>(sh.wave.acc, sh.wave.xch, sh.wave.tw, blockIdx.x, bar, bar_stride, n, LR, bg_bit,
-                                           bk_hat, tw_table, ks_bits, ext_b, ksd, wave_blocks * BR_WAVES, round_err, cs, out_ids, raw_ext);
+    static_assert(PL::N == HalfPlan::N && PL::GPW == 1 && BR_WAVES == 4, "all forms on 256 threads at the same ring degree");
+    __shared__ union { WaveShared<PL> wave; SplitShared<PL, 2> pair; QuadShared quad; } sh;
+    const uint32_t first_pair = blocks.waves * BR_WAVES, first_quad = gates - blocks.quads, b = blockIdx.x;
+    if (b < blocks.waves)
+        rotate_by_wavefront<PL, TRACK, LR>(sh.wave.acc, sh.wave.xch, sh.wave.tw, b, bar, bar_stride, n, LR, bg_bit, bk_hat,
+                                           tw_table, ks_bits, ext_b, ksd, first_pair, round_err, cs, out_ids, raw_ext);
+    else if (PAIRS && b < blocks.waves + blocks.pairs)
+        rotate_by_component<PL, TRACK, 2, LR>(sh.pair, first_pair + 2 * (b - blocks.waves), bar, bar_stride, n, LR, bg_bit,
+                                              bk_hat, tw_table, ks_bits, ext_b, ksd, first_quad, round_err, cs, out_ids, raw_ext);
     else
-        rotate_by_quad<TRACK, LR>(sh.quad, wave_blocks * BR_WAVES + (blockIdx.x - wave_blocks), bar, bar_stride, n, bg_bit,
-                                  bk_hat, half_table, ks_bits, ext_b, ksd, round_err, cs, out_ids, raw_ext);
+        rotate_by_quad<TRACK, LR>(sh.quad, first_quad + (b - blocks.waves - blocks.pairs), bar, bar_stride, n, bg_bit, bk_hat,
+                                  half_table, ks_bits, ext_b, ksd, round_err, cs, out_ids, raw_ext);
 }
 
 // Second half of a native MUX: the two rotations' samples are added, 1/8 goes on the body, and the
@@ -1904,16 +1934,17 @@ static hipError_t blind_rotate_t(const she_params &P, const DeviceKeys &K, size_
     const uint32_t ks_bits = P.ks_t * P.ks_basebit;
     const bool split = gates <= split_below;
     if constexpr (PL::N == HalfPlan::N) {
-        // full rounds on one wavefront per gate, the rest on four (measured beside the kernel); this kernel and the next are
-        // built for three digits per coefficient only
-        const size_t round = BR_WAVES * (size_t)K.cus, rest = gates % round;
-        if (P.l == 3 && gates > round && rest && rest <= std::min<size_t>(2 * (size_t)K.cus, split_below)) {
-            const size_t wave_blocks = (gates - rest) / BR_WAVES;
-#define SHE_LAUNCH_MIXED(TRACK)                                                                                       \
-    hipLaunchKernelGGL((k_blind_rotate_mixed<TRACK, 3>), dim3((unsigned)(wave_blocks + rest)), dim3(64 * BR_WAVES), 0, \
-                       st, W.bar, W.bar_stride, P.n, P.bg_bit, K.bk_hat, K.twiddles, K.half_twiddles, ks_bits, W.ext_b, \
-                       W.ksd, (uint32_t)wave_blocks, d_round_err, cs, d_out, raw_ext)
-            if (d_round_err) SHE_LAUNCH_MIXED(true); else SHE_LAUNCH_MIXED(false);
+        // this kernel and the next are built for three digits per coefficient only
+        const MixedBlocks blocks = P.l == 3 ? mixed_blocks(gates, K.cus, split_below) : MixedBlocks{};
+        if (blocks.pairs + blocks.quads) {
+            const dim3 grid(blocks.waves + blocks.pairs + blocks.quads);
+#define SHE_LAUNCH_MIXED(TRACK, PAIRS)                                                                                \
+    hipLaunchKernelGGL((k_blind_rotate_mixed<TRACK, 3, PAIRS>), grid, dim3(64 * BR_WAVES), 0, st, W.bar, W.bar_stride, \
+                       P.n, P.bg_bit, K.bk_hat, K.twiddles, K.half_twiddles, ks_bits, W.ext_b, W.ksd, (uint32_t)gates, \
+                       blocks, d_round_err, cs, d_out, raw_ext)
+            if (blocks.pairs) { if (d_round_err) SHE_LAUNCH_MIXED(true, true); else SHE_LAUNCH_MIXED(false, true); }
+            else if (d_round_err) SHE_LAUNCH_MIXED(true, false);
+            else SHE_LAUNCH_MIXED(false, false);
 #undef SHE_LAUNCH_MIXED
             return hipGetLastError();
         }
@@ -1945,9 +1976,9 @@ static hipError_t blind_rotate_t(const she_params &P, const DeviceKeys &K, size_
         //   N=512, l=3   1.9 / 2.6 / 2.8 / 3.3 / 4.6 / 6.2   2.3 / 2.3 / 3.7 / 3.7 / 5.5 / 5.5   3.8 to 1024, then 5.9
         //   N=256, l=3   1.4 / 1.8 / 2.1 / 2.5 / 3.1 / 3.7   1.6 / 1.6 / 2.5 / 2.6 / 3.6 / 3.6   3.4 to 1024, then 4.8
         // (at N=512, l=2 one per workgroup stays ahead at 1536: 3.8 against 4.0).  At N=1024 with l=3 launches of up to two
-        // gates per compute unit run on twelve or four wavefronts each and those of five to six go to the mixed kernel, so
-        // one per workgroup is the only form: 513 to 1024 gates, and above them, with SHE_OPT_SPLIT_BELOW raised, what the mixed
-        // kernel does not take.
+        // gates per compute unit run on twelve or four wavefronts each, those of up to three and of five to six go to the
+        // mixed kernel, and one per workgroup is the only form: 769 to 1024 gates (900: 5.65 ms, two per workgroup 6.2), and
+        // above them, with SHE_OPT_SPLIT_BELOW raised, what the mixed kernel does not take.
         const size_t per_cu = (gates + K.cus - 1) / std::max<uint32_t>(K.cus, 1);
         const bool triple = P.l == 3;
         constexpr bool quads = PL::N == HalfPlan::N;
