@@ -148,76 +148,47 @@ int ensure_raw(she_ctx *c, size_t jobs)
     return SHE_OK;
 }
 
-int ensure_mux_arrays(she_ctx *c, size_t muxes)
-{
-    if (muxes <= c->d_mux_cap) return SHE_OK;
-    HIP_TRY(c, hipStreamSynchronize(c->stream));
-    if (c->d_mtype) { hipFree(c->d_mtype); hipFree(c->d_min0); hipFree(c->d_min1); hipFree(c->d_mout); }
-    c->d_mtype = nullptr; c->d_min0 = c->d_min1 = c->d_mout = nullptr; c->d_mux_cap = 0;
-    muxes += muxes / 4;
-    HIP_TRY(c, hipMalloc((void **)&c->d_mtype, 2 * muxes));
-    HIP_TRY(c, hipMalloc((void **)&c->d_min0, 2 * muxes * sizeof(uint32_t)));
-    HIP_TRY(c, hipMalloc((void **)&c->d_min1, 2 * muxes * sizeof(uint32_t)));
-    HIP_TRY(c, hipMalloc((void **)&c->d_mout, muxes * sizeof(uint32_t)));
-    c->d_mux_cap = muxes;
-    return SHE_OK;
-}
-
-
-// Enqueues one level (device arrays), cut into chunks of at most MAX_LEVEL_CHUNK gates.
-// `W` is the level's scratch (the context's own buffers, or the caller-free static buffer); `timed` records HIP events
-// around the kernels (creating an event allocates, so the entry point that must not allocate passes false).
-int enqueue_level_on(she_ctx *c, const LevelWork &W, bool timed, const uint8_t *d_type, const uint32_t *d_in0,
-                     const uint32_t *d_in1, const uint32_t *d_out, size_t gates, const uint32_t *d_in2 = nullptr)
+// Enqueues one level: `gates` jobs of a gate each, then two jobs for each of `muxes` MUX entries (device arrays of
+// gates + 2 muxes jobs, d_out of gates + muxes ids).  All its rotations run in one launch where the scratch holds them, so that
+// a level of 96 gates and 416 MUXes takes as long as 928 rotations and not 1.7 ms more; otherwise in chunks of at most the
+// scratch's size, gates first.  `W` is the level's scratch (the context's own buffers, or the caller-free static buffer);
+// `timed` records HIP events around the kernels (creating an event allocates, so the entry point that must not allocate
+// passes false).
+int enqueue_level_on(she_ctx *c, LevelWork W, bool timed, const uint8_t *d_type, const uint32_t *d_in0,
+                     const uint32_t *d_in1, const uint32_t *d_out, size_t gates, size_t muxes = 0, const uint32_t *d_in2 = nullptr)
 {
     if (c->P.N > 1024) return fail(c, SHE_EINVAL, "gate bootstrapping is built for N <= 1024; N = 2048 serves the leveled calls");
     const CtSpace cs = space(c);
     LevelTimer *timer = timed ? &c->timer : nullptr;
     if (timed) c->timer_levels++;
-    for (size_t off = 0; off < gates; off += MAX_LEVEL_CHUNK) {
-        const size_t cnt = std::min<size_t>(MAX_LEVEL_CHUNK, gates - off);
+    const size_t holds = std::min<size_t>(W.gates, MAX_LEVEL_CHUNK), jobs = gates + 2 * muxes;
+    for (size_t off = 0; off < jobs;) {
+        size_t direct = gates, pairs = muxes;
+        if (jobs > holds) {
+            direct = off < gates ? std::min(holds, gates - off) : 0;
+            pairs = direct ? 0 : std::min(holds / 2, (jobs - off) / 2);
+        }
+        const size_t cnt = direct + 2 * pairs, entry = off <= gates ? off : gates + (off - gates) / 2;
+        W.direct = direct;
         if (timer) HIP_TRY(c, timer->mark(c->stream));
         HIP_TRY(c, launch_lincomb(c->P, cs, d_type + off, d_in0 + off, d_in1 + off, d_in2 ? d_in2 + off : nullptr, cnt, W,
                                   c->stream));
         if (timer) HIP_TRY(c, timer->mark(c->stream));
-        HIP_TRY(c, launch_blind_rotate(c->P, c->dk, cs, d_out + off, cnt, W, c->track_round ? c->d_round_err : nullptr, c->stream,
-                                       false, c->split_below));
+        HIP_TRY(c, launch_blind_rotate(c->P, c->dk, cs, direct ? d_out + entry : nullptr, cnt, W,
+                                       c->track_round ? c->d_round_err : nullptr, c->stream, pairs > 0, c->split_below));
         if (timer) HIP_TRY(c, timer->mark(c->stream));
-        HIP_TRY(c, launch_key_switch(c->P, c->dk, cs, d_out + off, cnt, W, c->stream));
+        if (pairs) HIP_TRY(c, launch_mux_combine(c->P, c->dk, cs, d_out + entry, pairs, W, c->stream));
+        HIP_TRY(c, launch_key_switch(c->P, c->dk, cs, d_out + entry, direct + pairs, W, c->stream));
         if (timer) HIP_TRY(c, timer->mark(c->stream));
+        off += cnt;
     }
     return SHE_OK;
 }
 
 int enqueue_level(she_ctx *c, const uint8_t *d_type, const uint32_t *d_in0, const uint32_t *d_in1,
-                  const uint32_t *d_out, size_t gates, const uint32_t *d_in2 = nullptr)
+                  const uint32_t *d_out, size_t gates, size_t muxes = 0, const uint32_t *d_in2 = nullptr)
 {
-    return enqueue_level_on(c, c->work, c->timing, d_type, d_in0, d_in1, d_out, gates, d_in2);
-}
-
-// Enqueues one level of native MUX entries: jobs 2m and 2m+1 are the two rotations of entry m
-// (device arrays of 2*muxes jobs), d_out has one id per entry.
-int enqueue_mux_level(she_ctx *c, const uint8_t *d_jtype, const uint32_t *d_jin0, const uint32_t *d_jin1,
-                      const uint32_t *d_out, size_t muxes)
-{
-    if (c->P.N > 1024) return fail(c, SHE_EINVAL, "gate bootstrapping is built for N <= 1024; N = 2048 serves the leveled calls");
-    const CtSpace cs = space(c);
-    LevelTimer *timer = c->timing ? &c->timer : nullptr;
-    const size_t step = MAX_LEVEL_CHUNK / 2;
-    for (size_t off = 0; off < muxes; off += step) {
-        const size_t cnt = std::min<size_t>(step, muxes - off);
-        if (timer) HIP_TRY(c, timer->mark(c->stream));
-        HIP_TRY(c, launch_lincomb(c->P, cs, d_jtype + 2 * off, d_jin0 + 2 * off, d_jin1 + 2 * off, nullptr, 2 * cnt, c->work,
-                                  c->stream));
-        if (timer) HIP_TRY(c, timer->mark(c->stream));
-        HIP_TRY(c, launch_blind_rotate(c->P, c->dk, cs, nullptr, 2 * cnt, c->work,
-                                       c->track_round ? c->d_round_err : nullptr, c->stream, true, c->split_below));
-        if (timer) HIP_TRY(c, timer->mark(c->stream));
-        HIP_TRY(c, launch_mux_combine(c->P, c->dk, cs, d_out + off, cnt, c->work, c->stream));
-        HIP_TRY(c, launch_key_switch(c->P, c->dk, cs, d_out + off, cnt, c->work, c->stream));
-        if (timer) HIP_TRY(c, timer->mark(c->stream));
-    }
-    return SHE_OK;
+    return enqueue_level_on(c, c->work, c->timing, d_type, d_in0, d_in1, d_out, gates, muxes, d_in2);
 }
 
 // Folds the recorded events into last_ms; the stream must have finished.
@@ -278,58 +249,59 @@ int run_netlist(she_ctx *c, Netlist &nl, const std::vector<uint32_t> &out_wires,
     if (!temp_slots) return fail(c, SHE_EDEVICE, "internal error: a temporary lost its slot while it was live");
     int rc = ensure_temp(c, temp_slots);
     if (rc) return rc;
-    // MUX entries become two rotation jobs each, kept in level order in their own arrays
-    std::vector<uint8_t> jt;
-    std::vector<uint32_t> j0, j1, mo;
-    std::vector<size_t> mux_first(levels + 1, 0);          // index of each level's first entry in mo
-    size_t widest = 0;
-    for (size_t lv = 0; lv < levels; lv++) {
-        mux_first[lv] = mo.size();
-        for (size_t g = mux_start[lv]; g < bounds[lv + 1]; g++) {
-            const uint32_t m = nl.type[g] - MUX_BASE;
-            jt.push_back((uint8_t)(m >> 4)); j0.push_back(nl.in0[g]); j1.push_back(nl.in1[g]);
-            jt.push_back((uint8_t)(m & 15)); j0.push_back(nl.in0[g]); j1.push_back(nl.in2[g]);
-            mo.push_back(nl.out[g]);
-        }
-        widest = std::max(widest, std::max(mux_start[lv] - bounds[lv], 2 * (bounds[lv + 1] - mux_start[lv])));
-    }
-    mux_first[levels] = mo.size();
+    // the jobs of a level: its gates, then two rotations for every MUX entry
+    std::vector<size_t> job_first(levels + 1, 0);
+    size_t widest = 0, most_gates = 0, most_muxes = 0;
     c->level_gates.resize(levels);
     c->level_muxes.resize(levels);
     for (size_t lv = 0; lv < levels; lv++) {
-        c->level_gates[lv] = mux_start[lv] - bounds[lv];
-        c->level_muxes[lv] = bounds[lv + 1] - mux_start[lv];
+        const size_t gates = mux_start[lv] - bounds[lv], muxes = bounds[lv + 1] - mux_start[lv];
+        c->level_gates[lv] = gates;
+        c->level_muxes[lv] = muxes;
+        job_first[lv + 1] = job_first[lv] + gates + 2 * muxes;
+        widest = std::max(widest, gates + 2 * muxes);
+        most_gates = std::max(most_gates, gates);
+        most_muxes = std::max(most_muxes, muxes);
     }
-    if ((rc = ensure_work(c, std::min<size_t>(widest, MAX_LEVEL_CHUNK)))) return rc;
-    if ((rc = ensure_gate_arrays(c, std::max(G, nl.copy_src.size())))) return rc;
-    if (!mo.empty()) {
-        if ((rc = ensure_mux_arrays(c, mo.size()))) return rc;
-        if ((rc = ensure_raw(c, std::min<size_t>(widest, MAX_LEVEL_CHUNK)))) return rc;
+    const size_t jobs = job_first[levels];
+    std::vector<uint8_t> jt;
+    std::vector<uint32_t> j0, j1, j2;
+    if (most_muxes) {
+        jt.reserve(jobs); j0.reserve(jobs); j1.reserve(jobs); j2.reserve(jobs);
+        auto job = [&](uint32_t code, uint32_t a, uint32_t b, uint32_t third) {
+            jt.push_back((uint8_t)code); j0.push_back(a); j1.push_back(b); j2.push_back(third);
+        };
+        for (size_t lv = 0; lv < levels; lv++) {
+            for (size_t g = bounds[lv]; g < mux_start[lv]; g++) job(nl.type[g], nl.in0[g], nl.in1[g], nl.in2[g]);
+            for (size_t g = mux_start[lv]; g < bounds[lv + 1]; g++) {
+                const uint32_t m = nl.type[g] - MUX_BASE;
+                job(m >> 4, nl.in0[g], nl.in1[g], 0);
+                job(m & 15, nl.in0[g], nl.in2[g], 0);
+            }
+        }
     }
+    const std::vector<uint8_t> &types = most_muxes ? jt : nl.type;
+    const std::vector<uint32_t> &in0 = most_muxes ? j0 : nl.in0, &in1 = most_muxes ? j1 : nl.in1, &in2 = most_muxes ? j2 : nl.in2;
+    // without memory for a level's gates and MUXes side by side there may be enough for one after the other
+    const size_t apart = std::max(most_gates, 2 * most_muxes);
+    rc = ensure_work(c, std::min<size_t>(widest, MAX_LEVEL_CHUNK));
+    if (rc == SHE_ENOMEM && apart < widest) rc = ensure_work(c, std::min<size_t>(apart, MAX_LEVEL_CHUNK));
+    if (rc) return rc;
+    if ((rc = ensure_gate_arrays(c, std::max(jobs, nl.copy_src.size())))) return rc;
+    if (most_muxes && (rc = ensure_raw(c, std::min<size_t>(2 * most_muxes, MAX_LEVEL_CHUNK)))) return rc;
     c->timer.clear();
     c->timer_levels = 0;
     if (G) {
-        HIP_TRY(c, hipMemcpyAsync(c->d_type, nl.type.data(), G, hipMemcpyHostToDevice, c->stream));
-        HIP_TRY(c, hipMemcpyAsync(c->d_in0, nl.in0.data(), G * 4, hipMemcpyHostToDevice, c->stream));
-        HIP_TRY(c, hipMemcpyAsync(c->d_in1, nl.in1.data(), G * 4, hipMemcpyHostToDevice, c->stream));
-        HIP_TRY(c, hipMemcpyAsync(c->d_in2, nl.in2.data(), G * 4, hipMemcpyHostToDevice, c->stream));
+        HIP_TRY(c, hipMemcpyAsync(c->d_type, types.data(), jobs, hipMemcpyHostToDevice, c->stream));
+        HIP_TRY(c, hipMemcpyAsync(c->d_in0, in0.data(), jobs * 4, hipMemcpyHostToDevice, c->stream));
+        HIP_TRY(c, hipMemcpyAsync(c->d_in1, in1.data(), jobs * 4, hipMemcpyHostToDevice, c->stream));
+        HIP_TRY(c, hipMemcpyAsync(c->d_in2, in2.data(), jobs * 4, hipMemcpyHostToDevice, c->stream));
         HIP_TRY(c, hipMemcpyAsync(c->d_out, nl.out.data(), G * 4, hipMemcpyHostToDevice, c->stream));
-        if (!mo.empty()) {
-            HIP_TRY(c, hipMemcpyAsync(c->d_mtype, jt.data(), jt.size(), hipMemcpyHostToDevice, c->stream));
-            HIP_TRY(c, hipMemcpyAsync(c->d_min0, j0.data(), j0.size() * 4, hipMemcpyHostToDevice, c->stream));
-            HIP_TRY(c, hipMemcpyAsync(c->d_min1, j1.data(), j1.size() * 4, hipMemcpyHostToDevice, c->stream));
-            HIP_TRY(c, hipMemcpyAsync(c->d_mout, mo.data(), mo.size() * 4, hipMemcpyHostToDevice, c->stream));
-        }
         for (size_t lv = 0; lv < levels; lv++) {
-            const size_t a = bounds[lv], m = mux_start[lv];
-            if (m > a && (rc = enqueue_level(c, c->d_type + a, c->d_in0 + a, c->d_in1 + a, c->d_out + a, m - a, c->d_in2 + a)))
+            const size_t f = job_first[lv];
+            if ((rc = enqueue_level(c, c->d_type + f, c->d_in0 + f, c->d_in1 + f, c->d_out + bounds[lv], c->level_gates[lv],
+                                    c->level_muxes[lv], c->d_in2 + f)))
                 return rc;
-            const size_t f = mux_first[lv], cnt = mux_first[lv + 1] - f;
-            if (cnt) {
-                if (m > a) c->timer_levels--;              // gates and MUX entries of one level count once
-                c->timer_levels++;
-                if ((rc = enqueue_mux_level(c, c->d_mtype + 2 * f, c->d_min0 + 2 * f, c->d_min1 + 2 * f, c->d_mout + f, cnt))) return rc;
-            }
         }
     }
     if (!nl.copy_src.empty()) {
@@ -530,7 +502,6 @@ void she_free(she_ctx *c)
     hipFree(c->work.bar); hipFree(c->work.ext_b); hipFree(c->work.ksd);
     hipFree(c->d_type); hipFree(c->d_in0); hipFree(c->d_in1); hipFree(c->d_in2); hipFree(c->d_out);
     hipFree(c->d_stage); hipFree(c->d_round_err); hipFree(c->work.raw_ext);
-    hipFree(c->d_mtype); hipFree(c->d_min0); hipFree(c->d_min1); hipFree(c->d_mout);
     free_leveled(c);
     delete c;
 }
@@ -658,7 +629,7 @@ try {
     HIP_TRY(c, hipMemcpyAsync(c->d_out, out, ngates * 4, hipMemcpyHostToDevice, c->stream));
     c->timer.clear();
     c->timer_levels = 0;
-    if ((rc = enqueue_level(c, c->d_type, c->d_in0, c->d_in1, c->d_out, ngates, c->d_in2))) return rc;
+    if ((rc = enqueue_level(c, c->d_type, c->d_in0, c->d_in1, c->d_out, ngates, 0, c->d_in2))) return rc;
     HIP_TRY(c, hipStreamSynchronize(c->stream));
     return finish_timing(c);
 } SHE_NOTHROW(c)
@@ -731,14 +702,14 @@ try {
         }
         if ((rc = ensure_work(c, std::min<size_t>(2 * nmux, MAX_LEVEL_CHUNK)))) return rc;
         if ((rc = ensure_raw(c, std::min<size_t>(2 * nmux, MAX_LEVEL_CHUNK)))) return rc;
-        if ((rc = ensure_mux_arrays(c, nmux))) return rc;
-        HIP_TRY(c, hipMemcpyAsync(c->d_mtype, jt.data(), jt.size(), hipMemcpyHostToDevice, c->stream));
-        HIP_TRY(c, hipMemcpyAsync(c->d_min0, j0.data(), j0.size() * 4, hipMemcpyHostToDevice, c->stream));
-        HIP_TRY(c, hipMemcpyAsync(c->d_min1, j1.data(), j1.size() * 4, hipMemcpyHostToDevice, c->stream));
-        HIP_TRY(c, hipMemcpyAsync(c->d_mout, out, nmux * 4, hipMemcpyHostToDevice, c->stream));
+        if ((rc = ensure_gate_arrays(c, 2 * nmux))) return rc;
+        HIP_TRY(c, hipMemcpyAsync(c->d_type, jt.data(), jt.size(), hipMemcpyHostToDevice, c->stream));
+        HIP_TRY(c, hipMemcpyAsync(c->d_in0, j0.data(), j0.size() * 4, hipMemcpyHostToDevice, c->stream));
+        HIP_TRY(c, hipMemcpyAsync(c->d_in1, j1.data(), j1.size() * 4, hipMemcpyHostToDevice, c->stream));
+        HIP_TRY(c, hipMemcpyAsync(c->d_out, out, nmux * 4, hipMemcpyHostToDevice, c->stream));
         c->timer.clear();
-        c->timer_levels = 1;
-        if ((rc = enqueue_mux_level(c, c->d_mtype, c->d_min0, c->d_min1, c->d_mout, nmux))) return rc;
+        c->timer_levels = 0;
+        if ((rc = enqueue_level(c, c->d_type, c->d_in0, c->d_in1, c->d_out, 0, nmux))) return rc;
         HIP_TRY(c, hipStreamSynchronize(c->stream));
         return finish_timing(c);
     } catch (const std::bad_alloc &) {

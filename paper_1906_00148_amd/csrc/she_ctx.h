@@ -65,9 +65,6 @@ struct she_ctx {
     bool cells3 = false;                 // SHE_OPT_GATE3_CELLS
     bool columns = false;                // SHE_OPT_COLUMN_ADDER
     size_t split_below = 0;              // SHE_OPT_SPLIT_BELOW (set at creation: 6 x compute units)
-    uint8_t *d_mtype = nullptr;          // device staging of MUX rotations: 2 jobs per MUX entry
-    uint32_t *d_min0 = nullptr, *d_min1 = nullptr, *d_mout = nullptr;
-    size_t d_mux_cap = 0;
     bool timing = true;                  // record HIP events around every kernel
     she::LevelTimer timer;               // events not yet folded into last_ms
     size_t timer_levels = 0;

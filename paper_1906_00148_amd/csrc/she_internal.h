@@ -42,6 +42,7 @@ struct LevelWork {                // scratch of one level launch, sized for `gat
     size_t gates = 0;
     uint32_t *raw_ext = nullptr;  // [jobs][N+1] extracted samples of MUX rotations (not yet key-switched)
     size_t raw_jobs = 0;
+    size_t direct = 0;            // gates of a launch; its rotations from there on belong to MUXes, two each
 };
 
 // ---- kernel launchers (she_kernels.hip); each returns a hipError_t and never synchronises ----
@@ -107,10 +108,12 @@ inline MixedBlocks mixed_blocks(size_t gates, uint32_t cus, size_t split_below)
 }
 hipError_t launch_blind_rotate(const she_params &P, const DeviceKeys &K, const CtSpace &cs, const uint32_t *d_out,
                                size_t gates, const LevelWork &W, unsigned *d_round_err /* nullptr = no tracking */,
-                               hipStream_t st, bool raw = false /* write W.raw_ext instead of digits and slots */,
+                               hipStream_t st, bool mux = false /* rotations from W.direct on write W.raw_ext instead of digits
+                                                                   and slots */,
                                size_t split_below = 0 /* levels, and rests beyond full rounds, of at most this many
                                                         gates may run on several wavefronts per gate */);
-// MUX m: sample = raw_ext[2m] + raw_ext[2m+1] + (0, 1/8) -> key-switch digits, body and slot initialisation of gate m
+// MUX m: sample = raw_ext[2m] + raw_ext[2m+1] + (0, 1/8) -> key-switch digits, body and slot initialisation of the level's
+// entry W.direct + m (d_out: the ids of all the level's entries)
 hipError_t launch_mux_combine(const she_params &P, const DeviceKeys &K, const CtSpace &cs, const uint32_t *d_out,
                               size_t muxes, const LevelWork &W, hipStream_t st);
 // Workgroups among which k_key_switch_mfma splits the range of N coefficients (`gate_blocks` x `col_tiles` of them for every

@@ -80,6 +80,13 @@ __global__ __launch_bounds__(128) void k_lincomb(CtSpace cs, const uint8_t *__re
 // ------------------------------------------------------------------------------------------
 constexpr int BR_WAVES = 4;     // measured: 2 and 8 wavefronts per workgroup are slower
 
+// Where the rotations of MUXes leave their samples: those of a launch from `first` on, if it has any.
+struct RawSamples {
+    uint32_t *ext, first;
+    __device__ __forceinline__ bool takes(uint32_t g) const { return ext && g >= first; }
+    __device__ __forceinline__ uint32_t *row(uint32_t g, uint32_t N) const { return ext + (size_t)(g - first) * (N + 1); }
+};
+
 // LC: the gadget length when it is known at compile time (the loops over the 2 LC rows of a step are then unrolled:
 // shifts and row offsets become constants, measured 1.2 % faster at l = 3 on alternating runs), 0 for any length.
 template <class PL> struct WaveShared {               // the LDS arrays of one workgroup
@@ -94,7 +101,7 @@ __device__ __forceinline__ void rotate_by_wavefront(
     const uint16_t *__restrict__ bar, uint32_t bar_stride, uint32_t n, uint32_t l_arg, uint32_t bg_bit,
     const double2 *__restrict__ bk_hat, const double2 *__restrict__ tw_table, uint32_t ks_bits,
     uint32_t *__restrict__ ext_b, uint16_t *__restrict__ ksd, uint32_t gates, unsigned *round_err, const CtSpace &cs,
-    const uint32_t *__restrict__ out_ids, uint32_t *__restrict__ raw_ext)
+    const uint32_t *__restrict__ out_ids, RawSamples raw)
 {
     constexpr int P = PL::P, L = PL::L, M = PL::M, N = PL::N, GPW = PL::GPW;
     const uint32_t l = LC ? (uint32_t)LC : l_arg;
@@ -224,9 +231,9 @@ __device__ __forceinline__ void rotate_by_wavefront(
     if (TRACK && round_err) atomicMax(round_err, __float_as_uint(worst));
 
     // sample extraction: a''_0 = A_0, a''_j = -A_{N-j}, b'' = B_0
-    if (live && raw_ext) {
+    if (live && raw.takes(g)) {
         // a rotation of a MUX: the sample itself is kept, two of them are summed before the key switch
-        uint32_t *dst = raw_ext + (size_t)g * (N + 1);
+        uint32_t *dst = raw.row(g, N);
         for (int j = t; j < N; j += L) dst[j] = (j == 0) ? acc[0][0] : 0u - acc[0][N - j];
         if (t == 0) dst[N] = acc[1][0];
     } else if (live) {
@@ -252,13 +259,13 @@ __global__ __launch_bounds__(64 * BR_WAVES, 2) void k_blind_rotate(
     const uint16_t *__restrict__ bar, uint32_t bar_stride, uint32_t n, uint32_t l, uint32_t bg_bit,
     const double2 *__restrict__ bk_hat, const double2 *__restrict__ tw_table, uint32_t ks_bits,
     uint32_t *__restrict__ ext_b, uint16_t *__restrict__ ksd, uint32_t gates, unsigned *round_err, CtSpace cs,
-    const uint32_t *__restrict__ out_ids, uint32_t *__restrict__ raw_ext)
+    const uint32_t *__restrict__ out_ids, RawSamples raw)
 {
     __shared__ uint32_t s_acc[BR_WAVES * PL::GPW][2][PL::N];
     __shared__ double2 s_xch[BR_WAVES * PL::GPW][PL::XSLOTS];
     __shared__ double2 s_tw[TwTable<PL>::COUNT];
     rotate_by_wavefront<PL, TRACK, LC>(s_acc, s_xch, s_tw, blockIdx.x, bar, bar_stride, n, l, bg_bit, bk_hat, tw_table,
-                                       ks_bits, ext_b, ksd, gates, round_err, cs, out_ids, raw_ext);
+                                       ks_bits, ext_b, ksd, gates, round_err, cs, out_ids, raw);
 }
 
 // ------------------------------------------------------------------------------------------
@@ -305,7 +312,7 @@ __device__ __forceinline__ void rotate_by_component(
     const uint16_t *__restrict__ bar, uint32_t bar_stride, uint32_t n, uint32_t l, uint32_t bg_bit,
     const double2 *__restrict__ bk_hat, const double2 *__restrict__ tw_table, uint32_t ks_bits,
     uint32_t *__restrict__ ext_b, uint16_t *__restrict__ ksd, uint32_t gates, unsigned *round_err, const CtSpace &cs,
-    const uint32_t *__restrict__ out_ids, uint32_t *__restrict__ raw_ext)
+    const uint32_t *__restrict__ out_ids, RawSamples raw)
 {
     constexpr int P = PL::P, L = PL::L, M = PL::M, N = PL::N;
     static_assert(PL::GPW == 1, "one transform per wavefront");
@@ -466,8 +473,8 @@ __device__ __forceinline__ void rotate_by_component(
 
     // sample extraction: wavefront 0 holds A (mask a''_0 = A_0, a''_j = -A_{N-j}), wavefront 1 holds B (body b'' = B_0)
     if (!live) return;
-    if (raw_ext) {
-        uint32_t *dst = raw_ext + (size_t)g * (N + 1);
+    if (raw.takes(g)) {
+        uint32_t *dst = raw.row(g, N);
         if (c == 0) {
             for (int j = t; j < N; j += L) dst[j] = (j == 0) ? acc[0] : 0u - acc[N - j];
         } else if (t == 0) {
@@ -495,11 +502,11 @@ __global__ __launch_bounds__(128 * GB, 2) void k_blind_rotate_split(
     const uint16_t *__restrict__ bar, uint32_t bar_stride, uint32_t n, uint32_t l, uint32_t bg_bit,
     const double2 *__restrict__ bk_hat, const double2 *__restrict__ tw_table, uint32_t ks_bits,
     uint32_t *__restrict__ ext_b, uint16_t *__restrict__ ksd, uint32_t gates, unsigned *round_err, CtSpace cs,
-    const uint32_t *__restrict__ out_ids, uint32_t *__restrict__ raw_ext)
+    const uint32_t *__restrict__ out_ids, RawSamples raw)
 {
     __shared__ SplitShared<PL, GB> sh;
     rotate_by_component<PL, TRACK, GB, LR>(sh, blockIdx.x * GB, bar, bar_stride, n, l, bg_bit, bk_hat, tw_table, ks_bits,
-                                           ext_b, ksd, gates, round_err, cs, out_ids, raw_ext);
+                                           ext_b, ksd, gates, round_err, cs, out_ids, raw);
 }
 
 // ------------------------------------------------------------------------------------------
@@ -536,7 +543,7 @@ __device__ __forceinline__ void rotate_by_quad(
     const uint16_t *__restrict__ bar, uint32_t bar_stride, uint32_t n, uint32_t bg_bit,
     const double2 *__restrict__ bk_hat, const double2 *__restrict__ half_table, uint32_t ks_bits,
     uint32_t *__restrict__ ext_b, uint16_t *__restrict__ ksd, unsigned *round_err, const CtSpace &cs,
-    const uint32_t *__restrict__ out_ids, uint32_t *__restrict__ raw_ext)
+    const uint32_t *__restrict__ out_ids, RawSamples raw)
 {
     using HP = HalfPlan;
     constexpr int N = HP::N, L = HP::L;
@@ -690,8 +697,8 @@ __device__ __forceinline__ void rotate_by_quad(
     // sample extraction by the whole workgroup: a''_0 = A_0, a''_j = -A_{N-j}, b'' = B_0
     lds_barrier();
     const uint32_t body = s_base[1][0] + dec_off;
-    if (raw_ext) {
-        uint32_t *dst = raw_ext + (size_t)g * (N + 1);
+    if (raw.takes(g)) {
+        uint32_t *dst = raw.row(g, N);
         for (int j = threadIdx.x; j < N; j += 256) dst[j] = (j == 0) ? s_base[0][0] + dec_off : 0u - (s_base[0][N - j] + dec_off);
         if (threadIdx.x == 0) dst[N] = body;
     } else {
@@ -714,11 +721,11 @@ __global__ __launch_bounds__(256, 2) void k_blind_rotate_quad(
     const uint16_t *__restrict__ bar, uint32_t bar_stride, uint32_t n, uint32_t bg_bit,
     const double2 *__restrict__ bk_hat, const double2 *__restrict__ half_table, uint32_t ks_bits,
     uint32_t *__restrict__ ext_b, uint16_t *__restrict__ ksd, unsigned *round_err, CtSpace cs,
-    const uint32_t *__restrict__ out_ids, uint32_t *__restrict__ raw_ext)
+    const uint32_t *__restrict__ out_ids, RawSamples raw)
 {
     __shared__ QuadShared sh;
     rotate_by_quad<TRACK, LR>(sh, blockIdx.x, bar, bar_stride, n, bg_bit, bk_hat, half_table, ks_bits, ext_b, ksd, round_err,
-                              cs, out_ids, raw_ext);
+                              cs, out_ids, raw);
 }
 
 // ------------------------------------------------------------------------------------------
@@ -784,7 +791,7 @@ __global__ __launch_bounds__(768, 3) void k_blind_rotate_wide(
     const uint16_t *__restrict__ bar, uint32_t bar_stride, uint32_t n, uint32_t bg_bit,
     const double2 *__restrict__ bk_hat, const double2 *__restrict__ half_table, uint32_t ks_bits,
     uint32_t *__restrict__ ext_b, uint16_t *__restrict__ ksd, uint32_t gates, unsigned *round_err, CtSpace cs,
-    const uint32_t *__restrict__ out_ids, uint32_t *__restrict__ raw_ext)
+    const uint32_t *__restrict__ out_ids, RawSamples raw)
 {
     using HP = HalfPlan;
     constexpr int N = HP::N, L = HP::L, LR = 3, THREADS = 768;
@@ -959,8 +966,8 @@ __global__ __launch_bounds__(768, 3) void k_blind_rotate_wide(
         return w[((((j >> 8) & 1) * 2 + (j >> 9)) * 64 + HalfLanes::position(j & 63)) * 4 + 2 * ((j >> 6) & 1) + ((j >> 7) & 1)] + dec_off;
     };
     const uint32_t body = word(1, 0);
-    if (raw_ext) {
-        uint32_t *dst = raw_ext + (size_t)g * (N + 1);
+    if (raw.takes(g)) {
+        uint32_t *dst = raw.row(g, N);
         for (int j = threadIdx.x; j < N; j += THREADS) dst[j] = (j == 0) ? word(0, 0) : 0u - word(0, N - j);
         if (threadIdx.x == 0) dst[N] = body;
     } else {
@@ -999,7 +1006,7 @@ __global__ __launch_bounds__(256, 2) void k_blind_rotate_mixed(
     const uint16_t *__restrict__ bar, uint32_t bar_stride, uint32_t n, uint32_t bg_bit,
     const double2 *__restrict__ bk_hat, const double2 *__restrict__ tw_table, const double2 *__restrict__ half_table,
     uint32_t ks_bits, uint32_t *__restrict__ ext_b, uint16_t *__restrict__ ksd, uint32_t gates, MixedBlocks blocks,
-    unsigned *round_err, CtSpace cs, const uint32_t *__restrict__ out_ids, uint32_t *__restrict__ raw_ext)
+    unsigned *round_err, CtSpace cs, const uint32_t *__restrict__ out_ids, RawSamples raw)
 {
     using PL = Plan<3, 3>;
     static_assert(PL::N == HalfPlan::N && PL::GPW == 1 && BR_WAVES == 4, "all forms on 256 threads at the same ring degree");
@@ -1007,13 +1014,13 @@ __global__ __launch_bounds__(256, 2) void k_blind_rotate_mixed(
     const uint32_t first_pair = blocks.waves * BR_WAVES, first_quad = gates - blocks.quads, b = blockIdx.x;
     if (b < blocks.waves)
         rotate_by_wavefront<PL, TRACK, LR>(sh.wave.acc, sh.wave.xch, sh.wave.tw, b, bar, bar_stride, n, LR, bg_bit, bk_hat,
-                                           tw_table, ks_bits, ext_b, ksd, first_pair, round_err, cs, out_ids, raw_ext);
+                                           tw_table, ks_bits, ext_b, ksd, first_pair, round_err, cs, out_ids, raw);
     else if (PAIRS && b < blocks.waves + blocks.pairs)
         rotate_by_component<PL, TRACK, 2, LR>(sh.pair, first_pair + 2 * (b - blocks.waves), bar, bar_stride, n, LR, bg_bit,
-                                              bk_hat, tw_table, ks_bits, ext_b, ksd, first_quad, round_err, cs, out_ids, raw_ext);
+                                              bk_hat, tw_table, ks_bits, ext_b, ksd, first_quad, round_err, cs, out_ids, raw);
     else
         rotate_by_quad<TRACK, LR>(sh.quad, first_quad + (b - blocks.waves - blocks.pairs), bar, bar_stride, n, bg_bit, bk_hat,
-                                  half_table, ks_bits, ext_b, ksd, round_err, cs, out_ids, raw_ext);
+                                  half_table, ks_bits, ext_b, ksd, round_err, cs, out_ids, raw);
 }
 
 // Second half of a native MUX: the two rotations' samples are added, 1/8 goes on the body, and the
@@ -1021,10 +1028,10 @@ __global__ __launch_bounds__(256, 2) void k_blind_rotate_mixed(
 __global__ __launch_bounds__(256) void k_mux_combine(const uint32_t *__restrict__ raw_ext, uint32_t N, uint32_t n,
                                                      uint32_t ks_bits, uint32_t *__restrict__ ext_b,
                                                      uint16_t *__restrict__ ksd, CtSpace cs,
-                                                     const uint32_t *__restrict__ out_ids)
+                                                     const uint32_t *__restrict__ out_ids, uint32_t first)
 {
-    const uint32_t g = blockIdx.x;
-    const uint32_t *e1 = raw_ext + (size_t)(2 * g) * (N + 1), *e0 = e1 + (N + 1);
+    const uint32_t *e1 = raw_ext + (size_t)(2 * blockIdx.x) * (N + 1), *e0 = e1 + (N + 1);
+    const uint32_t g = first + blockIdx.x;                       // its place in the level, behind the `first` gates
     const uint32_t rnd = 1u << (31 - ks_bits), sh = 32 - ks_bits;
     uint16_t *dst = ksd + ((size_t)(g / KS_GROUP) * N) * KS_GROUP + (g % KS_GROUP);
     for (uint32_t j = threadIdx.x; j < N; j += blockDim.x)
@@ -1929,7 +1936,7 @@ hipError_t launch_lincomb(const she_params &P, const CtSpace &cs, const uint8_t 
 template <class PL>
 static hipError_t blind_rotate_t(const she_params &P, const DeviceKeys &K, size_t gates, const LevelWork &W,
                                  unsigned *d_round_err, const CtSpace &cs, const uint32_t *d_out, hipStream_t st,
-                                 uint32_t *raw_ext, size_t split_below)
+                                 RawSamples raw, size_t split_below)
 {
     const uint32_t ks_bits = P.ks_t * P.ks_basebit;
     const bool split = gates <= split_below;
@@ -1941,7 +1948,7 @@ static hipError_t blind_rotate_t(const she_params &P, const DeviceKeys &K, size_
 #define SHE_LAUNCH_MIXED(TRACK, PAIRS)                                                                                \
     hipLaunchKernelGGL((k_blind_rotate_mixed<TRACK, 3, PAIRS>), grid, dim3(64 * BR_WAVES), 0, st, W.bar, W.bar_stride, \
                        P.n, P.bg_bit, K.bk_hat, K.twiddles, K.half_twiddles, ks_bits, W.ext_b, W.ksd, (uint32_t)gates, \
-                       blocks, d_round_err, cs, d_out, raw_ext)
+                       blocks, d_round_err, cs, d_out, raw)
             if (blocks.pairs) { if (d_round_err) SHE_LAUNCH_MIXED(true, true); else SHE_LAUNCH_MIXED(false, true); }
             else if (d_round_err) SHE_LAUNCH_MIXED(true, false);
             else SHE_LAUNCH_MIXED(false, false);
@@ -1953,7 +1960,7 @@ static hipError_t blind_rotate_t(const she_params &P, const DeviceKeys &K, size_
 #define SHE_LAUNCH_WIDE(TRACK)                                                                                        \
     hipLaunchKernelGGL((k_blind_rotate_wide<TRACK>), dim3(K.cus), dim3(768), 0, st, W.bar, W.bar_stride, P.n,         \
                        P.bg_bit, K.bk_hat, K.half_twiddles, ks_bits, W.ext_b, W.ksd, (uint32_t)gates, d_round_err,    \
-                       cs, d_out, raw_ext)
+                       cs, d_out, raw)
             if (d_round_err) SHE_LAUNCH_WIDE(true); else SHE_LAUNCH_WIDE(false);
 #undef SHE_LAUNCH_WIDE
             return hipGetLastError();
@@ -1962,7 +1969,7 @@ static hipError_t blind_rotate_t(const she_params &P, const DeviceKeys &K, size_
         if (split && P.l == 3 && gates <= 2 * (size_t)K.cus) {
 #define SHE_LAUNCH_QUAD(TRACK)                                                                                        \
     hipLaunchKernelGGL((k_blind_rotate_quad<TRACK, 3>), dim3((unsigned)gates), dim3(256), 0, st, W.bar, W.bar_stride, \
-                       P.n, P.bg_bit, K.bk_hat, K.half_twiddles, ks_bits, W.ext_b, W.ksd, d_round_err, cs, d_out, raw_ext)
+                       P.n, P.bg_bit, K.bk_hat, K.half_twiddles, ks_bits, W.ext_b, W.ksd, d_round_err, cs, d_out, raw)
             if (d_round_err) SHE_LAUNCH_QUAD(true); else SHE_LAUNCH_QUAD(false);
 #undef SHE_LAUNCH_QUAD
             return hipGetLastError();
@@ -1987,7 +1994,7 @@ static hipError_t blind_rotate_t(const she_params &P, const DeviceKeys &K, size_
 #define SHE_LAUNCH_SPLIT(TRACK, GB, LR)                                                                               \
     hipLaunchKernelGGL((k_blind_rotate_split<PL, TRACK, GB, LR>), grid, block, 0, st, W.bar, W.bar_stride, P.n, P.l,  \
                        P.bg_bit, K.bk_hat, K.twiddles, ks_bits, W.ext_b, W.ksd, (uint32_t)gates, d_round_err, cs,     \
-                       d_out, raw_ext)
+                       d_out, raw)
         if (triple) {
             if constexpr (quads) {
                 if (d_round_err) SHE_LAUNCH_SPLIT(true, 1, 3); else SHE_LAUNCH_SPLIT(false, 1, 3);
@@ -2004,27 +2011,27 @@ static hipError_t blind_rotate_t(const she_params &P, const DeviceKeys &K, size_
     const dim3 grid((unsigned)((gates + per_block - 1) / per_block)), block(64 * BR_WAVES);
     if (d_round_err)
         hipLaunchKernelGGL((k_blind_rotate<PL, true, 0>), grid, block, 0, st, W.bar, W.bar_stride, P.n, P.l, P.bg_bit,
-                           K.bk_hat, K.twiddles, ks_bits, W.ext_b, W.ksd, (uint32_t)gates, d_round_err, cs, d_out, raw_ext);
+                           K.bk_hat, K.twiddles, ks_bits, W.ext_b, W.ksd, (uint32_t)gates, d_round_err, cs, d_out, raw);
     else if (P.l == 3)
         hipLaunchKernelGGL((k_blind_rotate<PL, false, 3>), grid, block, 0, st, W.bar, W.bar_stride, P.n, P.l, P.bg_bit,
-                           K.bk_hat, K.twiddles, ks_bits, W.ext_b, W.ksd, (uint32_t)gates, d_round_err, cs, d_out, raw_ext);
+                           K.bk_hat, K.twiddles, ks_bits, W.ext_b, W.ksd, (uint32_t)gates, d_round_err, cs, d_out, raw);
     else
         hipLaunchKernelGGL((k_blind_rotate<PL, false, 0>), grid, block, 0, st, W.bar, W.bar_stride, P.n, P.l, P.bg_bit,
-                           K.bk_hat, K.twiddles, ks_bits, W.ext_b, W.ksd, (uint32_t)gates, d_round_err, cs, d_out, raw_ext);
+                           K.bk_hat, K.twiddles, ks_bits, W.ext_b, W.ksd, (uint32_t)gates, d_round_err, cs, d_out, raw);
     return hipGetLastError();
 }
 
 hipError_t launch_blind_rotate(const she_params &P, const DeviceKeys &K, const CtSpace &cs, const uint32_t *d_out,
-                               size_t gates, const LevelWork &W, unsigned *d_round_err, hipStream_t st, bool raw,
+                               size_t gates, const LevelWork &W, unsigned *d_round_err, hipStream_t st, bool mux,
                                size_t split_below)
 {
     if (!gates) return hipSuccess;
     if (!K.ks_bytes) d_out = nullptr;      // the generic key switch writes the slot itself
-    uint32_t *raw_ext = raw ? W.raw_ext : nullptr;
+    const RawSamples raw{mux ? W.raw_ext : nullptr, (uint32_t)W.direct};
     switch (P.N) {
-    case 256: return blind_rotate_t<Plan256>(P, K, gates, W, d_round_err, cs, d_out, st, raw_ext, split_below);
-    case 512: return blind_rotate_t<Plan512>(P, K, gates, W, d_round_err, cs, d_out, st, raw_ext, split_below);
-    case 1024: return blind_rotate_t<Plan1024>(P, K, gates, W, d_round_err, cs, d_out, st, raw_ext, split_below);
+    case 256: return blind_rotate_t<Plan256>(P, K, gates, W, d_round_err, cs, d_out, st, raw, split_below);
+    case 512: return blind_rotate_t<Plan512>(P, K, gates, W, d_round_err, cs, d_out, st, raw, split_below);
+    case 1024: return blind_rotate_t<Plan1024>(P, K, gates, W, d_round_err, cs, d_out, st, raw, split_below);
     }
     return hipErrorInvalidValue;
 }
@@ -2034,7 +2041,7 @@ hipError_t launch_mux_combine(const she_params &P, const DeviceKeys &K, const Ct
 {
     if (!muxes) return hipSuccess;
     hipLaunchKernelGGL(k_mux_combine, dim3((unsigned)muxes), dim3(256), 0, st, W.raw_ext, P.N, P.n,
-                       P.ks_t * P.ks_basebit, W.ext_b, W.ksd, cs, K.ks_bytes ? d_out : nullptr);
+                       P.ks_t * P.ks_basebit, W.ext_b, W.ksd, cs, K.ks_bytes ? d_out : nullptr, (uint32_t)W.direct);
     return hipGetLastError();
 }
 
