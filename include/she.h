@@ -177,7 +177,7 @@ int she_relu_maxpool(she_ctx *ctx, const uint32_t *x_ids, uint32_t H, uint32_t W
  * Section 3.1 (gates that do not depend on each other can be evaluated together).  Between she_defer_begin and
  * she_defer_run the layer operators (she_shift_acc, she_shift_acc_bias, she_relu, she_maxpool, she_relu_maxpool) only
  * record their netlists: an operator that reads a slot which a recorded operator writes is wired to that operator's
- * result.  she_defer_run then schedules ALL recorded entries at their earliest depth level and evaluates each level as
+ * result.  she_defer_run then schedules ALL recorded entries in as many levels as they are deep and evaluates each level as
  * one batch, so the last carries of a layer's adders run beside the first comparator stages of the pooling that
  * follows, instead of one operator after the other; every recorded output still lands in its pool slot.  The results
  * are the ciphertexts that the same calls give one by one (identical words without SHE_OPT_FOLD_CONSTANTS; with it
@@ -198,7 +198,7 @@ int she_defer_run(she_ctx *ctx, uint64_t *entries_out);
  * SHE_WIRE_ONE for the noiseless trivial ciphertexts, each optionally with SHE_WIRE_NOT (the complement, a free
  * word-wise negation; accepted only under SHE_OPT_FOLD_CONSTANTS, which absorbs it into the gate codes).
  * Codes: the ten 2-input codes, SHE_MAJ3 + mask, SHE_XOR3 + mask, and SHE_CIRCUIT_MUX (in0 ? in1 : in2, three gates
- * or one native entry under SHE_OPT_NATIVE_MUX).  The library schedules every entry at its earliest depth level,
+ * or one native entry under SHE_OPT_NATIVE_MUX).  The library schedules the entries in as many levels as the circuit is deep,
  * evaluates each level as one batch (as she_eval_gates / she_eval_gates3 / she_eval_mux do), keeps intermediate
  * results in its own temporaries, and leaves the results named by out_refs[0..nout) in the pool slots out_ids;
  * the options fold entries exactly as they do inside the layer operators.  out_ids must be distinct and disjoint

@@ -239,16 +239,27 @@ int run_netlist(she_ctx *c, Netlist &nl, const std::vector<uint32_t> &out_wires,
                 uint64_t *gates_out)
 {
     if (nl.overflow) return fail(c, SHE_ERANGE, "netlist too large for 31-bit wire ids");
-    std::vector<size_t> mux_start;
-    const std::vector<size_t> bounds = nl.levelize(&mux_start);
-    nl.bind_outputs(out_wires, out_ids);
-    const size_t G = nl.type.size(), levels = bounds.size() - 1;
+    const size_t G = nl.type.size();
     if (gates_out) *gates_out = G;
-    // temporaries share slots by lifetime: the buffer holds the widest set of live wires, not one slot per entry
-    const size_t temp_slots = nl.compact_temporaries(bounds);
-    if (!temp_slots) return fail(c, SHE_EDEVICE, "internal error: a temporary lost its slot while it was live");
-    int rc = ensure_temp(c, temp_slots);
+    std::vector<size_t> mux_start, bounds;
+    // The levels are evened out where level_time knows their kernels; what waits may keep more wires alive, and where there is
+    // no memory for them the entries run as early as they can.
+    const bool even = c->P.N == 1024 && c->P.l == 3 && c->split_below >= 6 * (size_t)c->dk.cus;
+    Netlist earliest(0);
+    if (even) earliest = nl;
+    int rc = SHE_OK;
+    for (uint32_t cus = even ? c->dk.cus : 0;; cus = 0) {
+        bounds = nl.levelize(&mux_start, cus);
+        nl.bind_outputs(out_wires, out_ids);
+        // temporaries share slots by lifetime: the buffer holds the widest set of live wires, not one slot per entry
+        const size_t temp_slots = nl.compact_temporaries(bounds);
+        if (!temp_slots) return fail(c, SHE_EDEVICE, "internal error: a temporary lost its slot while it was live");
+        rc = ensure_temp(c, temp_slots);
+        if (rc != SHE_ENOMEM || !cus) break;
+        nl = earliest;
+    }
     if (rc) return rc;
+    const size_t levels = bounds.size() - 1;
     // the jobs of a level: its gates, then two rotations for every MUX entry
     std::vector<size_t> job_first(levels + 1, 0);
     size_t widest = 0, most_gates = 0, most_muxes = 0;

@@ -188,6 +188,11 @@ constexpr int MUX_BASE = SHE_NUM_GATES;       // netlist type of a native MUX en
 inline bool is_mux_type(uint8_t t) { return t >= MUX_BASE && t < SHE_MAJ3; }
 inline bool has_third_operand(uint8_t t) { return t >= MUX_BASE; }     // MUX entries and three-input gates
 
+// Estimated time of a level, in microseconds at N = 1024 and l = 3, from its rotations per compute unit: the steps of the
+// kernels that launch_blind_rotate chooses, as measured at n = 630 on 256 compute units (a level of 256 / 512 / 768 / 1024 /
+// 1536 / 2048 rotations takes 1.85 / 3.5 / 4.05 / 5.85 / 7.65 / 10.35 ms, one rotation more 3.35 / 3.95 / 5.5 / 6.1 / 10.0 /
+// 11.9), with 0.1 ms for its other kernels.  Only ratios count, so that other key lengths are served as well.
+double level_time(uint64_t rotations, uint32_t cus);
 struct Netlist {
     // wire ids: [0, cap) pool slots, cap = trivial 0, cap+1 = trivial 1, cap+2.. temporaries.
     // With `fold` set, a gate fixed by constant or repeated operands is not emitted: gate()
@@ -220,8 +225,12 @@ struct Netlist {
     // anything else (inputs, constants, a wire used twice) is copied at the end
     void bind_outputs(const std::vector<uint32_t> &wires, const uint32_t *dst);
     // stable sort of the entries by (depth, gates before MUX entries); returns the first index of each
-    // level (+ end); mux_start[lv] receives the index of level lv's first MUX entry
-    std::vector<size_t> levelize(std::vector<size_t> *mux_start = nullptr);
+    // level (+ end); mux_start[lv] receives the index of level lv's first MUX entry.  With cus > 0 the levels, no more of them,
+    // are evened out for a device of that many compute units: see even_levels.
+    std::vector<size_t> levelize(std::vector<size_t> *mux_start = nullptr, uint32_t cus = 0);
+    // Moves entries that later levels have time for out of levels that they only just push over a step of level_time.
+    // `lev`: the earliest level of every entry, 1 .. deepest, the entries still in topological order.
+    void even_levels(std::vector<uint32_t> &lev, uint32_t deepest, uint32_t cus) const;
     // after levelize and bind_outputs: re-numbers the remaining temporaries so that slots are reused once their last
     // reader's level has run; `bounds` are levelize's.  Returns the slots needed (constants included), 0 on an
     // internal inconsistency.
