@@ -1680,11 +1680,11 @@ __global__ void k_copy_ct(CtSpace cs, const uint32_t *__restrict__ src_ids, cons
 // ------------------------------------------------------------------------------------------
 // Client side: fresh encryptions and phases of samples in the pool, one wavefront per sample.  The random words of a
 // sample's stream are addressed (she_host.cpp has the definition), so every lane makes its own.  Bound by the pool's
-// memory and the call itself (48 and 41 us for 6272 samples of n = 630, the key bits uploaded with each call and cleared
+// memory and the call itself (42 and 37 us for 6272 samples of n = 630, the key bits uploaded with each call and cleared
 // again at its end, 2 to 3 us of that); on the host's threads, with the pool filled from and read into a staged copy, 1.4
 // and 1.5 ms.
 // ------------------------------------------------------------------------------------------
-constexpr int CLIENT_WAVES = 4;
+constexpr int FRESH_WAVES = 7, PHASE_WAVES = 4, KEY_BATCH = 10;      // ten words per lane: a whole sample at n = 630
 
 __device__ __forceinline__ uint64_t stream_mix(uint64_t z)
 {
@@ -1692,7 +1692,8 @@ __device__ __forceinline__ uint64_t stream_mix(uint64_t z)
     z = (z ^ (z >> 27)) * 0x94D049BB133111EBull;
     return z ^ (z >> 31);
 }
-__device__ __forceinline__ uint64_t stream_word(uint64_t key, uint64_t c) { return stream_mix(key + (c + 1) * 0x9E3779B97F4A7C15ull); }
+constexpr uint64_t STREAM_STEP = 0x9E3779B97F4A7C15ull;
+__device__ __forceinline__ uint64_t stream_word(uint64_t key, uint64_t c) { return stream_mix(key + (c + 1) * STREAM_STEP); }
 
 // sum over the wavefront's lanes
 __device__ __forceinline__ uint32_t wave_sum(uint32_t v)
@@ -1702,55 +1703,90 @@ __device__ __forceinline__ uint32_t wave_sum(uint32_t v)
     return v;
 }
 
+// Seven wavefronts make the mask and its sum of a sample each while the eighth computes the seven errors, a logarithm and a
+// cosine in 64 bits, on a lane each; the key's bits are requested side by side.  Bound by the random words, three 32-bit
+// multiplications and two more for every one, and by the launch.  Calls for 100 / 1000 / 2500 / 6272 bits: 29.6 / 30.0 / 33.3
+// / 41.5 us; with the errors on the first lane of every sample's own wavefront, and the key bits one after the other, 32.1 /
+// 32.8 / 35.8 / 45.7; with 3, 11 or 15 samples a workgroup up to 1 us more.
 // The error is computed as she_host.cpp computes it, with this card's log and cos.  Both sides' functions are accurate to
 // a few units in the last place, so that the unrounded values differ by less than 2^-48 of their size: where the value is
 // further than 2^-44 of its size (and 2^-40) from halfway between two integers, both round to the same one.  Where it is
 // not, the sample's number goes into `retry` (its first word counts them), no error is added, and the host adds its own.
-__global__ __launch_bounds__(64 * CLIENT_WAVES) void k_fresh_samples(CtSpace cs, const uint32_t *__restrict__ ids,
-                                                                     const uint8_t *__restrict__ bits,
-                                                                     const uint8_t *__restrict__ lwe_key, uint32_t n,
-                                                                     uint64_t stream_base, double sigma, uint32_t count,
-                                                                     uint32_t *retry_count, uint32_t *__restrict__ retry)
+__global__ __launch_bounds__(64 * (FRESH_WAVES + 1)) void k_fresh_samples(CtSpace cs, const uint32_t *__restrict__ ids,
+                                                                          const uint8_t *__restrict__ bits,
+                                                                          const uint8_t *__restrict__ lwe_key, uint32_t n,
+                                                                          uint64_t stream_base, double sigma, uint32_t count,
+                                                                          uint32_t *retry_count, uint32_t *__restrict__ retry)
 {
 #pragma clang fp contract(off)
-    const uint32_t k = blockIdx.x * CLIENT_WAVES + (threadIdx.x >> 6), lane = threadIdx.x & 63;
-    if (k >= count) return;
-    const uint64_t key = stream_mix(stream_base + k);
-    uint32_t *dst = ct_ptr(cs, ids[k]);
-    uint32_t sum = 0;
-    for (uint32_t i = lane; i < n; i += 64) {
-        const uint32_t a = (uint32_t)(stream_word(key, i) >> 32);
-        dst[i] = a;
-        sum += lwe_key[i] ? a : 0u;
+    __shared__ uint32_t s_sum[FRESH_WAVES];
+    const uint32_t wave = threadIdx.x >> 6, lane = threadIdx.x & 63, first = blockIdx.x * FRESH_WAVES;
+    const uint32_t k = first + (wave < FRESH_WAVES ? wave : lane);
+    const bool live = k < count && (wave < FRESH_WAVES || lane < FRESH_WAVES);
+    uint32_t body = 0;
+    if (live && wave < FRESH_WAVES) {
+        const uint64_t key = stream_mix(stream_base + k);
+        uint32_t *dst = ct_ptr(cs, ids[k]);
+        uint32_t sum = 0;
+        for (uint32_t i0 = lane; i0 < n; i0 += 64 * KEY_BATCH) {
+            uint32_t bit[KEY_BATCH];
+#pragma unroll
+            for (int q = 0; q < KEY_BATCH; q++) bit[q] = lwe_key[std::min(i0 + 64 * q, n - 1)];
+            uint64_t at = key + (uint64_t)(i0 + 1) * STREAM_STEP;                  // stream_word's argument, one addition a word
+#pragma unroll
+            for (int q = 0; q < KEY_BATCH; q++, at += 64 * STREAM_STEP) {
+                const uint32_t i = i0 + 64 * q;
+                if (i < n) {
+                    const uint32_t a = (uint32_t)(stream_mix(at) >> 32);
+                    dst[i] = a;
+                    sum += bit[q] ? a : 0u;
+                }
+            }
+        }
+        sum = wave_sum(sum);
+        if (lane == 0) s_sum[wave] = sum;
+    } else if (live) {
+        const uint64_t key = stream_mix(stream_base + k);
+        const double unit = 1.0 / 9007199254740992.0;                         // 2^-53
+        const double u1 = (double)((stream_word(key, n) >> 11) + 1) * unit;
+        const double u2 = (double)(stream_word(key, (uint64_t)n + 1) >> 11) * unit;
+        const double radius = sqrt(-2.0 * log(u1));
+        const double normal = radius * cos(6.283185307179586476925286766559 * u2);
+        const double scaled = normal * sigma * 4294967296.0, rounded = rint(scaled);
+        const double to_half = 0.5 - fabs(scaled - rounded);
+        body = (bits[k] ? (1u << 29) : 0u - (1u << 29)) + (uint32_t)(int64_t)rounded;
+        if (!(to_half > fabs(scaled) * 0x1p-44 + 0x1p-40)) {
+            retry[atomicAdd(retry_count, 1u)] = k;
+            body = bits[k] ? (1u << 29) : 0u - (1u << 29);
+        }
     }
-    sum = wave_sum(sum);
-    if (lane) return;
-    const double unit = 1.0 / 9007199254740992.0;                             // 2^-53
-    const double u1 = (double)((stream_word(key, n) >> 11) + 1) * unit;
-    const double u2 = (double)(stream_word(key, (uint64_t)n + 1) >> 11) * unit;
-    const double radius = sqrt(-2.0 * log(u1));
-    const double normal = radius * cos(6.283185307179586476925286766559 * u2);
-    const double scaled = normal * sigma * 4294967296.0, rounded = rint(scaled);
-    const double to_half = 0.5 - fabs(scaled - rounded);
-    uint32_t error = (uint32_t)(int64_t)rounded;
-    if (!(to_half > fabs(scaled) * 0x1p-44 + 0x1p-40)) {
-        retry[atomicAdd(retry_count, 1u)] = k;
-        error = 0;
-    }
-    dst[n] = (bits[k] ? (1u << 29) : 0u - (1u << 29)) + sum + error;
+    __syncthreads();
+    if (live && wave == FRESH_WAVES) ct_ptr(cs, ids[k])[n] = body + s_sum[lane];
 }
 
-__global__ __launch_bounds__(64 * CLIENT_WAVES) void k_phase_bits(CtSpace cs, const uint32_t *__restrict__ ids,
-                                                                  const uint8_t *__restrict__ lwe_key, uint32_t n,
-                                                                  uint32_t count, uint8_t *__restrict__ bits)
+// A lane's words and key bits are requested side by side, not one after the other: calls for 100 / 2500 / 6272 bits
+// 29.6 / 30.5 / 36.8 us against 31.7 / 32.4 / 38.6 (3.0 / 3.3 / 5.8 in the kernel against 5.4 / 5.6 / 9.1).
+__global__ __launch_bounds__(64 * PHASE_WAVES) void k_phase_bits(CtSpace cs, const uint32_t *__restrict__ ids,
+                                                                 const uint8_t *__restrict__ lwe_key, uint32_t n,
+                                                                 uint32_t count, uint8_t *__restrict__ bits)
 {
-    const uint32_t k = blockIdx.x * CLIENT_WAVES + (threadIdx.x >> 6), lane = threadIdx.x & 63;
+    const uint32_t k = blockIdx.x * PHASE_WAVES + (threadIdx.x >> 6), lane = threadIdx.x & 63;
     if (k >= count) return;
     const uint32_t *ct = ct_ptr(cs, ids[k]);
+    const uint32_t body = ct[n];
     uint32_t sum = 0;
-    for (uint32_t i = lane; i < n; i += 64) sum += lwe_key[i] ? ct[i] : 0u;
+    for (uint32_t i0 = lane; i0 < n; i0 += 64 * KEY_BATCH) {
+        uint32_t word[KEY_BATCH], bit[KEY_BATCH];
+#pragma unroll
+        for (int q = 0; q < KEY_BATCH; q++) {
+            const uint32_t i = std::min(i0 + 64 * q, n - 1);                   // past the end: the last word, not added
+            word[q] = ct[i]; bit[q] = lwe_key[i];
+        }
+#pragma unroll
+        for (int q = 0; q < KEY_BATCH; q++) sum += bit[q] && i0 + 64 * q < n ? word[q] : 0u;
+    }
     sum = wave_sum(sum);
-    if (lane == 0) bits[k] = (int32_t)(ct[n] - sum) > 0;
+    if (lane == 0) bits[k] = (int32_t)(body - sum) > 0;
 }
 
 // The words of the staging buffer that held the key's bits and plaintext bits, cleared at the end of a client call.  The
@@ -2070,7 +2106,7 @@ hipError_t launch_fresh_samples(const CtSpace &cs, const uint32_t *d_ids, const 
                                 uint32_t *d_retry, hipStream_t st)
 {
     if (!count) return hipSuccess;
-    hipLaunchKernelGGL(k_fresh_samples, dim3((unsigned)((count + CLIENT_WAVES - 1) / CLIENT_WAVES)), dim3(64 * CLIENT_WAVES),
+    hipLaunchKernelGGL(k_fresh_samples, dim3((unsigned)((count + FRESH_WAVES - 1) / FRESH_WAVES)), dim3(64 * (FRESH_WAVES + 1)),
                        0, st, cs, d_ids, d_bits, d_key, n, stream_base, sigma, (uint32_t)count, d_retry_count, d_retry);
     return hipGetLastError();
 }
@@ -2078,7 +2114,7 @@ hipError_t launch_phase_bits(const CtSpace &cs, const uint32_t *d_ids, const uin
                              uint8_t *d_bits, hipStream_t st)
 {
     if (!count) return hipSuccess;
-    hipLaunchKernelGGL(k_phase_bits, dim3((unsigned)((count + CLIENT_WAVES - 1) / CLIENT_WAVES)), dim3(64 * CLIENT_WAVES), 0,
+    hipLaunchKernelGGL(k_phase_bits, dim3((unsigned)((count + PHASE_WAVES - 1) / PHASE_WAVES)), dim3(64 * PHASE_WAVES), 0,
                        st, cs, d_ids, d_key, n, (uint32_t)count, d_bits);
     return hipGetLastError();
 }
