@@ -801,6 +801,7 @@ __global__ __launch_bounds__(768, 3) void k_blind_rotate_wide(
         read_ahead(bk_hat, (size_t)n * 2 * LR * 2 * HP::M, g - gates, gridDim.x - gates);
         return;
     }
+    uint32_t *const raw_row = raw.takes(g) ? raw.row(g, N) : nullptr;         // (decided at the end: + 0.5 % for one gate)
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), t = threadIdx.x & 63;
     const int p = wave >> 2, c = (wave >> 1) & 1, h = wave & 1;
     HalfLanes hl;
@@ -966,8 +967,8 @@ __global__ __launch_bounds__(768, 3) void k_blind_rotate_wide(
         return w[((((j >> 8) & 1) * 2 + (j >> 9)) * 64 + HalfLanes::position(j & 63)) * 4 + 2 * ((j >> 6) & 1) + ((j >> 7) & 1)] + dec_off;
     };
     const uint32_t body = word(1, 0);
-    if (raw.takes(g)) {
-        uint32_t *dst = raw.row(g, N);
+    if (raw_row) {
+        uint32_t *dst = raw_row;
         for (int j = threadIdx.x; j < N; j += THREADS) dst[j] = (j == 0) ? word(0, 0) : 0u - word(0, N - j);
         if (threadIdx.x == 0) dst[N] = body;
     } else {
