@@ -1664,6 +1664,100 @@ __global__ __launch_bounds__(64 * KSM_WAVES, 3) void k_key_switch_mfma(CtSpace c
     }
 }
 
+// The same for a few gates, one workgroup of them, and at most KSF_STEPS coefficients a workgroup.  Such a level is bound by
+// how much of the key is under way: k_key_switch_mfma has one step's 4 KiB per workgroup, waits for them 0.4 to 0.8 us a step,
+// and cannot have more, since a wait for its digits is a wait for everything.  Here all digits are in LDS before the first step
+// and three steps' bytes are under way; wavefronts without a gate only bring their plane.  us by HIP events at n = 630 for 1 /
+// 31 / 64 / 83 / 130 / 200 / 256 gates: 27 / 32 / 38 / 38 / 38 / 38.5 / 39 -> 17.7 / 22.4 / 28 / 30.5 / 33.5 / 36.5 / 37.5 to 41:
+// what is left grows with the sums that 32 splits add atomically.  (Half as many splits 24 / 29 / 34 / 38 / 39 / 40 / 41, seven
+// steps under way 21 / 26 / 31.5 / 35 / 38 / 41 / 43.)  So it has the levels of up to KSF_GATES.
+constexpr int KSF_STEPS = 32, KSF_GATES = 192;
+__global__ __launch_bounds__(64 * KSM_WAVES, 3) void k_key_switch_few(CtSpace cs, const int8_t *__restrict__ ksb,
+                                                                    uint32_t cols_p, const uint16_t *__restrict__ ksd,
+                                                                    const uint32_t *__restrict__ out_ids, uint32_t N,
+                                                                    uint32_t n, uint32_t gates, uint32_t i_per_block)
+{
+    constexpr int GROUPS = KSF_GATES / KS_GROUP;
+    static_assert(KSF_GATES <= 32 * KSM_WAVES * KSM_TILES && KSF_GATES % (32 * KSM_TILES) == 0, "whole wavefronts of gates");
+    __shared__ uint4 s_b0[4 * 64], s_b1[4 * 64], s_b2[4 * 64], s_b3[4 * 64];     // [plane][lane], one array per stage
+    __shared__ uint4 s_digits[GROUPS][KSF_STEPS * KS_GROUP / 8];
+    const uint32_t wave = threadIdx.x >> 6, lane = threadIdx.x & 63, half = lane >> 5, c32 = lane & 31;
+    const uint32_t tile0 = wave * KSM_TILES, col = blockIdx.x * 32 + c32;
+    const uint32_t i0 = blockIdx.y * i_per_block, i1 = i0 + i_per_block;
+
+    // the digits of all gates for these coefficients
+    const uint32_t words = i_per_block * KS_GROUP / 8, live_groups = (gates + KS_GROUP - 1) / KS_GROUP;
+    for (uint32_t e = threadIdx.x; e < live_groups * words; e += 64 * KSM_WAVES) {
+        const uint32_t grp = e / words, w = e % words;
+        s_digits[grp][w] = reinterpret_cast<const uint4 *>(ksd + ((size_t)grp * N + i0) * KS_GROUP)[w];
+    }
+    __syncthreads();
+
+    v16i acc[KSM_TILES][4];
+#pragma unroll
+    for (int t = 0; t < KSM_TILES; t++)
+#pragma unroll
+        for (int p = 0; p < 4; p++)
+#pragma unroll
+            for (int r = 0; r < 16; r++) acc[t][p][r] = 0;
+    const uint4 *mine = reinterpret_cast<const uint4 *>(ksb + ((size_t)wave * cols_p + col) * 32 + 16 * half);
+    const size_t step_u4 = (size_t)4 * cols_p * 2;                          // one i further, in 16-byte units
+    const uint32_t ysh = 8 * (1 - half);
+    const bool live = tile0 * KS_GROUP < gates;                             // the same for the wavefront
+    auto fetch = [&](uint32_t i, uint4 *stage) { load_to_lds16(mine + (size_t)min(i, i1 - 1) * step_u4, stage + wave * 64); };
+
+    auto step = [&](uint32_t i, const uint4 *cur, uint4 *free_stage) {
+        // this step's bytes have landed, those of the two steps behind it may be on their way; nobody reads the free stage
+        __builtin_amdgcn_s_waitcnt(0x0F72);                                 // vmcnt(2)
+        __builtin_amdgcn_s_barrier();
+        fetch(i + 3, free_stage);                                           // past the end: the last step again, unused
+        __builtin_amdgcn_sched_barrier(0);
+        if (live) {
+            v4i b[4];
+#pragma unroll
+            for (int p = 0; p < 4; p++) {
+                const uint4 w = cur[p * 64 + lane];
+                b[p] = v4i{(int)w.x, (int)w.y, (int)w.z, (int)w.w};
+            }
+#pragma unroll
+            for (int t = 0; t < KSM_TILES; t++) {
+                const uint32_t yv = reinterpret_cast<const uint16_t *>(s_digits[tile0 + t])[(i - i0) * KS_GROUP + c32];
+                const uint32_t y = (yv >> ysh) & 0xffu;                     // this half's four digits
+                v4i a;
+                a.x = onehot_byte((y >> 6) & 3);
+                a.y = onehot_byte((y >> 4) & 3);
+                a.z = onehot_byte((y >> 2) & 3);
+                a.w = onehot_byte(y & 3);
+#pragma unroll
+                for (int p = 0; p < 4; p++) acc[t][p] = __builtin_amdgcn_mfma_i32_32x32x32_i8(a, b[p], acc[t][p], 0, 0, 0);
+            }
+        }
+        __builtin_amdgcn_sched_barrier(0);
+    };
+    fetch(i0, s_b0); fetch(i0 + 1, s_b1); fetch(i0 + 2, s_b2);
+    for (uint32_t i = i0; i < i1; i += 4) {
+        step(i, s_b0, s_b3);
+        step(i + 1, s_b1, s_b0);
+        step(i + 2, s_b2, s_b1);
+        step(i + 3, s_b3, s_b2);
+    }
+    __builtin_amdgcn_s_waitcnt(0x0F70);                                     // no load into LDS is in flight at the end
+
+    if (col > n || !live) return;
+#pragma unroll
+    for (int t = 0; t < KSM_TILES; t++) {
+#pragma unroll
+        for (int r = 0; r < 16; r++) {
+            const uint32_t row = 8 * (r / 4) + 4 * half + (r % 4);
+            const uint32_t g = (tile0 + t) * 32 + row;
+            if (g >= gates) continue;
+            const uint32_t v = (uint32_t)acc[t][0][r] + ((uint32_t)acc[t][1][r] << 8) + ((uint32_t)acc[t][2][r] << 16) +
+                               ((uint32_t)acc[t][3][r] << 24);
+            atomicAdd(ct_ptr(cs, out_ids[g]) + col, 0u - v);
+        }
+    }
+}
+
 // ------------------------------------------------------------------------------------------
 // Pool plumbing
 // ------------------------------------------------------------------------------------------
@@ -2091,6 +2185,11 @@ hipError_t launch_key_switch(const she_params &P, const DeviceKeys &K, const CtS
         const unsigned gate_blocks = (unsigned)((gates + per_block - 1) / per_block);
         const unsigned col_tiles = K.ks_cols / 32;
         const unsigned split = key_switch_split(P.N, gates, gate_blocks, col_tiles, K.cus);
+        if (gates <= KSF_GATES && P.N / split <= KSF_STEPS) {
+            hipLaunchKernelGGL(k_key_switch_few, dim3(col_tiles, split), dim3(64 * KSM_WAVES), 0, st, cs, K.ks_bytes, K.ks_cols,
+                               W.ksd, d_out, P.N, P.n, (uint32_t)gates, P.N / split);
+            return hipGetLastError();
+        }
         const dim3 grid(gate_blocks, col_tiles, split);
         hipLaunchKernelGGL(k_key_switch_mfma, grid, dim3(64 * KSM_WAVES), 0, st, cs, K.ks_bytes, K.ks_cols, W.ksd, d_out,
                            P.N, P.n, (uint32_t)gates, P.N / split);              // N / split: a power of two >= 8
