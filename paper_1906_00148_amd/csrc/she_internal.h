@@ -79,8 +79,13 @@ inline void fill_cmux_ids(CmuxIds &ids, const uint32_t *sel, const uint32_t *in1
 hipError_t launch_cmux(const she_params &P, const DeviceKeys &K, const double2 *trgsw_hat, uint32_t *trlwe,
                        const uint32_t *sel, const uint32_t *in1, const uint32_t *in0, const uint32_t *out, size_t count,
                        unsigned *d_round_err, hipStream_t st);
-// samples ids[0 .. count) of the pool -> d_dst [count][2][N] in the order of their coefficients
-hipError_t launch_trlwe_gather(const uint32_t *trlwe, uint32_t *d_dst, const uint32_t *d_ids, size_t count, uint32_t N,
+// Reads of so few samples have their ids in the kernel's arguments: 1 KB of the 4 that HIP takes.
+constexpr size_t GATHER_ARG_IDS = 256;
+struct GatherIds { uint32_t id[GATHER_ARG_IDS]; };
+inline bool gather_ids_in_arguments(size_t count) { return count <= GATHER_ARG_IDS; }
+// samples ids[0 .. count) of the pool -> d_dst [count][2][N] in the order of their coefficients; the list: host memory, read
+// before the call returns, if gather_ids_in_arguments(count); device memory if not
+hipError_t launch_trlwe_gather(const uint32_t *trlwe, uint32_t *d_dst, const uint32_t *ids, size_t count, uint32_t N,
                                hipStream_t st);
 // d_in2 may be null when no type is a three-input gate
 hipError_t launch_lincomb(const she_params &P, const CtSpace &cs, const uint8_t *d_type, const uint32_t *d_in0,

@@ -182,8 +182,12 @@ try {
     uint32_t *d_ids = c->d_stage + step * words;
     for (size_t off = 0; off < count; off += step) {
         const size_t cnt = std::min(step, count - off);
-        HIP_TRY(c, hipMemcpyAsync(d_ids, ids + off, cnt * 4, hipMemcpyHostToDevice, c->stream));
-        HIP_TRY(c, launch_trlwe_gather(c->lev.trlwe, c->d_stage, d_ids, cnt, N, c->stream));
+        const uint32_t *list = ids + off;
+        if (!gather_ids_in_arguments(cnt)) {
+            HIP_TRY(c, hipMemcpyAsync(d_ids, list, cnt * 4, hipMemcpyHostToDevice, c->stream));
+            list = d_ids;
+        }
+        HIP_TRY(c, launch_trlwe_gather(c->lev.trlwe, c->d_stage, list, cnt, N, c->stream));
         HIP_TRY(c, hipMemcpyAsync(samples + off * words, c->d_stage, cnt * words * 4, hipMemcpyDeviceToHost, c->stream));
         HIP_TRY(c, hipStreamSynchronize(c->stream));
     }
