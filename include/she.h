@@ -230,15 +230,17 @@ int she_get_option(she_ctx *ctx, int option, int *value);   /* SHE_EINVAL for an
 /* SHE_OPT_SPLIT_BELOW (default: 6 x the device's compute units, 1536 on MI355X): a kernel launch of at
  * most this many blind rotations spreads each one over two wavefronts (one per accumulator component),
  * which shortens the serial chain per CMux when the level is too small to fill the chip; larger launches
- * keep one wavefront per rotation.  0 never splits.  At N = 1024 with l = 3 there are three more forms:
+ * keep one wavefront per rotation.  0 never splits.  At N = 1024 with l = 3 there are four more forms:
  *  - a launch of at most this many rotations and at most one per compute unit spreads each one over twelve
  *    wavefronts (one per digit, component and half of the spectrum), and compute units left idle read the key ahead; such a
  *    rotation needs a compute unit to itself, so launches of several contexts share the chip by compute units;
  *  - one of at most this many and at most two per compute unit spreads each over four wavefronts (one per component
  *    and half of the spectrum);
+ *  - one of at most this many and of two to three per compute unit runs as one rotation on four and two on two wavefronts
+ *    each on every compute unit;
  *  - a launch of more than four per compute unit, larger than this option or not, keeps full rounds of four per
- *    compute unit on one wavefront each and runs the rest on four each, if the rest is at most two per compute
- *    unit and at most this many rotations.
+ *    compute unit on one wavefront each and runs a rest of at most this many rotations on several each: on four up to
+ *    one per compute unit, on two up to two, and beyond two rounds or more up to three as above.
  * Every ciphertext comes out the same word for word either way (all kernels round exact integers). */
 /* SHE_OPT_COLUMN_ADDER (default 0; needs SHE_OPT_FOLD_CONSTANTS and SHE_OPT_GATE3_CELLS, else she_shift_acc returns
  * SHE_EINVAL): she_shift_acc sums by column compression instead of adder trees and a subtraction (Section 3.3: adders
