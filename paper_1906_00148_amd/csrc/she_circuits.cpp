@@ -192,7 +192,6 @@ void Netlist::bind_outputs(const std::vector<uint32_t> &wires, const uint32_t *d
     for (auto &w : copy_src) fix(w);
 }
 
-// Must run before bind_outputs (every gate output is still a temporary wire).
 double level_time(uint64_t rotations, uint32_t cus)
 {
     if (!rotations) return 0;
@@ -301,6 +300,7 @@ void Netlist::even_levels(std::vector<uint32_t> &lev, uint32_t deepest, uint32_t
     if (time < least) lev = tried;
 }
 
+// Must run before bind_outputs (every gate output is still a temporary wire).
 std::vector<size_t> Netlist::levelize(std::vector<size_t> *mux_start, uint32_t cus)
 {
     // depth of a wire = 0 for inputs and constants, else 1 + deepest operand; entries were
