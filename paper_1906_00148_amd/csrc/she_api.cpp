@@ -149,9 +149,9 @@ int ensure_raw(she_ctx *c, size_t jobs)
 }
 
 // Enqueues one level: `gates` jobs of a gate each, then two jobs for each of `muxes` MUX entries (device arrays of
-// gates + 2 muxes jobs, d_out of gates + muxes ids).  All its rotations run in one launch where the scratch holds them, so that
-// a level of 96 gates and 416 MUXes takes as long as 928 rotations and not 1.7 ms more; otherwise in chunks of at most the
-// scratch's size, gates first.  `W` is the level's scratch (the context's own buffers, or the caller-free static buffer);
+// gates + 2 muxes jobs, d_out of gates + muxes ids).  Where the scratch holds them all its rotations run in one launch, so that
+// a level of 96 gates and 416 MUXes takes as long as 928 rotations and not 1.7 ms more, or in two where launches_apart knows
+// that to be shorter; otherwise in chunks of at most the scratch's size, gates first.  `W` is the level's scratch (the context's own buffers, or the caller-free static buffer);
 // `timed` records HIP events around the kernels (creating an event allocates, so the entry point that must not allocate
 // passes false).
 int enqueue_level_on(she_ctx *c, LevelWork W, bool timed, const uint8_t *d_type, const uint32_t *d_in0,
@@ -174,8 +174,15 @@ int enqueue_level_on(she_ctx *c, LevelWork W, bool timed, const uint8_t *d_type,
         HIP_TRY(c, launch_lincomb(c->P, cs, d_type + off, d_in0 + off, d_in1 + off, d_in2 ? d_in2 + off : nullptr, cnt, W,
                                   c->stream));
         if (timer) HIP_TRY(c, timer->mark(c->stream));
-        HIP_TRY(c, launch_blind_rotate(c->P, c->dk, cs, direct ? d_out + entry : nullptr, cnt, W,
-                                       c->track_round ? c->d_round_err : nullptr, c->stream, pairs > 0, c->split_below));
+        // a launch for the MUXes alone has all its rotations write samples, none digits
+        const size_t alone = launches_apart(c->P, direct, 2 * pairs, c->dk.cus, c->split_below) ? direct : 0;
+        unsigned *const track = c->track_round ? c->d_round_err : nullptr;
+        LevelWork rest = W;
+        rest.bar += alone * W.bar_stride;
+        rest.direct -= alone;
+        if (alone) HIP_TRY(c, launch_blind_rotate(c->P, c->dk, cs, d_out + entry, alone, W, track, c->stream, false, c->split_below));
+        HIP_TRY(c, launch_blind_rotate(c->P, c->dk, cs, direct > alone ? d_out + entry : nullptr, cnt - alone, rest, track,
+                                       c->stream, pairs > 0, c->split_below));
         if (timer) HIP_TRY(c, timer->mark(c->stream));
         if (pairs) HIP_TRY(c, launch_mux_combine(c->P, c->dk, cs, d_out + entry, pairs, W, c->stream));
         HIP_TRY(c, launch_key_switch(c->P, c->dk, cs, d_out + entry, direct + pairs, W, c->stream));
@@ -244,7 +251,7 @@ int run_netlist(she_ctx *c, Netlist &nl, const std::vector<uint32_t> &out_wires,
     std::vector<size_t> mux_start, bounds;
     // The levels are evened out where level_time knows their kernels; what waits may keep more wires alive, and where there is
     // no memory for them the entries run as early as they can.
-    const bool even = c->P.N == 1024 && c->P.l == 3 && c->split_below >= 6 * (size_t)c->dk.cus;
+    const bool even = level_time_holds(c->P, c->dk.cus, c->split_below);
     Netlist earliest(0);
     if (even) earliest = nl;
     int rc = SHE_OK;

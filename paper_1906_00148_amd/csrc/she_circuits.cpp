@@ -192,32 +192,73 @@ void Netlist::bind_outputs(const std::vector<uint32_t> &wires, const uint32_t *d
     for (auto &w : copy_src) fix(w);
 }
 
+constexpr double LEVEL_OTHER = 100;        // us of a level's kernels besides the blind rotation
+
 double level_time(uint64_t rotations, uint32_t cus)
 {
     if (!rotations) return 0;
     struct Point { double per_cu, us; };
-    static const Point small[] = {{0, 1700}, {1, 1850}, {1, 3350}, {2, 3500}, {2, 3950}, {3, 4050}, {3, 5500}, {4, 5850},
-                                  {4, 6100}, {5, 6900}, {5, 7200}, {6, 7650}, {6, 10000}, {8, 10350}};
-    constexpr double OTHER = 100, ROUND = 5050;                       // a round: four rotations per compute unit
+    static const Point up_to_16[] = {{0, 1700}, {1, 1850}, {1, 3350}, {2, 3500}, {2, 3950}, {3, 4050}, {3, 5500}, {4, 5850},
+                                     {4, 6100}, {5, 6900}, {5, 7200}, {6, 7650}, {6, 9750}, {8, 10350}, {8, 11950}, {9, 12000},
+                                     {9, 13750}, {10, 13750}, {10, 14600}, {11, 14600}, {11, 16050}, {13, 16050}, {13, 17950},
+                                     {14, 17950}, {14, 19750}, {15, 19750}, {15, 20050}, {16, 20050}};
+    constexpr double FOUR_ROUNDS = 20050, ROUND = 4900;               // a round: four rotations per compute unit
     const double per_cu = (double)rotations / cus;
-    if (per_cu <= 8) {
+    if (per_cu <= 16) {
         size_t k = 1;
-        while (small[k].per_cu < per_cu) k++;
-        const Point &a = small[k - 1], &b = small[k];
-        return OTHER + a.us + (b.us - a.us) * (per_cu - a.per_cu) / (b.per_cu - a.per_cu);
+        while (up_to_16[k].per_cu < per_cu) k++;
+        const Point &a = up_to_16[k - 1], &b = up_to_16[k];
+        return LEVEL_OTHER + a.us + (b.us - a.us) * (per_cu - a.per_cu) / (b.per_cu - a.per_cu);
     }
     const uint64_t rounds = rotations / (4 * (uint64_t)cus);
     const double rest = per_cu - 4.0 * rounds;
-    const bool odd = rounds & 1;
-    const double add = rest <= 0 ? 0 : rest <= 1 ? 1600 : rest <= 2 ? (odd ? 2200 : 3300) : rest <= 3 ? (odd ? 3800 : 4300) : ROUND;
-    return OTHER + ROUND * rounds + add;
+    const double add = rest <= 0 ? 0 : rest <= 1 ? 900 : rest <= 2 ? 2700 : rest <= 3 ? 3600 : ROUND;
+    return LEVEL_OTHER + FOUR_ROUNDS + ROUND * (rounds - 4) + add;
+}
+
+double level_time(uint64_t gates, uint64_t mux_rotations, uint32_t cus)
+{
+    const double one = level_time(gates + mux_rotations, cus);
+    if (!gates || !mux_rotations) return one;
+    return std::min(one, level_time(gates, cus) + level_time(mux_rotations, cus) - LEVEL_OTHER);
+}
+
+// What a launch takes at other parameters than level_time's, in hundredths of two full rounds on one wavefront per rotation:
+// up to one, two .. six rotations per compute unit on two wavefronts each, one full round, three, four, and what every further
+// one adds.  Measured at n = 630 on 256 compute units, where two rounds take 7.9 ms (N = 1024, l = 2), 6.1 (512, l = 3), 4.85
+// (256, l = 3); the sets are apart by up to 15 % of these, and by 3 % from one gadget length to the next.
+static double launch_time(const she_params &P, uint64_t rotations, uint32_t cus, size_t split_below)
+{
+    struct Times { double several[6], one_round, three, four, round; };
+    static const Times n1024 = {{33, 40, 50, 59, 87, 94}, 61, 160, 196, 47.5}, n512_l3 = {{30, 38, 46, 54, 78, 91}, 63, 150, 200.5, 46},
+                       n512 = {{32.5, 38, 49, 57, 75, 84}, 63, 150, 200.5, 46}, n256_l3 = {{27, 32, 43, 51, 64, 74}, 70, 143.5, 188.5, 45},
+                       n256 = {{34, 38, 48, 56, 70, 80}, 70, 143.5, 188.5, 45};
+    const Times &T = P.N == 1024 ? n1024 : P.N == 512 ? (P.l == 3 ? n512_l3 : n512) : P.l == 3 ? n256_l3 : n256;
+    if (rotations <= std::min<uint64_t>(split_below, 6 * (uint64_t)cus)) return T.several[(rotations - 1) / cus];
+    const uint64_t rounds = (rotations - 1) / (4 * (uint64_t)cus) + 1;
+    return rounds == 1 ? T.one_round : rounds == 2 ? 100 : rounds == 3 ? T.three : T.four + T.round * (rounds - 4);
+}
+
+bool level_time_holds(const she_params &P, uint32_t cus, size_t split_below)
+{
+    return P.N == 1024 && P.l == 3 && split_below >= 6 * (size_t)cus;
+}
+
+bool launches_apart(const she_params &P, uint64_t gates, uint64_t mux_rotations, uint32_t cus, size_t split_below)
+{
+    if (!gates || !mux_rotations || !cus) return false;
+    if (P.N == 1024 && P.l == 3)
+        return level_time_holds(P, cus, split_below) && level_time(gates, mux_rotations, cus) < level_time(gates + mux_rotations, cus);
+    return launch_time(P, gates, cus, split_below) + launch_time(P, mux_rotations, cus, split_below) <
+           launch_time(P, gates + mux_rotations, cus, split_below);
 }
 
 // List scheduling: at each level the entries that are ready, the ones that can wait least first, up to the count where the
 // level's time less the worth of the rotations is least; the counts tried are what has to run now, multiples of the compute
 // units, and everything.  A rotation run now is taken to save 0.7 of what it costs in a full round: what can wait does, and
-// runs where a later level has room, or as its last.  (A 576-term neuron 60.4 ms at the earliest levels, 56.0 / 56.7 / 56.7 ms
-// with 0.6 to 0.8 / 1.0 / 1.2; a 10 x 10 x 4 convolution with pooling 178 and 164 / 169 / 171, by the estimate.)  Where the
+// runs where a later level has room, or as its last.  (576-term neurons 61.4 ms at the earliest levels, 58.0 / 56.9 / 56.6 /
+// 56.7 ms with 0.6 / 0.7 / 1.0 / 1.2; 10 x 10 x 4 convolutions with pooling 179 and 168 / 166 / 172 / 173, by the estimate,
+// means over four sets of weights.)  Where the
 // estimate is no better the earliest levels stay.  It takes the host 1.5 to 3 ms for 26000 entries, so that circuits whose
 // levels average more than four full rounds, with nothing to gain, are left alone.
 void Netlist::even_levels(std::vector<uint32_t> &lev, uint32_t deepest, uint32_t cus) const
@@ -230,7 +271,7 @@ void Netlist::even_levels(std::vector<uint32_t> &lev, uint32_t deepest, uint32_t
     struct Entry { uint32_t ops[3], late; uint8_t inputs, weight; };
     std::vector<Entry> e(n);
     std::vector<uint32_t> first(n + 1, 0);
-    std::vector<uint64_t> size(deepest + 1, 0);
+    std::vector<uint64_t> gates(deepest + 1, 0), muxes(deepest + 1, 0);
     for (size_t g = 0; g < n; g++) {
         e[g].inputs = 0; e[g].late = deepest; e[g].weight = is_mux_type(type[g]) ? 2 : 1;
         for (uint32_t w : {in0[g], in1[g], has_third_operand(type[g]) ? in2[g] : 0u})
@@ -239,7 +280,7 @@ void Netlist::even_levels(std::vector<uint32_t> &lev, uint32_t deepest, uint32_t
                 e[g].ops[e[g].inputs++] = op;
                 first[op + 1]++;
             }
-        size[lev[g]] += e[g].weight;
+        (e[g].weight == 2 ? muxes : gates)[lev[g]]++;
     }
     for (size_t g = 0; g < n; g++) first[g + 1] += first[g];
     std::vector<uint32_t> reader(first[n]), at(first.begin(), first.end() - 1);
@@ -248,7 +289,7 @@ void Netlist::even_levels(std::vector<uint32_t> &lev, uint32_t deepest, uint32_t
     for (size_t g = n; g-- > 0;)
         for (int k = 0; k < e[g].inputs; k++) e[e[g].ops[k]].late = std::min(e[e[g].ops[k]].late, e[g].late - 1);
     double least = 0;
-    for (uint32_t lv = 1; lv <= deepest; lv++) least += level_time(size[lv], cus);
+    for (uint32_t lv = 1; lv <= deepest; lv++) least += level_time(gates[lv], 2 * muxes[lv], cus);
     const double worth = 0.7 * (level_time(64 * (uint64_t)cus, cus) - level_time(32 * (uint64_t)cus, cus)) / (32.0 * cus);
 
     struct Ready { uint32_t head, tail; uint64_t rotations; };           // entries that can run, by their latest level
@@ -278,7 +319,7 @@ void Netlist::even_levels(std::vector<uint32_t> &lev, uint32_t deepest, uint32_t
         };
         if (now < total) consider(now);
         for (uint64_t r = (now / cus + 1) * cus; r < total; r += cus) consider(r);
-        uint64_t run = 0;
+        uint64_t run = 0, mux_rotations = 0;
         fresh.clear();
         for (uint32_t l = lv; l <= deepest && run < std::max(take, now); l++) {
             Ready &r = ready[l];
@@ -287,12 +328,13 @@ void Netlist::even_levels(std::vector<uint32_t> &lev, uint32_t deepest, uint32_t
                 r.head = next[g];
                 r.rotations -= e[g].weight;
                 run += e[g].weight;
+                mux_rotations += e[g].weight == 2 ? 2 : 0;
                 tried[g] = lv;
                 fresh.push_back(g);
             }
         }
         total -= run;
-        time += level_time(run, cus);
+        time += level_time(run - mux_rotations, mux_rotations, cus);
         for (uint32_t g : fresh)
             for (uint32_t k = first[g]; k < first[g + 1]; k++)
                 if (--waits[reader[k]] == 0) add(reader[k]);

@@ -194,10 +194,19 @@ inline bool is_mux_type(uint8_t t) { return t >= MUX_BASE && t < SHE_MAJ3; }
 inline bool has_third_operand(uint8_t t) { return t >= MUX_BASE; }     // MUX entries and three-input gates
 
 // Estimated time of a level, in microseconds at N = 1024 and l = 3, from its rotations per compute unit: the steps of the
-// kernels that launch_blind_rotate chooses, as measured at n = 630 on 256 compute units (a level of 256 / 512 / 768 / 1024 /
-// 1536 / 2048 rotations takes 1.85 / 3.5 / 4.05 / 5.85 / 7.65 / 10.35 ms, one rotation more 3.35 / 3.95 / 5.5 / 6.1 / 10.0 /
-// 11.9), with 0.1 ms for its other kernels.  Only ratios count, so that other key lengths are served as well.
+// kernels that launch_blind_rotate chooses, as measured at n = 630 on 256 compute units (a launch of 256 / 512 / 768 / 1024 /
+// 1536 / 2048 / 3072 / 4096 rotations takes 1.85 / 3.5 / 4.05 / 5.85 / 7.65 / 10.35 / 16.05 / 20.05 ms, one rotation more 3.35 /
+// 3.95 / 5.5 / 6.1 / 9.75 / 11.95 / 16.05 / 20.95), with 0.1 ms for its other kernels.  Only ratios count, so that other key
+// lengths are served as well.
 double level_time(uint64_t rotations, uint32_t cus);
+double level_time(uint64_t gates, uint64_t mux_rotations, uint32_t cus);       // in one launch or two: see launches_apart
+bool level_time_holds(const she_params &P, uint32_t cus, size_t split_below);  // the kernels are the ones that it knows
+// Whether the rotations of a level's gates and those of its MUXes run in two launches, one after the other, because together
+// they would take longer: where the sum just exceeds what runs on several wavefronts per rotation, or a number of full rounds.
+// Measured at n = 630 on 256 compute units, ms, one launch / two: N = 1024, l = 3: 1030 gates and 255 MUXes 9.45 / 9.30,
+// 1157 and 579 13.8 / 12.5, but 600 and 400 7.3 / 9.3; l = 2: 2048 and 64 12.4 / 11.0, 250 and 128 3.1 / 5.1; N = 512, l = 3:
+// 3000 and 40 12.3 / 11.0; N = 256, l = 3: 800 and 370 4.85 / 4.55, 2048 and 64 6.9 / 6.1, 250 and 128 1.55 / 2.6.
+bool launches_apart(const she_params &P, uint64_t gates, uint64_t mux_rotations, uint32_t cus, size_t split_below);
 struct Netlist {
     // wire ids: [0, cap) pool slots, cap = trivial 0, cap+1 = trivial 1, cap+2.. temporaries.
     // With `fold` set, a gate fixed by constant or repeated operands is not emitted: gate()

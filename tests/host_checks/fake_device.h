@@ -8,6 +8,7 @@
 #include <cstring>
 #include <functional>
 #include <map>
+#include <vector>
 
 #include "she_internal.h"
 
@@ -17,6 +18,8 @@ inline size_t held = 0, limit = ~(size_t)0;          // bytes in them, bytes the
 inline long calls = 0, fail_at = 0;                  // fallible calls so far, the one that fails (0: none)
 inline hipError_t last_error = hipSuccess;           // sticky until hipGetLastError
 inline std::function<void(const char *, size_t)> on_free;   // sees a block as it goes back
+struct Rotations { size_t count, direct; const uint16_t *bar; bool mux, out; };
+inline std::vector<Rotations> rotations;             // the launches of blind rotations so far
 
 inline hipError_t result(hipError_t e) { if (e != hipSuccess) last_error = e; return e; }
 inline hipError_t step() { return result(++calls == fail_at ? hipErrorUnknown : hipSuccess); }
@@ -89,8 +92,12 @@ hipError_t launch_cmux(const she_params &, const DeviceKeys &, const double2 *, 
                        const uint32_t *, const uint32_t *, size_t, unsigned *, hipStream_t) { return fake::step(); }
 hipError_t launch_lincomb(const she_params &, const CtSpace &, const uint8_t *, const uint32_t *, const uint32_t *,
                           const uint32_t *, size_t, const LevelWork &, hipStream_t) { return fake::step(); }
-hipError_t launch_blind_rotate(const she_params &, const DeviceKeys &, const CtSpace &, const uint32_t *, size_t,
-                               const LevelWork &, unsigned *, hipStream_t, bool, size_t) { return fake::step(); }
+hipError_t launch_blind_rotate(const she_params &, const DeviceKeys &, const CtSpace &, const uint32_t *d_out, size_t count,
+                               const LevelWork &W, unsigned *, hipStream_t, bool mux, size_t)
+{
+    fake::rotations.push_back({count, W.direct, W.bar, mux, d_out != nullptr});
+    return fake::step();
+}
 hipError_t launch_mux_combine(const she_params &, const DeviceKeys &, const CtSpace &, const uint32_t *, size_t,
                               const LevelWork &, hipStream_t) { return fake::step(); }
 hipError_t launch_key_switch(const she_params &, const DeviceKeys &, const CtSpace &, const uint32_t *, size_t,
