@@ -93,8 +93,13 @@ int ensure_temp(she_ctx *c, size_t slots)
 {
     if (slots <= c->temp_slots) return SHE_OK;
     if (c->temp) { HIP_TRY(c, hipStreamSynchronize(c->stream)); HIP_TRY(c, hipFree(c->temp)); c->temp = nullptr; c->temp_slots = 0; }
-    slots = std::max<size_t>(slots + slots / 8, 1024);
-    HIP_TRY(c, hipMalloc((void **)&c->temp, slots * c->stride * sizeof(uint32_t)));
+    const size_t spare = std::max<size_t>(slots + slots / 8, 1024);
+    auto allocate = [&](size_t count) { return hipMalloc((void **)&c->temp, count * c->stride * sizeof(uint32_t)); };
+    if (allocate(spare) == hipSuccess) slots = spare;
+    else {
+        (void)hipGetLastError();
+        HIP_TRY(c, allocate(slots));
+    }
     c->temp_slots = slots;
     // trivial ciphertexts of 0 and 1: zero mask, body -1/8 and +1/8
     std::vector<uint32_t> consts(2 * (size_t)c->stride, 0u);
@@ -146,6 +151,52 @@ int ensure_raw(she_ctx *c, size_t jobs)
     HIP_TRY(c, hipMalloc((void **)&c->work.raw_ext, jobs * (size_t)(c->P.N + 1) * sizeof(uint32_t)));
     c->work.raw_jobs = jobs;
     return SHE_OK;
+}
+
+// The sizes of the scratch that circuits run in.
+struct Scratch { size_t temp_slots, work, arrays, raw; };
+Scratch scratch_held(const she_ctx *c) { return {c->temp_slots, c->work.gates, c->d_gate_cap, c->work.raw_jobs}; }
+
+// Gives back what has changed since the context held `had`, or is incomplete; everything else stays where it is.
+int give_back(she_ctx *c, const Scratch &had)
+{
+    HIP_TRY(c, hipStreamSynchronize(c->stream));
+    const Scratch now = scratch_held(c);
+    if (now.temp_slots != had.temp_slots || !now.temp_slots) {
+        hipFree(c->temp);
+        c->temp = nullptr; c->temp_slots = 0;
+    }
+    if (now.work != had.work || !now.work) {
+        hipFree(c->work.bar); hipFree(c->work.ext_b); hipFree(c->work.ksd);
+        c->work.bar = nullptr; c->work.ext_b = nullptr; c->work.ksd = nullptr; c->work.gates = 0;
+    }
+    if (now.arrays != had.arrays || !now.arrays) {
+        hipFree(c->d_type); hipFree(c->d_in0); hipFree(c->d_in1); hipFree(c->d_in2); hipFree(c->d_out);
+        c->d_type = nullptr; c->d_in0 = c->d_in1 = c->d_in2 = c->d_out = nullptr; c->d_gate_cap = 0;
+    }
+    if (now.raw != had.raw || !now.raw) {
+        hipFree(c->work.raw_ext);
+        c->work.raw_ext = nullptr; c->work.raw_jobs = 0;
+    }
+    return SHE_OK;
+}
+
+// Makes room for a circuit: first with `need.work` rotations side by side, then, where there is no memory for all of it, with
+// `fewer`, for which levels run in chunks.  What an attempt has grown goes back before the next one, or it would hold the
+// memory that the next one needs; after the last (`last`) it stays.
+int ensure_circuit(she_ctx *c, const Scratch &need, size_t fewer, const Scratch &had, bool last)
+{
+    for (size_t work : {need.work, fewer}) {
+        int rc = ensure_temp(c, need.temp_slots);
+        if (!rc) rc = ensure_work(c, work);
+        if (!rc) rc = ensure_gate_arrays(c, need.arrays);
+        if (!rc && need.raw) rc = ensure_raw(c, need.raw);
+        if (rc != SHE_ENOMEM || (work == fewer && last)) return rc;
+        const std::string why = c->err;
+        if ((rc = give_back(c, had))) return rc;
+        if (work == fewer) return fail(c, SHE_ENOMEM, why);
+    }
+    return SHE_ENOMEM;
 }
 
 // Enqueues one level: `gates` jobs of a gate each, then two jobs for each of `muxes` MUX entries (device arrays of
@@ -240,47 +291,53 @@ bool params_supported(const she_params &P, std::string &why)
     return true;
 }
 
-// Runs a finished netlist: levelize, bind outputs, upload, per level one batch of gates and one of
-// MUX entries, copies, sync.
+// Runs a finished netlist: levelize, bind outputs, upload, one batch of gates and MUX rotations per level, copies, sync.
 int run_netlist(she_ctx *c, Netlist &nl, const std::vector<uint32_t> &out_wires, const uint32_t *out_ids,
                 uint64_t *gates_out)
 {
     if (nl.overflow) return fail(c, SHE_ERANGE, "netlist too large for 31-bit wire ids");
     const size_t G = nl.type.size();
     if (gates_out) *gates_out = G;
-    std::vector<size_t> mux_start, bounds;
-    // The levels are evened out where level_time knows their kernels; what waits may keep more wires alive, and where there is
-    // no memory for them the entries run as early as they can.
-    const bool even = level_time_holds(c->P, c->dk.cus, c->split_below);
-    Netlist earliest(0);
-    if (even) earliest = nl;
-    int rc = SHE_OK;
-    for (uint32_t cus = even ? c->dk.cus : 0;; cus = 0) {
-        bounds = nl.levelize(&mux_start, cus);
+    std::vector<size_t> mux_start, bounds, job_first;
+    size_t most_muxes = 0;
+    // The levels are evened out where level_time knows their kernels; what waits may keep more wires alive and make levels
+    // wider, and where there is no memory for them the entries run as early as they can.
+    const Scratch had = scratch_held(c);
+    Netlist earliest(0);                                    // the netlist as it was, while its levels are evened
+    for (uint32_t cus = level_time_holds(c->P, c->dk.cus, c->split_below) ? c->dk.cus : 0;; cus = 0) {
+        bounds = nl.levelize(&mux_start, cus, &earliest);
         nl.bind_outputs(out_wires, out_ids);
         // temporaries share slots by lifetime: the buffer holds the widest set of live wires, not one slot per entry
         const size_t temp_slots = nl.compact_temporaries(bounds);
         if (!temp_slots) return fail(c, SHE_EDEVICE, "internal error: a temporary lost its slot while it was live");
-        rc = ensure_temp(c, temp_slots);
-        if (rc != SHE_ENOMEM || !cus) break;
-        nl = earliest;
+        const size_t levels = bounds.size() - 1;
+        // the jobs of a level: its gates, then two rotations for every MUX entry
+        job_first.assign(levels + 1, 0);
+        size_t widest = 0, most_gates = 0;
+        most_muxes = 0;
+        c->level_gates.resize(levels);
+        c->level_muxes.resize(levels);
+        for (size_t lv = 0; lv < levels; lv++) {
+            const size_t gates = mux_start[lv] - bounds[lv], muxes = bounds[lv + 1] - mux_start[lv];
+            c->level_gates[lv] = gates;
+            c->level_muxes[lv] = muxes;
+            job_first[lv + 1] = job_first[lv] + gates + 2 * muxes;
+            widest = std::max(widest, gates + 2 * muxes);
+            most_gates = std::max(most_gates, gates);
+            most_muxes = std::max(most_muxes, muxes);
+        }
+        const bool evened = !earliest.type.empty();
+        auto chunk = [](size_t rotations) { return std::min<size_t>(rotations, MAX_LEVEL_CHUNK); };
+        // without memory for a level's gates and MUXes side by side there may be enough for one after the other
+        const int rc = ensure_circuit(c, {temp_slots, chunk(widest), std::max(job_first[levels], nl.copy_src.size()), chunk(2 * most_muxes)},
+                                      chunk(std::max(most_gates, 2 * most_muxes)), had, !evened);
+        if (!rc) break;
+        if (rc != SHE_ENOMEM || !evened) return rc;
+        std::swap(nl, earliest);
+        earliest = Netlist(0);
     }
-    if (rc) return rc;
+    earliest = Netlist(0);
     const size_t levels = bounds.size() - 1;
-    // the jobs of a level: its gates, then two rotations for every MUX entry
-    std::vector<size_t> job_first(levels + 1, 0);
-    size_t widest = 0, most_gates = 0, most_muxes = 0;
-    c->level_gates.resize(levels);
-    c->level_muxes.resize(levels);
-    for (size_t lv = 0; lv < levels; lv++) {
-        const size_t gates = mux_start[lv] - bounds[lv], muxes = bounds[lv + 1] - mux_start[lv];
-        c->level_gates[lv] = gates;
-        c->level_muxes[lv] = muxes;
-        job_first[lv + 1] = job_first[lv] + gates + 2 * muxes;
-        widest = std::max(widest, gates + 2 * muxes);
-        most_gates = std::max(most_gates, gates);
-        most_muxes = std::max(most_muxes, muxes);
-    }
     const size_t jobs = job_first[levels];
     std::vector<uint8_t> jt;
     std::vector<uint32_t> j0, j1, j2;
@@ -300,13 +357,7 @@ int run_netlist(she_ctx *c, Netlist &nl, const std::vector<uint32_t> &out_wires,
     }
     const std::vector<uint8_t> &types = most_muxes ? jt : nl.type;
     const std::vector<uint32_t> &in0 = most_muxes ? j0 : nl.in0, &in1 = most_muxes ? j1 : nl.in1, &in2 = most_muxes ? j2 : nl.in2;
-    // without memory for a level's gates and MUXes side by side there may be enough for one after the other
-    const size_t apart = std::max(most_gates, 2 * most_muxes);
-    rc = ensure_work(c, std::min<size_t>(widest, MAX_LEVEL_CHUNK));
-    if (rc == SHE_ENOMEM && apart < widest) rc = ensure_work(c, std::min<size_t>(apart, MAX_LEVEL_CHUNK));
-    if (rc) return rc;
-    if ((rc = ensure_gate_arrays(c, std::max(jobs, nl.copy_src.size())))) return rc;
-    if (most_muxes && (rc = ensure_raw(c, std::min<size_t>(2 * most_muxes, MAX_LEVEL_CHUNK)))) return rc;
+    int rc = SHE_OK;
     c->timer.clear();
     c->timer_levels = 0;
     if (G) {

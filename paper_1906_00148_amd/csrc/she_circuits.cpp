@@ -3,6 +3,7 @@
 // Section 3.2 turns multiplications by power-of-two weights into shifts that only re-wire
 // encrypted bits, Section 3.3 sums the shifted terms with a mixed-bitwidth adder tree.)
 #include <algorithm>
+#include <new>
 
 #include "she_internal.h"
 
@@ -260,8 +261,8 @@ bool launches_apart(const she_params &P, uint64_t gates, uint64_t mux_rotations,
 // 56.7 ms with 0.6 / 0.7 / 1.0 / 1.2; 10 x 10 x 4 convolutions with pooling 179 and 168 / 166 / 172 / 173, by the estimate,
 // means over four sets of weights.)  Where the
 // estimate is no better the earliest levels stay.  It takes the host 1.5 to 3 ms for 26000 entries, so that circuits whose
-// levels average more than four full rounds, with nothing to gain, are left alone.
-void Netlist::even_levels(std::vector<uint32_t> &lev, uint32_t deepest, uint32_t cus) const
+// levels average more than sixteen entries per compute unit, with nothing to gain, are left alone.
+std::vector<uint32_t> Netlist::even_levels(const std::vector<uint32_t> &lev, uint32_t deepest, uint32_t cus) const
 {
     const size_t n = type.size();
     const uint32_t first_temp = cap + 2, none = 0xFFFFFFFFu;
@@ -339,11 +340,12 @@ void Netlist::even_levels(std::vector<uint32_t> &lev, uint32_t deepest, uint32_t
             for (uint32_t k = first[g]; k < first[g + 1]; k++)
                 if (--waits[reader[k]] == 0) add(reader[k]);
     }
-    if (time < least) lev = tried;
+    if (!(time < least)) tried.clear();
+    return tried;
 }
 
 // Must run before bind_outputs (every gate output is still a temporary wire).
-std::vector<size_t> Netlist::levelize(std::vector<size_t> *mux_start, uint32_t cus)
+std::vector<size_t> Netlist::levelize(std::vector<size_t> *mux_start, uint32_t cus, Netlist *unsorted)
 {
     // depth of a wire = 0 for inputs and constants, else 1 + deepest operand; entries were
     // appended in topological order, so one pass suffices
@@ -359,7 +361,17 @@ std::vector<size_t> Netlist::levelize(std::vector<size_t> *mux_start, uint32_t c
         depth[out[g] - first_temp] = d + 1;
         deepest = std::max(deepest, d + 1);
     }
-    if (cus && type.size() <= (size_t)deepest * 16 * cus) even_levels(lev, deepest, cus);
+    if (cus && type.size() <= (size_t)deepest * 16 * cus) {
+        std::vector<uint32_t> evened;
+        try {
+            evened = even_levels(lev, deepest, cus);
+            if (unsorted && !evened.empty()) *unsorted = *this;
+        } catch (const std::bad_alloc &) {                             // no memory on the host for it: the earliest levels
+            evened.clear();
+            if (unsorted) *unsorted = Netlist(0);
+        }
+        if (!evened.empty()) lev.swap(evened);
+    }
     // bucket = 2*level + (1 for a MUX entry): gates of a level come before its MUX entries
     std::vector<size_t> start(2 * (size_t)deepest + 3, 0);
     auto bucket = [&](size_t g) { return 2 * (size_t)lev[g] + (is_mux_type(type[g]) ? 1 : 0); };

@@ -240,11 +240,13 @@ struct Netlist {
     void bind_outputs(const std::vector<uint32_t> &wires, const uint32_t *dst);
     // stable sort of the entries by (depth, gates before MUX entries); returns the first index of each
     // level (+ end); mux_start[lv] receives the index of level lv's first MUX entry.  With cus > 0 the levels, no more of them,
-    // are evened out for a device of that many compute units: see even_levels.
-    std::vector<size_t> levelize(std::vector<size_t> *mux_start = nullptr, uint32_t cus = 0);
-    // Moves entries that later levels have time for out of levels that they only just push over a step of level_time.
-    // `lev`: the earliest level of every entry, 1 .. deepest, the entries still in topological order.
-    void even_levels(std::vector<uint32_t> &lev, uint32_t deepest, uint32_t cus) const;
+    // are evened out for a device of that many compute units (see even_levels); if they are, *unsorted receives the netlist as
+    // it was, for a caller that may have to fall back on the earliest levels.
+    std::vector<size_t> levelize(std::vector<size_t> *mux_start = nullptr, uint32_t cus = 0, Netlist *unsorted = nullptr);
+    // Levels that move entries for which later ones have time out of levels that they only just push over a step of level_time;
+    // empty where the estimate gains nothing.  `lev`: the earliest level of every entry, 1 .. deepest, the entries still in
+    // topological order.
+    std::vector<uint32_t> even_levels(const std::vector<uint32_t> &lev, uint32_t deepest, uint32_t cus) const;
     // after levelize and bind_outputs: re-numbers the remaining temporaries so that slots are reused once their last
     // reader's level has run; `bounds` are levelize's.  Returns the slots needed (constants included), 0 on an
     // internal inconsistency.
