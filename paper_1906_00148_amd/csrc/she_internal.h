@@ -111,6 +111,15 @@ inline MixedBlocks mixed_blocks(size_t gates, uint32_t cus, size_t split_below)
     b.waves = (uint32_t)(rounds * cus);
     return b;
 }
+// Which kernel a launch of that many rotations gets at N = 1024 with l = 3 (measured beside each of them).
+enum class RotationKernel { WIDE, QUAD, SPLIT, MIXED, WAVES };
+inline RotationKernel rotation_kernel(size_t gates, uint32_t cus, size_t split_below)
+{
+    const MixedBlocks b = mixed_blocks(gates, cus, split_below);
+    if (b.pairs + b.quads) return RotationKernel::MIXED;
+    if (gates > split_below) return RotationKernel::WAVES;
+    return gates <= cus ? RotationKernel::WIDE : gates <= 2 * (size_t)cus ? RotationKernel::QUAD : RotationKernel::SPLIT;
+}
 hipError_t launch_blind_rotate(const she_params &P, const DeviceKeys &K, const CtSpace &cs, const uint32_t *d_out,
                                size_t gates, const LevelWork &W, unsigned *d_round_err /* nullptr = no tracking */,
                                hipStream_t st, bool mux = false /* rotations from W.direct on write W.raw_ext instead of digits

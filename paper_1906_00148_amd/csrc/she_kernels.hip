@@ -2091,9 +2091,10 @@ static hipError_t blind_rotate_t(const she_params &P, const DeviceKeys &K, size_
     const uint32_t ks_bits = P.ks_t * P.ks_basebit;
     const bool split = gates <= split_below;
     if constexpr (PL::N == HalfPlan::N) {
-        // this kernel and the next are built for three digits per coefficient only
-        const MixedBlocks blocks = P.l == 3 ? mixed_blocks(gates, K.cus, split_below) : MixedBlocks{};
-        if (blocks.pairs + blocks.quads) {
+        // these three kernels are built for three digits per coefficient only
+        const RotationKernel kernel = P.l == 3 ? rotation_kernel(gates, K.cus, split_below) : RotationKernel::WAVES;
+        if (kernel == RotationKernel::MIXED) {
+            const MixedBlocks blocks = mixed_blocks(gates, K.cus, split_below);
             const dim3 grid(blocks.waves + blocks.pairs + blocks.quads);
 #define SHE_LAUNCH_MIXED(TRACK, PAIRS)                                                                                \
     hipLaunchKernelGGL((k_blind_rotate_mixed<TRACK, 3, PAIRS>), grid, dim3(64 * BR_WAVES), 0, st, W.bar, W.bar_stride, \
@@ -2106,7 +2107,7 @@ static hipError_t blind_rotate_t(const she_params &P, const DeviceKeys &K, size_
             return hipGetLastError();
         }
         // up to one gate per compute unit: twelve wavefronts per gate (measured beside the kernel)
-        if (split && P.l == 3 && gates <= K.cus) {
+        if (kernel == RotationKernel::WIDE) {
 #define SHE_LAUNCH_WIDE(TRACK)                                                                                        \
     hipLaunchKernelGGL((k_blind_rotate_wide<TRACK>), dim3(K.cus), dim3(768), 0, st, W.bar, W.bar_stride, P.n,         \
                        P.bg_bit, K.bk_hat, K.half_twiddles, ks_bits, W.ext_b, W.ksd, (uint32_t)gates, d_round_err,    \
@@ -2116,7 +2117,7 @@ static hipError_t blind_rotate_t(const she_params &P, const DeviceKeys &K, size_
             return hipGetLastError();
         }
         // up to two gates per compute unit: four wavefronts per gate (measured beside the kernel)
-        if (split && P.l == 3 && gates <= 2 * (size_t)K.cus) {
+        if (kernel == RotationKernel::QUAD) {
 #define SHE_LAUNCH_QUAD(TRACK)                                                                                        \
     hipLaunchKernelGGL((k_blind_rotate_quad<TRACK, 3>), dim3((unsigned)gates), dim3(256), 0, st, W.bar, W.bar_stride, \
                        P.n, P.bg_bit, K.bk_hat, K.half_twiddles, ks_bits, W.ext_b, W.ksd, d_round_err, cs, d_out, raw)

@@ -1,6 +1,7 @@
 // The level scheduler (she_circuits.cpp: levelize, even_levels) on the host: whatever the circuit and the device, evened levels
 // hold every entry once, each after its operands, in as many levels as the circuit is deep, none empty, MUXes behind gates, and
-// their estimated time is at most that of the earliest levels; level_time grows with the level up to its steps and beyond.
+// their estimated time is at most that of the earliest levels; circuits with room to gain gain it, and ones without stay as they
+// are; level_time grows with the level and steps where the launch gets another kernel or another division among its forms.
 #include <chrono>
 #include <cstdio>
 #include <random>
@@ -32,9 +33,9 @@ static double estimate(const Netlist &nl, const std::vector<size_t> &bounds, uin
 {
     double us = 0;
     for (size_t lv = 0; lv + 1 < bounds.size(); lv++) {
-        uint64_t r = 0;
-        for (size_t g = bounds[lv]; g < bounds[lv + 1]; g++) r += is_mux_type(nl.type[g]) ? 2 : 1;
-        us += level_time(r, cus);
+        uint64_t gates = 0, muxes = 0;
+        for (size_t g = bounds[lv]; g < bounds[lv + 1]; g++) (is_mux_type(nl.type[g]) ? muxes : gates)++;
+        us += level_time(gates, 2 * muxes, cus);
     }
     return us;
 }
@@ -70,9 +71,61 @@ static void check(const Netlist &nl, uint32_t cus, const char *what)
     CHECK(even.compact_temporaries(b1) > 0, "%s: a temporary lost its slot\n", what);
 }
 
+// `wide` entries that nobody reads beside a chain of `depth`: with more of them than the first level has room for
+static Netlist slack(uint32_t wide, uint32_t depth, bool muxes)
+{
+    Netlist nl(8, false, true);
+    uint32_t w = nl.gate(SHE_AND, 0, 1);
+    for (uint32_t k = 1; k < depth; k++) w = nl.gate(SHE_OR, w, k % 8);
+    for (uint32_t k = 0; k < wide; k++)
+        if (muxes) nl.mux(k % 8, (k + 1) % 8, (k + 2) % 8);
+        else nl.gate(SHE_AND, k % 8, (k + 3) % 8);
+    return nl;
+}
+
+// evened levels must take less than `share` of the earliest ones' time, and hand out the netlist as it was
+static void gains(const Netlist &nl, uint32_t cus, double share, const char *what)
+{
+    Netlist early = nl, even = nl, unsorted(0);
+    const std::vector<size_t> b0 = early.levelize(), b1 = even.levelize(nullptr, cus, &unsorted);
+    const double t0 = estimate(early, b0, cus), t1 = estimate(even, b1, cus);
+    CHECK(b1 != b0 && t1 < share * t0, "%s: %.0f us at the earliest, %.0f evened\n", what, t0, t1);
+    CHECK(unsorted.type == nl.type && unsorted.in0 == nl.in0 && unsorted.in1 == nl.in1 && unsorted.in2 == nl.in2 &&
+          unsorted.out == nl.out && unsorted.next_temp == nl.next_temp, "%s: not the netlist as it was\n", what);
+}
+
+static void gains_nothing(const Netlist &nl, uint32_t cus, const char *what)
+{
+    Netlist early = nl, even = nl, unsorted(0);
+    const std::vector<size_t> b0 = early.levelize(), b1 = even.levelize(nullptr, cus, &unsorted);
+    CHECK(b1 == b0 && even.out == early.out && unsorted.type.empty(), "%s: moved entries\n", what);
+}
+
+// what a launch runs: kernel, full rounds, and the forms beside them
+struct Form {
+    RotationKernel kernel; uint32_t waves; bool pairs, quads; uint64_t rounds;
+    bool operator!=(const Form &o) const
+    {
+        return kernel != o.kernel || waves != o.waves || pairs != o.pairs || quads != o.quads || rounds != o.rounds;
+    }
+};
+static Form form(uint64_t r, uint32_t cus)
+{
+    const MixedBlocks b = mixed_blocks(r, cus, 6 * (size_t)cus);
+    const RotationKernel kernel = rotation_kernel(r, cus, 6 * (size_t)cus);
+    return {kernel, b.waves, b.pairs > 0, b.quads > 0, kernel == RotationKernel::WAVES ? (r - 1) / (4 * (uint64_t)cus) : 0};
+}
+
 int main()
 {
     std::mt19937 rng(7);
+    gains(slack(300, 6, false), 256, 0.9, "300 gates beside a chain");                   // 3.4 ms and five of 1.8 -> six of 1.8
+    gains(slack(780, 12, false), 256, 0.9, "780 gates beside a chain");
+    gains(slack(150, 6, true), 256, 0.9, "150 MUXes beside a chain");
+    gains(slack(75, 6, false), 64, 0.9, "75 gates beside a chain on 64 compute units");
+    gains_nothing(slack(255, 6, false), 256, "a level of one gate per compute unit");
+    gains_nothing(slack(300, 1, false), 256, "one level");
+    gains_nothing(slack(40000, 2, false), 256, "levels of many rounds");
     check(Netlist(4), 256, "empty");
     for (uint32_t cus : {1u, 4u, 64u, 256u})
         for (size_t entries : {1, 2, 17, 300, 3000})
@@ -86,6 +139,14 @@ int main()
         for (uint64_t r = 1; r < 40 * (uint64_t)cus; r++)
             CHECK(level_time(r, cus) > 0 && (level_time(r + 4 * (uint64_t)cus, cus) > level_time(r, cus)), "%llu rotations on %u\n",
                   (unsigned long long)r, cus);
+    for (uint32_t cus : {64u, 256u, 304u})
+        for (uint64_t r = 1; r < 40 * (uint64_t)cus; r++) {
+            const double up = level_time(r + 1, cus) - level_time(r, cus);
+            const bool changes = form(r, cus) != form(r + 1, cus);
+            CHECK(up >= 0, "%llu rotations on %u: less for one more\n", (unsigned long long)r, cus);
+            CHECK(up < 100 || changes, "%llu rotations on %u: a step of %.0f us within one form\n", (unsigned long long)r, cus, up);
+            CHECK(up > 200 || !changes || r > 6 * (uint64_t)cus, "%llu rotations on %u: no step to another form\n", (unsigned long long)r, cus);
+        }
     std::printf("failures %d\n", failures);
     Netlist big = circuit(rng, 8, 26000, 4000, true);
     const auto t0 = std::chrono::steady_clock::now();

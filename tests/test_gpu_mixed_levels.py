@@ -1,6 +1,7 @@
 """Levels that k_blind_rotate_mixed runs in pairs (two wavefronts per rotation, two rotations per workgroup), alone and beside
 the other forms, give the same ciphertext words as one wavefront per rotation (SHE_OPT_SPLIT_BELOW = 0), whose words are the
-oracle's (test_gpu_launch_sizes.py): the first and last size of each division on 256 compute units, with a last pair of one."""
+oracle's (test_gpu_launch_sizes.py): the first and last size of each division on 256 compute units, with a last pair of one.
+(That these launches have pairs at all: test_host_mixed.py.)"""
 import numpy as np
 import pytest
 
