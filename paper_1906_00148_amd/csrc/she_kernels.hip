@@ -271,7 +271,8 @@ __global__ __launch_bounds__(64 * BR_WAVES, 2) void k_blind_rotate(
 // ------------------------------------------------------------------------------------------
 // Blind rotation of a small level on two wavefronts per gate, one or two gates per workgroup: at N = 1024 with l = 3 levels
 // of more than three and at most four gates per compute unit, and two gates at a time k_blind_rotate_mixed's pairs
-// (k_blind_rotate_wide and k_blind_rotate_quad have the smaller levels, k_blind_rotate_mixed the others), at other parameters levels of up to six (SHE_OPT_SPLIT_BELOW's default).
+// (k_blind_rotate_wide and k_blind_rotate_quad have the smaller levels, k_blind_rotate_mixed the others), at other parameters
+// levels of up to six (SHE_OPT_SPLIT_BELOW's default).
 // A level of a few hundred gates leaves most SIMDs with one wavefront or none, and the time of
 // the kernel above is then the latency of one wavefront's serial chain of 6 forward and 2
 // inverse transforms per CMux.  Here wavefront c of a gate owns accumulator component c: it
@@ -510,8 +511,9 @@ __global__ __launch_bounds__(128 * GB, 2) void k_blind_rotate_split(
 }
 
 // ------------------------------------------------------------------------------------------
-// Blind rotation of a level of more than one and at most two gates per compute unit, and of the rest of a larger one beyond
-// full rounds (k_blind_rotate_mixed): one gate per workgroup of four wavefronts (N = 1024, l = LR).  What bounds such a level
+// Blind rotation of a level of more than one and at most two gates per compute unit, and of parts of larger ones (in
+// k_blind_rotate_mixed: a rest of at most one gate per compute unit beyond full rounds, and one gate per compute unit beside
+// pairs): one gate per workgroup of four wavefronts (N = 1024, l = LR).  What bounds such a level
 // is the length of one gate's chain of n CMuxes, so the chain is cut as far as the transforms allow without a wavefront
 // waiting for another inside one.
 // Wavefront (c, h) owns accumulator component c and half h of the spectrum (HalfLanes): it cuts the digits of all of
@@ -528,8 +530,8 @@ __global__ __launch_bounds__(128 * GB, 2) void k_blind_rotate_split(
 // compute unit take 5.4 us: the vector ALU is busy 72 % of it, and wavefronts wait to issue LDS instructions a tenth of it (a
 // fifth with the last exchange through LDS as well).
 // Measured at n = 630, ms per launch of 300 / 512 gates: 3.4 / 3.65 (3.45 / 3.85 with the last exchange through LDS as well)
-// against 3.9 / 4.0 of k_blind_rotate_split; beyond two gates per compute unit that kernel is the faster one (700 gates:
-// 5.2 against 4.9; three quads per compute unit on 168 registers 5.1).
+// against 3.9 / 4.0 of k_blind_rotate_split; with a third gate per compute unit quads alone are slower (700 gates: 5.2 ms, three
+// to a compute unit on 168 registers 5.1) than that kernel (4.9) and than k_blind_rotate_mixed's pair and quad (4.0).
 // ------------------------------------------------------------------------------------------
 struct QuadShared {
     uint32_t rot[2][HalfPlan::N], base[2][HalfPlan::N];
@@ -1000,7 +1002,7 @@ __global__ __launch_bounds__(768, 3) void k_blind_rotate_wide(
 //   a rest of up to two gates per compute unit, quads against pairs: 1300 gates 8.8 / 7.2, 1536 8.5 / 7.65, 2400 13.9 / 13.8,
 //   2560 13.8 / 13.7, 3584 19.4 / 17.7, 4608 22.8 / 22.6, 5600 28.0 / 27.0;
 //   up to three, as before (k_blind_rotate_split, or wavefronts) against a pair and a quad each: 514 gates 4.94 / 3.95, 768
-//   4.93 / 4.00, 2700 16.0 / 14.5, 3840 20.1 / 19.4, 4700 24.9 / 23.6, 13001 62.4 / 61.4.
+//   4.93 / 4.00, 2700 16.0 / 14.5, 3840 20.1 / 19.4, 4700 24.9 / 23.6, 13001 65.2 / 64.4.
 // A rest of more than three gates per compute unit gains nothing (3900: 20.1 / 21.5).
 template <bool TRACK, int LR, bool PAIRS>
 __global__ __launch_bounds__(256, 2) void k_blind_rotate_mixed(
